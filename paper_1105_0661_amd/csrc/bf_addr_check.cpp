@@ -9,7 +9,7 @@
 #include <thread>
 #include <vector>
 
-#include "bf_common.h"
+#include "bf_split_worker.h"
 
 namespace lbf {
 
@@ -128,7 +128,57 @@ void walk_h(Walk& w, const BlockDesc& d, int lo, int hi) {
     }
 }
 
-// items [lo, hi) of the FP32 worker
+// items [lo, hi) of the FP32 split worker (complex int8/int16 samples), its
+// residual and exact-path loads included
+void walk_split(Walk& w, const BlockDesc& d, int lo, int hi) {
+    const int bytes = sample_bytes(d.xtype);
+    const uint64_t xbuf = (uint64_t)d.S * d.C * d.T * bytes, wbuf = (uint64_t)d.C * d.B * d.S * 8;
+    const uint64_t stride64 = (uint64_t)d.C * d.T * bytes;
+    const uint32_t stride = (uint32_t)stride64;
+    if (stride != stride64) return w.fail("station stride does not fit 32 bits");
+    const int NS = split_streams(d), NK = split_ksteps(d.S), NBT = 8 / NS;
+    const int SPC = 16 / bytes, CPS = kTile / SPC, CPTILE = 8 * NK * CPS;
+    const int CPT = (NS * CPTILE + kThreadsH - 1) / kThreadsH;
+    int nbg;
+    const int items = block_items_split(d, &nbg);
+    for (int item = lo; item < std::min(hi, items) && !w.bad; ++item) {
+        const ItemPos ip = item_pos(d, item, nbg);
+        const int nsteps = (ip.ntiles + NS - 1) / NS;
+        for (int tid = 0; tid < kThreadsH; ++tid) {
+            const int lane = tid & 63, wave = tid / 64, r = lane & 31, h = lane >> 5, trow = tile_row_sample(r);
+            const int bt = wave % NBT, sigma = wave / NBT;
+            const int beam = d.b0 + (ip.bg * NBT + bt) * kTile + r;
+            for (int s = 0; s < 8 * NK; ++s) {
+                const bool ok = beam < d.b1 && s < d.S;
+                if (ok && ((uint64_t)beam * d.S + s) * 8u + 8u > weight_range(d, 8))
+                    return w.fail("weight load of beam %d station %d past its channel", beam, s);
+                w.access("weight load", weight_base(d, ip.c, 8), weight_range(d, 8),
+                         ok ? ((uint64_t)beam * d.S + s) * 8u : kNoLoad, ok ? weight_off(beam, d.S, s, 8) : kNoLoad, 8,
+                         wbuf, false);
+            }
+            // the loaders run one step ahead of the last one
+            for (int k = 0; k < nsteps + 1; ++k)
+                for (int i = 0; i < CPT; ++i) {
+                    const Chunk16 ch = h_chunk(tid + kThreadsH * i, k, NS, CPTILE, CPS, ip.tile_lo, ip.ntiles);
+                    const int s0 = ch.s & ~7, t = ch.tile * kTile + ch.q * SPC;
+                    const uint64_t o64 = (uint64_t)(ch.s & 7) * stride64 + ((uint64_t)ip.c * d.T + t) * bytes;
+                    w.access("sample load", group_base(s0, stride), group_range(s0, d.S, stride), o64,
+                             sample_off(ch.s & 7, stride, ip.c, d.T, t, bytes), 16, xbuf, false);
+                }
+            for (int k = 0; k < nsteps; ++k) {
+                const int tile = ip.tile_lo + sigma + NS * k;
+                const int t = std::min(std::min(tile, ip.tile_lo + ip.ntiles - 1) * kTile + trow, d.T - 1);
+                for (int s = 0; s < 8 * NK; ++s)
+                    w.access("sample load", group_base(s & ~7, stride), group_range(s & ~7, d.S, stride),
+                             (uint64_t)(s & 7) * stride64 + ((uint64_t)ip.c * d.T + t) * bytes,
+                             sample_off(s & 7, stride, ip.c, d.T, t, bytes), bytes, xbuf, false);
+                stores_of_tile(w, d, ip.c, beam, d.b1, tile, h, tile < ip.tile_lo + ip.ntiles);
+            }
+        }
+    }
+}
+
+// items [lo, hi) of the FP32 worker of complex float samples
 void walk_f32(Walk& w, const BlockDesc& d, int lo, int hi) {
     const int bytes = sample_bytes(d.xtype);
     const uint64_t xbuf = (uint64_t)d.S * d.C * d.T * bytes, wbuf = (uint64_t)d.C * d.B * d.S * 8;
@@ -184,7 +234,9 @@ bool check_fast_addressing(const BlockDesc& d, int threads, uint64_t* accesses, 
     if (d.ctype != CT_F32) np = split_fast_h(d, part);
     for (int p = 0; p < np; ++p) {
         int nbg;
-        items[p] = d.ctype == CT_F32 ? block_items_fast_f32(part[p], &nbg) : block_items_fast_h(part[p], &nbg);
+        items[p] = d.ctype != CT_F32        ? block_items_fast_h(part[p], &nbg)
+                   : d.xtype == XT_CF32 ? block_items_fast_f32(part[p], &nbg)
+                                        : block_items_split(part[p], &nbg);
     }
     threads = std::max(1, std::min(threads, 64));
     std::vector<Walk> w(threads * np);
@@ -195,7 +247,8 @@ bool check_fast_addressing(const BlockDesc& d, int threads, uint64_t* accesses, 
             Walk* wk = &w[p * threads + i];
             const BlockDesc* dp = &part[p];
             th.emplace_back([=] {
-                if (dp->ctype == CT_F32) walk_f32(*wk, *dp, lo, hi);
+                if (dp->ctype == CT_F32 && dp->xtype == XT_CF32) walk_f32(*wk, *dp, lo, hi);
+                else if (dp->ctype == CT_F32) walk_split(*wk, *dp, lo, hi);
                 else walk_h(*wk, *dp, lo, hi);
             });
         }

@@ -1,0 +1,406 @@
+// bf_split_worker.h -- the FP32 contraction worker for complex int8/int16
+// samples: FP32 results from FP16 matrix instructions.
+//
+// The FP32 matrix instruction runs at 1/16 of the FP16 rate.  The operands
+// of this contraction split without loss into FP16 pieces, and FP16 products
+// are exact in the FP32 accumulators:
+//  - int8 samples are FP16 numbers; an int16 sample is h + r with h its
+//    FP16 rounding and |r| <= 8, and r = 0 for every |x| <= 2048;
+//  - a weight is scaled by a power of two per beam (largest component of the
+//    beam to [2^14, 2^15)) and cut into P pieces w1 = f16(w), w2 = f16(w - w1),
+//    (w3 = f16(w - w1 - w2)).  Two pieces hold 22 bits and two signs, an error
+//    of at most one unit in the 24th bit; three pieces hold all 24 bits.  The
+//    scale leaves with the epilogue (2^-s for voltages, 2^-2s for Stokes).
+// P = 2 from 17 stations up (K-steps of 8 stations: 4 to 8), where the FP32
+// chain's own roundings, 2 S of them, are far above that error; P = 3 below
+// (2 K-steps), where they are not and the few K-steps cost little.
+// Relative rms error of the voltages against 64 bits, unit-modulus weights,
+// Gaussian int16 samples (FP32 matrix instructions -> this worker): 5.3e-8 ->
+// 2.9e-8 at 4 stations, 1.02e-7 -> 4.7e-8 at 16, 1.06e-7 -> 6.2e-8 at 17,
+// 2.03e-7 -> 9.6e-8 at 64; no station count from 1 to 64 is further off.
+//
+// What P pieces cannot hold takes the exact path, FP32 matrix instructions
+// over the same samples (one station each, in station order): a wave one of
+// whose beams has a weight that is not finite, or stations whose weights
+// differ in magnitude by more than 2^14 (the smallest would lose bits to the
+// FP16 range).  Sample residuals r, where a step holds any, take a second
+// accumulation straight from HBM.
+//
+// Work split as in item_h_fast: a work group of 8 waves takes one channel and
+// 8/NS beam tiles of 32, its 32-sample tiles dealt to NS streams; samples are
+// staged once per work group in LDS, a wave keeps its beam tile's weight
+// pieces in registers (16 P NK of them), one accumulator set, the two waves
+// of a SIMD staggered so that one's epilogue meets the other's MFMAs.
+#pragma once
+#include "bf_common.h"
+#include "bf_workers.h"
+
+namespace lbf {
+
+// K-steps of 8 stations and weight pieces of the split worker
+__host__ __device__ constexpr int split_ksteps(int S) { return S <= 16 ? 2 : S <= 32 ? 4 : (S + 7) / 8; }
+__host__ __device__ constexpr int split_pieces(int NK) { return NK == 2 ? 3 : 2; }
+
+// Sample streams: 4 (items of 64 beams) for at most 64 beams, where an item of
+// 128 would leave half its waves idle, else 2; complex int16 from 6 K-steps up
+// always 2 (the loaders of 4 streams beside the weight pieces would spill).
+inline int split_streams(const BlockDesc& d) {
+    if (d.b1 - d.b0 > 64) return 2;
+    return d.xtype == XT_CI16 && split_ksteps(d.S) >= 6 ? 2 : 4;
+}
+
+// Work items: (channel of [c0, c0 + nc), group of 256/NS beams, segment)
+inline int block_items_split(const BlockDesc& d, int* nbg) {
+    const int per = 8 / split_streams(d) * kTile;
+    *nbg = (d.b1 - d.b0 + per - 1) / per;
+    const int ntiles = (d.T + kTile - 1) / kTile, seg = seg_tiles(d, *nbg);
+    return d.nc * *nbg * ((ntiles + seg - 1) / seg);
+}
+
+// Smallest ratio of a beam's station weights (larger component of each) to
+// its largest one that the pieces hold to 24 bits
+constexpr float kSplitRange = 16384.0f;
+
+// An offset past every weight descriptor: the load returns zero
+constexpr uint32_t kNoLoad = 0xfffffff0u;
+
+// a if ok, else b, as a lane select the compiler keeps (a plain ?: becomes a branch around the access)
+LBF_INLINE uint32_t select_off(bool ok, uint32_t a, uint32_t b) {
+    const uint64_t m = __builtin_amdgcn_ballot_w64(ok);
+    uint32_t r;
+    __asm__("v_cndmask_b32_e64 %0, %1, %2, %3" : "=v"(r) : "v"(b), "v"(a), "s"(m));
+    return r;
+}
+
+LBF_INLINE uint32_t pack_h(_Float16 lo, _Float16 hi) {
+    const halfx2 v = {lo, hi};
+    return __builtin_bit_cast(uint32_t, v);
+}
+
+// The residuals x - f16(x) of a complex int16 value, as a packed f16 word
+LBF_INLINE uint32_t residual_i16x2(uint32_t w) {
+    const int re = (int)(int16_t)w, im = (int)(int16_t)(w >> 16);
+    return pack_h((_Float16)(float)(re - (int)(float)(_Float16)(float)re),
+                  (_Float16)(float)(im - (int)(float)(_Float16)(float)im));
+}
+
+// Stokes or voltages of one tile out of scaled accumulators (weights times
+// 2^sc): as stokes_store_cm / volt_store_cm, with the scale taken out exactly
+template <int PR, int TI>
+LBF_INLINE void split_stokes_store(const floatx16 (&acc)[4], __amdgpu_buffer_rsrc_t rs, int ld, int T2, int beam, int t0,
+                                   int h, bool ok, int sc) {
+    constexpr int NOUT = 16 / TI;
+    const int tq0 = (t0 + 16 * h) / TI;
+#pragma unroll
+    for (int o = 0; o < NOUT; ++o) {
+        float sm[4], v[4];
+        stokes_sums<PR, TI>(acc, o * TI, sm);
+        stokes_from_sums<PR>(sm, v);
+#pragma unroll
+        for (int q = 0; q < (PR == PR_IQUV ? 4 : 1); ++q) v[q] = __builtin_amdgcn_ldexpf(v[q], -2 * sc);
+        const int tq = tq0 + o;
+        stokes_store_row<PR>(v, rs, ld, tq, beam, ok && tq < T2);
+        __builtin_amdgcn_sched_barrier(0);                     // one period's temporaries at a time
+    }
+}
+
+template <int PR>
+LBF_INLINE void split_epilogue(const floatx16 (&acc)[4], __amdgpu_buffer_rsrc_t rs, int ld, int T, int t_int, int beam,
+                               int t0, int h, bool ok, int sc) {
+    if constexpr (PR == PR_VOLT) {
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            const int t = t0 + 16 * h + k;
+            const uint32_t off = store_off(ok && t < T, volt_off(beam, T, t));
+            floatx4 v;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) v[q] = __builtin_amdgcn_ldexpf(acc[q][k], -sc);
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), rs, (int)off, 0, 0);
+            if (k & 1) __builtin_amdgcn_sched_barrier(0);
+        }
+    } else {
+        switch (t_int) {                                       // uniform
+            case 1: split_stokes_store<PR, 1>(acc, rs, ld, T, beam, t0, h, ok, sc); break;
+            case 2: split_stokes_store<PR, 2>(acc, rs, ld, T / 2, beam, t0, h, ok, sc); break;
+            case 4: split_stokes_store<PR, 4>(acc, rs, ld, T / 4, beam, t0, h, ok, sc); break;
+            case 8: split_stokes_store<PR, 8>(acc, rs, ld, T / 8, beam, t0, h, ok, sc); break;
+            default: split_stokes_store<PR, 16>(acc, rs, ld, T / 16, beam, t0, h, ok, sc); break;
+        }
+    }
+}
+
+template <int XT, int PR, int NK, int NS>
+LBF_INLINE void item_f32_split(const BlockDesc& d, int item, int nbg, uint32_t* at, int* flags) {
+    typedef MfmaH<CT_F16> M;
+    typedef M::vec V;
+    typedef float float2v __attribute__((ext_vector_type(2)));
+    constexpr int P = split_pieces(NK);
+    constexpr int BYTES = sample_bytes(XT);
+    constexpr int NBT = 8 / NS;                            // beam tiles per item
+    constexpr int SPC = Chunk<XT, CT_F16>::samples;        // samples per 16-byte chunk
+    constexpr int CPS = kTile / SPC;                       // chunks per station per tile
+    constexpr int CPTILE = 8 * NK * CPS;                   // chunks per tile
+    constexpr int CPT = (NS * CPTILE + kThreadsH - 1) / kThreadsH;   // chunks per thread per step
+    const int T = d.T, S = d.S;
+    const ItemPos ip = item_pos(d, item, nbg);
+    const int c = ip.c, bg = ip.bg, tile_lo = ip.tile_lo, ntiles = ip.ntiles;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    const int r = lane & 31, h = lane >> 5;
+    const int bt = wave % NBT, sigma = wave / NBT;         // beam tile, sample stream
+    const int beam = d.b0 + (bg * NBT + bt) * kTile + r;
+    const bool beam_ok = beam < d.b1;
+    const int nsteps = (ntiles + NS - 1) / NS;
+    const uint32_t stride_bytes = (uint32_t)((size_t)d.C * T * BYTES);
+    const int T2 = PR == PR_VOLT ? T : T / d.t_int;
+    const __amdgpu_buffer_rsrc_t ors = channel_rsrc(d, c, out_channel_bytes(d, PR, T2));
+    const __amdgpu_buffer_rsrc_t wrs = weight_rsrc(d, c, 8);
+
+    // loaders, as item_h_fast's: one step ahead
+    u32x4 raw[CPT];
+    auto load_chunks = [&](int k) {
+        int tid = threadIdx.x;
+        __asm__ volatile("" : "+v"(tid));                  // addresses formed anew each step, not kept in registers
+#pragma unroll
+        for (int i = 0; i < CPT; ++i) {
+            const Chunk16 ch = h_chunk(tid + kThreadsH * i, k, NS, CPTILE, CPS, tile_lo, ntiles);
+            const __amdgpu_buffer_rsrc_t rs = group_rsrc(d.x, ch.s & ~7, S, stride_bytes);
+            const uint32_t off = sample_off(ch.s & 7, stride_bytes, c, T, ch.tile * kTile + ch.q * SPC, BYTES);
+            raw[i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)off, 0, 0));
+        }
+    };
+    auto store_chunks = [&](int k) {
+        int tid = threadIdx.x;
+        __asm__ volatile("" : "+v"(tid));
+#pragma unroll
+        for (int i = 0; i < CPT; ++i) {
+            const int j = tid + kThreadsH * i;
+            const int sg = j / CPTILE, jt = j % CPTILE, s = jt / CPS, q = jt % CPS;
+            if (NS * CPTILE % kThreadsH == 0 || j < NS * CPTILE) {
+                uint32_t* ab = at + (sg * 2 + (k & 1)) * kATileWords;
+                uint32_t big = 0u;
+#pragma unroll
+                for (int js = 0; js < SPC; ++js) {
+                    uint32_t fx, fy;
+                    Chunk<XT, CT_F16>::xy(raw[i], js, fx, fy);
+                    const int t = q * SPC + js;
+                    ab[a_word(t, 0, s)] = fx;
+                    ab[a_word(t, 1, s)] = fy;
+                }
+                if constexpr (XT == XT_CI16) {
+                    // any component outside [-2048, 2047]: x + 2048 has one of its top four bits set
+                    typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+                    const u16x2 bias = {2048, 2048};
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const uint32_t v = raw[i][e];     // a value: a bit cast of the element itself reads element 0
+                        big |= __builtin_bit_cast(uint32_t, (u16x2)(__builtin_bit_cast(u16x2, v) + bias));
+                    }
+                    if (big & 0xf000f000u) flags[(k & 1) * NS + sg] = k;
+                }
+            }
+        }
+    };
+    load_chunks(0);
+
+    // this wave's weight pieces, both variants, all K-steps; stations >= S and
+    // beams >= B as zeros.  Magnitudes are compared as integers, which orders
+    // NaN above infinity above the numbers.
+    u32x4 wr[P][NK], wi[P][NK];
+    int sc;
+    bool exact;
+    {
+        // two readings of the weights (the second from cache): the magnitudes,
+        // then the pieces, so that the raw weights never sit beside the pieces
+        auto load_w = [&](int kk, int i) {
+            const int s = 8 * kk + 4 * h + i;
+            return __builtin_bit_cast(float2v, __builtin_amdgcn_raw_buffer_load_b64(
+                wrs, (int)select_off(beam_ok && s < S, weight_off(beam, S, s, 8), kNoLoad), 0, 0));
+        };
+        uint32_t wmax = 0u, wmin = 0xffffffffu;               // wmin: the smallest non-zero magnitude minus one
+#pragma unroll
+        for (int kk = 0; kk < NK; ++kk)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float2v w = load_w(kk, i);
+                const uint32_t a = __float_as_uint(w[0]) & 0x7fffffffu, b = __float_as_uint(w[1]) & 0x7fffffffu;
+                const uint32_t m = max(a, b);
+                wmax = max(wmax, m);
+                wmin = min(wmin, m - 1u);
+            }
+        wmax = max(wmax, (uint32_t)__shfl_xor((int)wmax, 32, kWave));
+        wmin = min(wmin, (uint32_t)__shfl_xor((int)wmin, 32, kWave));
+        const float fmx = __uint_as_float(wmax), fmn = __uint_as_float(wmin + 1u);
+        const bool bad = wmax >= 0x7f800000u || (wmax != 0u && fmn * kSplitRange < fmx);
+        exact = __builtin_amdgcn_ballot_w64(bad) != 0;
+        sc = wmax != 0u && wmax < 0x7f800000u ? 15 - __builtin_amdgcn_frexp_expf(fmx) : 0;
+        __asm__ volatile("" : "+v"(sc) : : "memory");           // the second reading stays a second one
+#pragma unroll
+        for (int kk = 0; kk < NK; ++kk) {
+            float2v w[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) w[i] = load_w(kk, i);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                float re = __builtin_amdgcn_ldexpf(w[i][0], sc), im = __builtin_amdgcn_ldexpf(w[i][1], sc);
+#pragma unroll
+                for (int p = 0; p < P; ++p) {
+                    const _Float16 pr = (_Float16)re, pi = (_Float16)im;
+                    re -= (float)pr;                       // exact
+                    im -= (float)pi;
+                    wr[p][kk][i] = pack_h(pr, -pi);
+                    wi[p][kk][i] = pack_h(pi, pr);
+                }
+            }
+            if (kk & 1) __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    // a wave whose beam tile lies wholly past the block's beams, or that takes
+    // the exact path, only loads, stages and meets the barriers
+    const bool idle = d.b0 + (bg * NBT + bt) * kTile >= d.b1 || exact;
+    const int trow = tile_row_sample(r);
+    const int sw = a_swz(trow);
+
+    if (XT == XT_CI16) {
+        if (tid < 2 * NS) flags[tid] = -1;
+        __syncthreads();
+    }
+    store_chunks(0);
+    __syncthreads();
+
+    floatx16 acc[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) acc[q] = zero16();
+    auto mfma4 = [&](const V& a, const V& b, const u32x4& r4, const u32x4& i4) {
+        const V br = __builtin_bit_cast(V, r4), bi = __builtin_bit_cast(V, i4);
+        acc[0] = M::mfma(a, br, acc[0]);
+        acc[1] = M::mfma(a, bi, acc[1]);
+        acc[2] = M::mfma(b, br, acc[2]);
+        acc[3] = M::mfma(b, bi, acc[3]);
+    };
+    auto epilogue = [&](int k) {
+        const int tile = tile_lo + sigma + NS * k;
+        const bool ok = k >= 0 && tile < tile_lo + ntiles && beam_ok;
+        split_epilogue<PR>(acc, ors, d.ld_row, T, d.t_int, beam, tile * kTile, h, ok, sc);
+    };
+    const bool late = wave >= 4;                           // the second wave of each SIMD
+    for (int k = 0; k < nsteps; ++k) {
+        load_chunks(k + 1);
+        if (!idle) {
+            if (late && k > 0) epilogue(k - 1);
+            int rowx = (sigma * 2 + (k & 1)) * kATileWords + 2 * trow * kARow;
+            __asm__ volatile("" : "+v"(rowx));
+            const uint32_t* ax0 = at + rowx;
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) acc[q] = zero16();
+            if (XT == XT_CI16 && __builtin_amdgcn_readfirstlane(flags[(k & 1) * NS + sigma]) == k) {
+                // residuals of this tile's samples, straight from HBM (rows past T: its last sample)
+                const int t = min((min(tile_lo + sigma + NS * k, tile_lo + ntiles - 1)) * kTile + trow, T - 1);
+#pragma unroll
+                for (int kk = 0; kk < NK; ++kk) {
+                    const __amdgpu_buffer_rsrc_t rs = group_rsrc(d.x, 8 * kk, S, stride_bytes);
+                    u32x4 ux, uy;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+                        const u32x2 v = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(
+                            rs, (int)sample_off(4 * h + i, stride_bytes, c, T, t, BYTES), 0, 0));
+                        ux[i] = residual_i16x2(v[0]);
+                        uy[i] = residual_i16x2(v[1]);
+                    }
+                    const V a = __builtin_bit_cast(V, ux), b = __builtin_bit_cast(V, uy);
+#pragma unroll
+                    for (int p = P - 1; p >= 0; --p) mfma4(a, b, wr[p][kk], wi[p][kk]);
+                    __builtin_amdgcn_sched_barrier(0);         // one K-step's loads at a time
+                }
+            }
+#pragma unroll
+            for (int kk = 0; kk < NK; ++kk) {
+                const int off = 4 * ((2 * kk + h) ^ sw);
+                const V a = __builtin_bit_cast(V, *reinterpret_cast<const u32x4*>(ax0 + off));
+                const V b = __builtin_bit_cast(V, *reinterpret_cast<const u32x4*>(ax0 + kARow + off));
+#pragma unroll
+                for (int p = P - 1; p >= 0; --p) mfma4(a, b, wr[p][kk], wi[p][kk]);   // the small pieces first
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            if (!late) epilogue(k);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        store_chunks(k + 1);
+        __syncthreads();
+    }
+    if (!idle) {
+        if (late) epilogue(nsteps - 1);
+        return;
+    }
+    if (!exact) return;
+    // the exact path: lane half h holds the re (0) or im (1) component of
+    // station s as K index h of a 32x32x2 FP32 MFMA
+    sc = 0;
+    const uint32_t hsh = (uint32_t)h * (XT == XT_CI8 ? 8u : 16u);
+    for (int k = 0; k < nsteps; ++k) {
+        const int tile = tile_lo + sigma + NS * k;
+        if (tile >= tile_lo + ntiles) break;
+        const int t = min(tile * kTile + trow, T - 1);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc[q] = zero16();
+        for (int s = 0; s < S; ++s) {
+            const float2v w = __builtin_bit_cast(float2v, __builtin_amdgcn_raw_buffer_load_b64(
+                wrs, (int)weight_off(beam, S, s, 8), 0, 0));
+            float ax, ay;
+            Raw<XT>::half(buffer_sample<XT>(group_rsrc(d.x, s & ~7, S, stride_bytes),
+                                            sample_off(s & 7, stride_bytes, c, T, t, BYTES)), hsh, ax, ay);
+            const float br = h ? -w[1] : w[0], bi = h ? w[0] : w[1];
+            acc[0] = mfma_f32(ax, br, acc[0]);
+            acc[1] = mfma_f32(ax, bi, acc[1]);
+            acc[2] = mfma_f32(ay, br, acc[2]);
+            acc[3] = mfma_f32(ay, bi, acc[3]);
+        }
+        epilogue(k);
+    }
+}
+
+// 8 waves, two per SIMD; LDS: NS streams x 2 buffers of one A tile
+template <int XT, int PR, int NK, int NS>
+__global__ __launch_bounds__(kThreadsH) void bf_f32_split_kernel(BlockDesc d, int nbg, int nitems) {
+    __shared__ __attribute__((aligned(16))) uint32_t at[NS * 2 * kATileWords];
+    __shared__ int flags[2 * NS];
+    item_f32_split<XT, PR, NK, NS>(d, xcd_remap(blockIdx.x, nitems), nbg, at, flags);
+}
+
+template <int XT, int PR, int NK>
+inline void launch_split_nk(const BlockDesc& d, int ns, int nbg, int n, hipStream_t st) {
+    const dim3 g(n), b(kThreadsH);
+    if constexpr (XT == XT_CI8 || NK < 6) {
+        if (ns == 4) {
+            hipLaunchKernelGGL((bf_f32_split_kernel<XT, PR, NK, 4>), g, b, 0, st, d, nbg, n);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((bf_f32_split_kernel<XT, PR, NK, 2>), g, b, 0, st, d, nbg, n);
+}
+
+template <int XT, int PR>
+inline void launch_split_pr(const BlockDesc& d, int nbg, int n, hipStream_t st) {
+    const int ns = split_streams(d);
+    switch (split_ksteps(d.S)) {
+        case 2: launch_split_nk<XT, PR, 2>(d, ns, nbg, n, st); break;
+        case 4: launch_split_nk<XT, PR, 4>(d, ns, nbg, n, st); break;
+        case 5: launch_split_nk<XT, PR, 5>(d, ns, nbg, n, st); break;
+        case 6: launch_split_nk<XT, PR, 6>(d, ns, nbg, n, st); break;
+        case 7: launch_split_nk<XT, PR, 7>(d, ns, nbg, n, st); break;
+        default: launch_split_nk<XT, PR, 8>(d, ns, nbg, n, st); break;
+    }
+}
+
+template <int XT>
+inline hipError_t launch_split_xt(const BlockDesc& d, hipStream_t st) {
+    int nbg;
+    const int n = block_items_split(d, &nbg);
+    if (d.product == PR_VOLT) launch_split_pr<XT, PR_VOLT>(d, nbg, n, st);
+    else if (d.product == PR_I) launch_split_pr<XT, PR_I>(d, nbg, n, st);
+    else launch_split_pr<XT, PR_IQUV>(d, nbg, n, st);
+    return hipGetLastError();
+}
+
+}  // namespace lbf

@@ -1,11 +1,11 @@
 // bf_workers.h -- the per-work-item contraction workers.
 //
-// Fast workers (up to 64 stations of complex int8/int16, t_int <= 16, no
-// channel integration): item_f32_fast and item_h_fast, described where they
-// are defined; they write Stokes products channel-major.
+// Fast workers (up to 64 stations, t_int <= 16, no channel integration):
+// item_f32_fast and item_h_fast, described where they are defined, and
+// item_f32_split (bf_split_worker.h); they write Stokes products
+// channel-major.
 //
-// Generic workers (any station count, complex float input, channel
-// integration, t_int >= 32): work item = (channel group of f_int channels,
+// Generic workers (any station count, any integration): work item = (channel group of f_int channels,
 // group of up to 128 beams).  A work group of 4 waves stages that beam group's
 // weights for one channel in LDS; each wave walks its own 32-sample tiles
 // (groups of tiles when t_int >= 32), streaming station samples from HBM
@@ -19,10 +19,11 @@
 namespace lbf {
 
 // ===========================================================================
-// fast workers: up to 64 stations of complex int8/int16 samples
+// fast workers: up to 64 stations
 // ===========================================================================
 
-// FP32 operands (MFMA 32x32x2 f32: one station per MFMA, K = (re, im)).
+// FP32 operands and complex float samples (MFMA 32x32x2 f32: one station per
+// MFMA, K = (re, im)); integer samples take bf_split_worker.h's worker.
 //
 // A work item is one channel, 128 beams and a segment of sample tiles
 // (seg_tiles); a work group has 8 waves (two per SIMD).  The weights of the
@@ -81,10 +82,6 @@ LBF_INLINE void item_f32_fast(const BlockDesc& d, int item, int nbg, float* pl) 
     const int T2 = PR == PR_VOLT ? T : T / TI;
     const __amdgpu_buffer_rsrc_t ors = channel_rsrc(d, c, out_channel_bytes(d, PR, T2));
     const int trow = tile_row_sample(r);
-    // weights read one quad of stations ahead (8 more registers): where they
-    // fit without spills -- not with complex float samples (16-byte ring
-    // entries) nor beside the 16 output sums of unintegrated Stokes
-    constexpr bool PF = XT != XT_CF32 && (PR == PR_VOLT || TI >= 2);
 
     stage_weights_f32_planes(pl, d, c, b0);
     __syncthreads();
@@ -135,13 +132,6 @@ LBF_INLINE void item_f32_fast(const BlockDesc& d, int item, int nbg, float* pl) 
         for (int o = 0; o < NOUT; ++o)
 #pragma unroll
             for (int q = 0; q < 4; ++q) sm[o][q] = 0.f;
-        // weights of the first 4 stations; with PF each later quad's are read
-        // one quad ahead, so that the LDS latency passes under 16 MFMAs
-        floatx4 br, bi;
-        if constexpr (PF) {
-            br = *reinterpret_cast<const floatx4*>(pl + wro);
-            bi = *reinterpret_cast<const floatx4*>(pl + wio);
-        }
 #pragma unroll
         for (int gi = 0; gi < 8; ++gi) {
             if (gi < ngrp) {                                   // uniform
@@ -155,17 +145,9 @@ LBF_INLINE void item_f32_fast(const BlockDesc& d, int item, int nbg, float* pl) 
 #pragma unroll
                     for (int i = 0; i < 4; ++i) R::half(ring[gi & 1][4 * i4 + i], hsh, ax[i], ay[i]);
                     load_quad(gi & 1, i4, k * ngrp + gi + 2);
-                    floatx4 nbr, nbi;
-                    if constexpr (PF) {
-                        const int s4n = s4 + 4 < 8 * ngrp ? s4 + 4 : s4;    // the last quad reads itself again
-                        nbr = *reinterpret_cast<const floatx4*>(pl + wro + s4n);
-                        nbi = *reinterpret_cast<const floatx4*>(pl + wio + s4n);
-                    }
-                    __builtin_amdgcn_sched_barrier(0);                     // those reads issue before the MFMAs
-                    if constexpr (!PF) {
-                        br = *reinterpret_cast<const floatx4*>(pl + wro + s4);
-                        bi = *reinterpret_cast<const floatx4*>(pl + wio + s4);
-                    }
+                    __builtin_amdgcn_sched_barrier(0);                     // the refill issues before the MFMAs
+                    const floatx4 br = *reinterpret_cast<const floatx4*>(pl + wro + s4);
+                    const floatx4 bi = *reinterpret_cast<const floatx4*>(pl + wio + s4);
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
                         const bool first = gi == 0 && i4 == 0 && i == 0;
@@ -173,10 +155,6 @@ LBF_INLINE void item_f32_fast(const BlockDesc& d, int item, int nbg, float* pl) 
                         acc[1] = mfma_f32(ax[i], bi[i], first ? zero16() : acc[1]);
                         acc[2] = mfma_f32(ay[i], br[i], first ? zero16() : acc[2]);
                         acc[3] = mfma_f32(ay[i], bi[i], first ? zero16() : acc[3]);
-                    }
-                    if constexpr (PF) {
-                        br = nbr;
-                        bi = nbi;
                     }
                 }
             }

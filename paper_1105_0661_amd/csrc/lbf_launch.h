@@ -46,6 +46,8 @@ constexpr size_t kNoAllocScratchBytes = 64ull << 20;
 hipError_t noalloc_scratch(void** p);
 hipError_t launch_beamform_generic(const BlockDesc& d, hipStream_t st);
 hipError_t launch_fast_f32(const BlockDesc& d, hipStream_t st);
+hipError_t launch_split_ci8(const BlockDesc& d, hipStream_t st);    // FP32, complex int8 / int16 samples
+hipError_t launch_split_ci16(const BlockDesc& d, hipStream_t st);
 hipError_t launch_fast_f16(const BlockDesc& d, hipStream_t st);
 hipError_t launch_fast_bf16(const BlockDesc& d, hipStream_t st);
 // stage == nullptr: staging from the stream-ordered pool; else block j has
