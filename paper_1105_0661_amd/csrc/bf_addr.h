@@ -81,26 +81,37 @@ LBF_HD uint64_t weight_base(const BlockDesc& d, int c, int bytes) { return (uint
 LBF_HD uint32_t weight_range(const BlockDesc& d, int bytes) { return (uint32_t)d.B * (uint32_t)d.S * (uint32_t)bytes; }
 LBF_HD uint32_t weight_off(int beam, int S, int s, int bytes) { return ((uint32_t)beam * S + s) * (uint32_t)bytes; }
 
-// The FP16/BF16 worker's sample loaders: chunk j (thread tid + 512 i) of step
-// k covers stream sg, station s and samples SPC q .. SPC q + SPC - 1 of tile
-// `tile` (the stream's tile of that step, or its last tile once it has run
-// out).  Chunks past the step's ns tiles (a step of fewer chunks than
-// threads) load the tiles of a later step (in range, clamped to the item's
-// last tile), which warms the cache for that step, and are not staged.
-// (Skipping their loads, with an out-of-range offset, costs registers that
-// the two headline shapes do not have.)
-struct Chunk16 {
-    int s, q, tile;
-};
+// Station planes of a tile: the descriptor of group_base / group_range moved
+// to sample t of channel c (tile_off bytes into each plane), so that a
+// thread's offset, station and sample within the tile, is the same for every
+// tile and channel.
+LBF_HD uint32_t tile_off(int c, int T, int t, int bytes) { return (uint32_t)(c * T + t) * (uint32_t)bytes; }
+LBF_HD uint32_t tile_range(int s0, int S, uint32_t stride_bytes, uint32_t off) {
+    const uint32_t r = group_range(s0, S, stride_bytes);
+    return r == 0 ? 0 : r - off;
+}
 
-LBF_HD Chunk16 h_chunk(int j, int k, int ns, int cptile, int cps, int tile_lo, int ntiles) {
-    const int sg = j / cptile, jt = j % cptile;
-    Chunk16 ch;
-    ch.s = jt / cps;
-    ch.q = jt % cps;
+// The sample loaders of the workers that stage tiles in LDS: a tile's 16-byte
+// chunks (spc samples of one station), stations padded to sp (16, 32 or 64),
+// are dealt to the work group's threads, chunk i of thread tid being number
+// tid + kLoaders i of the step's ns tiles.  All the divisors are powers of
+// two, a wave's chunks belong to one group of 8 stations and one stream, and
+// the station's number within its group does not depend on i.
+constexpr int kLoaders = 512;
+
+LBF_HD constexpr int padded_stations(int nk) { return nk <= 2 ? 16 : nk <= 4 ? 32 : 64; }
+LBF_HD constexpr int chunks_per_thread(int ns, int sp, int cps) {
+    return (ns * sp * cps + kLoaders - 1) / kLoaders;
+}
+LBF_HD constexpr int chunk_stream(int tid, int i, int sp, int cps) { return (tid + kLoaders * i) / (sp * cps); }
+LBF_HD constexpr int chunk_station(int tid, int i, int sp, int cps) { return (tid + kLoaders * i) / cps % sp; }
+LBF_HD constexpr int chunk_q(int tid, int cps) { return tid % cps; }
+// bytes of a thread's offset into the descriptor: station of the group, chunk of the tile
+LBF_HD uint32_t chunk_off(int s, int q, uint32_t stride_bytes) { return (uint32_t)(s & 7) * stride_bytes + 16u * (uint32_t)q; }
+// the stream's tile of step k, or the item's last tile once it has run out
+LBF_HD int stream_tile(int sg, int k, int ns, int tile_lo, int ntiles) {
     const int i = sg + ns * k;
-    ch.tile = tile_lo + (i < ntiles - 1 ? i : ntiles - 1);
-    return ch;
+    return tile_lo + (i < ntiles - 1 ? i : ntiles - 1);
 }
 
 // Output of one channel (order 1 staging, or voltages): one descriptor per

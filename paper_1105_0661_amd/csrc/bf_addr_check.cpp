@@ -96,8 +96,7 @@ void walk_h(Walk& w, const BlockDesc& d, int lo, int hi) {
     const uint32_t stride = (uint32_t)stride64;
     if (stride != stride64) return w.fail("station stride does not fit 32 bits");
     const int NS = fast_h_streams(d), NK = fast_h_ksteps(d.S), NBT = 8 / NS;
-    const int SPC = 16 / bytes, CPS = kTile / SPC, CPTILE = 8 * NK * CPS;
-    const int CPT = (NS * CPTILE + kThreadsH - 1) / kThreadsH;
+    const int CPS = kTile * bytes / 16, SP = padded_stations(NK), CPT = chunks_per_thread(NS, SP, CPS);
     int nbg;
     const int items = block_items_fast_h(d, &nbg);
     for (int item = lo; item < std::min(hi, items) && !w.bad; ++item) {
@@ -114,11 +113,13 @@ void walk_h(Walk& w, const BlockDesc& d, int lo, int hi) {
             // the loaders run up to two steps ahead of the last one
             for (int k = 0; k < nsteps + 2; ++k)
                 for (int i = 0; i < CPT; ++i) {
-                    const Chunk16 ch = h_chunk(tid + kThreadsH * i, k, NS, CPTILE, CPS, ip.tile_lo, ip.ntiles);
-                    const int s0 = ch.s & ~7, t = ch.tile * kTile + ch.q * SPC;
-                    const uint64_t o64 = (uint64_t)(ch.s & 7) * stride64 + ((uint64_t)ip.c * d.T + t) * bytes;
-                    w.access("sample load", group_base(s0, stride), group_range(s0, d.S, stride), o64,
-                             sample_off(ch.s & 7, stride, ip.c, d.T, t, bytes), 16, xbuf, false);
+                    const int sg = chunk_stream(tid, i, SP, CPS), s = chunk_station(tid, i, SP, CPS), s0 = s & ~7;
+                    if (sg >= NS) continue;                    // past the step's chunks: an out-of-range offset
+                    const int t = stream_tile(sg, k, NS, ip.tile_lo, ip.ntiles) * kTile, q = chunk_q(tid, CPS);
+                    const uint32_t off = tile_off(ip.c, d.T, t, bytes);
+                    if (off != ((uint64_t)ip.c * d.T + t) * bytes) return w.fail("the tile's offset wraps");
+                    w.access("sample load", group_base(s0, stride) + off, tile_range(s0, d.S, stride, off),
+                             (uint64_t)(s & 7) * stride64 + 16u * q, chunk_off(s, q, stride), 16, xbuf, false);
                 }
             for (int k = 0; k < nsteps; ++k) {
                 const int tile = ip.tile_lo + sigma + NS * k;
@@ -137,8 +138,7 @@ void walk_split(Walk& w, const BlockDesc& d, int lo, int hi) {
     const uint32_t stride = (uint32_t)stride64;
     if (stride != stride64) return w.fail("station stride does not fit 32 bits");
     const int NS = split_streams(d), NK = split_ksteps(d.S), NBT = 8 / NS;
-    const int SPC = 16 / bytes, CPS = kTile / SPC, CPTILE = 8 * NK * CPS;
-    const int CPT = (NS * CPTILE + kThreadsH - 1) / kThreadsH;
+    const int CPS = kTile * bytes / 16, SP = padded_stations(NK), CPT = chunks_per_thread(NS, SP, CPS);
     int nbg;
     const int items = block_items_split(d, &nbg);
     for (int item = lo; item < std::min(hi, items) && !w.bad; ++item) {
@@ -159,11 +159,13 @@ void walk_split(Walk& w, const BlockDesc& d, int lo, int hi) {
             // the loaders run one step ahead of the last one
             for (int k = 0; k < nsteps + 1; ++k)
                 for (int i = 0; i < CPT; ++i) {
-                    const Chunk16 ch = h_chunk(tid + kThreadsH * i, k, NS, CPTILE, CPS, ip.tile_lo, ip.ntiles);
-                    const int s0 = ch.s & ~7, t = ch.tile * kTile + ch.q * SPC;
-                    const uint64_t o64 = (uint64_t)(ch.s & 7) * stride64 + ((uint64_t)ip.c * d.T + t) * bytes;
-                    w.access("sample load", group_base(s0, stride), group_range(s0, d.S, stride), o64,
-                             sample_off(ch.s & 7, stride, ip.c, d.T, t, bytes), 16, xbuf, false);
+                    const int sg = chunk_stream(tid, i, SP, CPS), s = chunk_station(tid, i, SP, CPS), s0 = s & ~7;
+                    if (sg >= NS) continue;                    // past the step's chunks: an out-of-range offset
+                    const int t = stream_tile(sg, k, NS, ip.tile_lo, ip.ntiles) * kTile, q = chunk_q(tid, CPS);
+                    const uint32_t off = tile_off(ip.c, d.T, t, bytes);
+                    if (off != ((uint64_t)ip.c * d.T + t) * bytes) return w.fail("the tile's offset wraps");
+                    w.access("sample load", group_base(s0, stride) + off, tile_range(s0, d.S, stride, off),
+                             (uint64_t)(s & 7) * stride64 + 16u * q, chunk_off(s, q, stride), 16, xbuf, false);
                 }
             for (int k = 0; k < nsteps; ++k) {
                 const int tile = ip.tile_lo + sigma + NS * k;

@@ -10,18 +10,9 @@
 // fast path (more than 64 stations, t_int other than 16, channel integration,
 // complex float input) are rare in a batch and run through their own launches
 // on the same stream.
-#include "bf_common.h"
-#include "bf_workers.h"
+#include "bf_batch_impl.h"
 
 namespace lbf {
-
-struct BatchArgs {
-    BlockDesc blk[kMaxBatch];
-    int item_start[kMaxBatch + 1];   // prefix sums of items per block
-    int nbg[kMaxBatch];
-    int n;
-};
-static_assert(sizeof(BatchArgs) <= 4096, "kernel argument block");
 
 // Items of t_int = 16 Stokes blocks (the common integration) run the fast
 // workers; everything else in a batch runs the generic ones.
@@ -36,77 +27,6 @@ inline int batch_variant(const BlockDesc& d) {
     const int xp = (d.xtype == XT_CI8 ? 0 : 2) + (d.product == PR_I ? 0 : 1);
     const int ns = fast_h_streams(d);
     return (xp * 5 + ik) * 3 + (ns == 1 ? 0 : ns == 2 ? 1 : 2);
-}
-
-template <int XT, int CT, int PR, int NK, int NS>
-__global__ __launch_bounds__(kThreadsH) void bf_batch_kernel(BatchArgs a, int* counter) {
-    __shared__ __attribute__((aligned(16))) uint32_t at[NS * 2 * kATileWords];
-    __shared__ int next;
-    const int total = a.item_start[a.n];
-    for (;;) {
-        __syncthreads();
-        if (threadIdx.x == 0) next = atomicAdd(counter, 1);
-        __syncthreads();
-        const int it = next;
-        if (it >= total) break;     // every work group leaves once the list is exhausted
-        int j = 0;
-        while (j + 1 < a.n && a.item_start[j + 1] <= it) ++j;
-        item_h_fast<XT, CT, PR, 16, NK, NS>(a.blk[j], it - a.item_start[j], a.nbg[j], at);
-    }
-}
-
-__global__ void fill_int_kernel(int* p, int n, int v) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = v;
-}
-
-// One persistent launch of variant <XT, CT, PR, NK, NS>: one resident work
-// group per slot the hardware offers; the queue, not the grid, spreads the
-// uneven items.
-template <int XT, int CT, int PR, int NK, int NS>
-hipError_t launch_batch_k(const BatchArgs& a, int* counter, hipStream_t st) {
-    int dev = 0, cus = 256, per_cu = 1;
-    if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, bf_batch_kernel<XT, CT, PR, NK, NS>, kThreadsH, 0);
-    if (per_cu < 1) per_cu = 1;
-    const int total = a.item_start[a.n];
-    const int slots = cus * per_cu;
-    hipLaunchKernelGGL(fill_int_kernel, dim3(1), dim3(64), 0, st, counter, 1, 0);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((bf_batch_kernel<XT, CT, PR, NK, NS>), dim3(total < slots ? total : slots), dim3(kThreadsH), 0,
-                       st, a, counter);
-    return hipGetLastError();
-}
-
-template <int XT, int CT, int PR, int NK>
-hipError_t launch_batch_nk(int v, const BatchArgs& a, int* counter, hipStream_t st) {
-    switch (v % 3) {
-        case 0: return launch_batch_k<XT, CT, PR, NK, 1>(a, counter, st);
-        case 1: return launch_batch_k<XT, CT, PR, NK, 2>(a, counter, st);
-        default: return launch_batch_k<XT, CT, PR, NK, 4>(a, counter, st);
-    }
-}
-
-template <int XT, int CT, int PR>
-hipError_t launch_batch_pr(int v, const BatchArgs& a, int* counter, hipStream_t st) {
-    switch (v % 15 / 3) {
-        case 0: return launch_batch_nk<XT, CT, PR, 4>(v, a, counter, st);
-        case 1: return launch_batch_nk<XT, CT, PR, 5>(v, a, counter, st);
-        case 2: return launch_batch_nk<XT, CT, PR, 6>(v, a, counter, st);
-        case 3: return launch_batch_nk<XT, CT, PR, 7>(v, a, counter, st);
-        default: return launch_batch_nk<XT, CT, PR, 8>(v, a, counter, st);
-    }
-}
-
-template <int CT>
-hipError_t launch_batch_variant(int v, const BatchArgs& a, int* counter, hipStream_t st) {
-    switch (v / 15) {
-        case 0: return launch_batch_pr<XT_CI8, CT, PR_I>(v, a, counter, st);
-        case 1: return launch_batch_pr<XT_CI8, CT, PR_IQUV>(v, a, counter, st);
-        case 2: return launch_batch_pr<XT_CI16, CT, PR_I>(v, a, counter, st);
-        default: return launch_batch_pr<XT_CI16, CT, PR_IQUV>(v, a, counter, st);
-    }
 }
 
 // One group of batch-kernel blocks; block idx[g] forms its Stokes products
@@ -153,8 +73,8 @@ static hipError_t run_batch_group(const BlockDesc* blks, const int* idx, int n, 
             g.n++;
         }
         if (g.n == 0) continue;
-        e = a.blk[0].ctype == CT_F16 ? launch_batch_variant<CT_F16>(v, g, d_counter, st)
-                                     : launch_batch_variant<CT_BF16>(v, g, d_counter, st);
+        e = a.blk[0].ctype == CT_F16 ? launch_batch_f16(v, g, d_counter, st)
+                                     : launch_batch_bf16(v, g, d_counter, st);
     }
     for (int g = 0; g < n && e == hipSuccess; ++g) {
         const BlockDesc& b = blks[idx[g]];

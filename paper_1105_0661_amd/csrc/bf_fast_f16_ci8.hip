@@ -1,0 +1,8 @@
+// bf_fast_f16_ci8.hip -- fast contraction kernels with F16 operands, complex int8 samples.
+#include "bf_fast_impl.h"
+
+namespace lbf {
+hipError_t launch_f16_ci8(const BlockDesc& d, int nbg, int n, hipStream_t st) {
+    return launch_h_xt<XT_CI8, CT_F16>(d, nbg, n, st);
+}
+}  // namespace lbf

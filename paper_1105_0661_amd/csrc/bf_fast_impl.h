@@ -1,5 +1,5 @@
 // bf_fast_impl.h -- kernels and launchers of the fast contraction workers,
-// instantiated per operand type in bf_fast_f32.hip / _f16.hip / _bf16.hip.
+// instantiated per operand and sample type in bf_fast_*.hip.
 #pragma once
 #include "bf_common.h"
 #include "bf_workers.h"
@@ -104,6 +104,21 @@ inline hipError_t launch_h_xt(const BlockDesc& d, int nbg, int n, hipStream_t st
     return launch_h_pr<XT, CT, PR_IQUV>(d, nbg, n, st);
 }
 
+// the launch of one part, by sample type (bf_fast_f16_*.hip, bf_fast_bf16_*.hip)
+template <int CT> hipError_t launch_fast_h_part(const BlockDesc& d, int nbg, int n, hipStream_t st);
+template <>
+inline hipError_t launch_fast_h_part<CT_F16>(const BlockDesc& d, int nbg, int n, hipStream_t st) {
+    return d.xtype == XT_CI8    ? launch_f16_ci8(d, nbg, n, st)
+           : d.xtype == XT_CI16 ? launch_f16_ci16(d, nbg, n, st)
+                                : launch_f16_cf32(d, nbg, n, st);
+}
+template <>
+inline hipError_t launch_fast_h_part<CT_BF16>(const BlockDesc& d, int nbg, int n, hipStream_t st) {
+    return d.xtype == XT_CI8    ? launch_bf16_ci8(d, nbg, n, st)
+           : d.xtype == XT_CI16 ? launch_bf16_ci16(d, nbg, n, st)
+                                : launch_bf16_cf32(d, nbg, n, st);
+}
+
 template <int CT>
 inline hipError_t launch_fast_h(const BlockDesc& d, hipStream_t st) {
     BlockDesc part[2];
@@ -111,9 +126,7 @@ inline hipError_t launch_fast_h(const BlockDesc& d, hipStream_t st) {
     for (int p = 0; p < np; ++p) {
         int nbg;
         const int n = block_items_fast_h(part[p], &nbg);
-        const hipError_t e = d.xtype == XT_CI8    ? launch_h_xt<XT_CI8, CT>(part[p], nbg, n, st)
-                             : d.xtype == XT_CI16 ? launch_h_xt<XT_CI16, CT>(part[p], nbg, n, st)
-                                                  : launch_h_xt<XT_CF32, CT>(part[p], nbg, n, st);
+        const hipError_t e = launch_fast_h_part<CT>(part[p], nbg, n, st);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

@@ -137,10 +137,8 @@ LBF_INLINE void item_f32_split(const BlockDesc& d, int item, int nbg, uint32_t* 
     constexpr int P = split_pieces(NK);
     constexpr int BYTES = sample_bytes(XT);
     constexpr int NBT = 8 / NS;                            // beam tiles per item
-    constexpr int SPC = Chunk<XT, CT_F16>::samples;        // samples per 16-byte chunk
-    constexpr int CPS = kTile / SPC;                       // chunks per station per tile
-    constexpr int CPTILE = 8 * NK * CPS;                   // chunks per tile
-    constexpr int CPT = (NS * CPTILE + kThreadsH - 1) / kThreadsH;   // chunks per thread per step
+    typedef TileLoader<XT, CT_F16, NK, NS> Loader;
+    constexpr int CPT = Loader::CPT;                       // chunks per thread per step
     const int T = d.T, S = d.S;
     const ItemPos ip = item_pos(d, item, nbg);
     const int c = ip.c, bg = ip.bg, tile_lo = ip.tile_lo, ntiles = ip.ntiles;
@@ -155,50 +153,29 @@ LBF_INLINE void item_f32_split(const BlockDesc& d, int item, int nbg, uint32_t* 
     const __amdgpu_buffer_rsrc_t ors = channel_rsrc(d, c, out_channel_bytes(d, PR, T2));
     const __amdgpu_buffer_rsrc_t wrs = weight_rsrc(d, c, 8);
 
-    // loaders, as item_h_fast's: one step ahead
+    // samples one step ahead
+    Loader ld;
+    ld.init(d, ip);
     u32x4 raw[CPT];
-    auto load_chunks = [&](int k) {
-        int tid = threadIdx.x;
-        __asm__ volatile("" : "+v"(tid));                  // addresses formed anew each step, not kept in registers
+    auto load_chunks = [&](int k) { ld.load(k, raw); };
+    auto store_chunk = [&](int k, int i) {
+        ld.store(at, k, i, raw);
+        if constexpr (XT == XT_CI16) {
+            // any component outside [-2048, 2047]: x + 2048 has one of its top four bits set
+            typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+            const u16x2 bias = {2048, 2048};
+            uint32_t big = 0u;
 #pragma unroll
-        for (int i = 0; i < CPT; ++i) {
-            const Chunk16 ch = h_chunk(tid + kThreadsH * i, k, NS, CPTILE, CPS, tile_lo, ntiles);
-            const __amdgpu_buffer_rsrc_t rs = group_rsrc(d.x, ch.s & ~7, S, stride_bytes);
-            const uint32_t off = sample_off(ch.s & 7, stride_bytes, c, T, ch.tile * kTile + ch.q * SPC, BYTES);
-            raw[i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)off, 0, 0));
+            for (int e = 0; e < 4; ++e) {
+                const uint32_t v = raw[i][e];             // a value: a bit cast of the element itself reads element 0
+                big |= __builtin_bit_cast(uint32_t, (u16x2)(__builtin_bit_cast(u16x2, v) + bias));
+            }
+            if (big & 0xf000f000u) flags[(k & 1) * NS + ld.stream(i)] = k;
         }
     };
     auto store_chunks = [&](int k) {
-        int tid = threadIdx.x;
-        __asm__ volatile("" : "+v"(tid));
 #pragma unroll
-        for (int i = 0; i < CPT; ++i) {
-            const int j = tid + kThreadsH * i;
-            const int sg = j / CPTILE, jt = j % CPTILE, s = jt / CPS, q = jt % CPS;
-            if (NS * CPTILE % kThreadsH == 0 || j < NS * CPTILE) {
-                uint32_t* ab = at + (sg * 2 + (k & 1)) * kATileWords;
-                uint32_t big = 0u;
-#pragma unroll
-                for (int js = 0; js < SPC; ++js) {
-                    uint32_t fx, fy;
-                    Chunk<XT, CT_F16>::xy(raw[i], js, fx, fy);
-                    const int t = q * SPC + js;
-                    ab[a_word(t, 0, s)] = fx;
-                    ab[a_word(t, 1, s)] = fy;
-                }
-                if constexpr (XT == XT_CI16) {
-                    // any component outside [-2048, 2047]: x + 2048 has one of its top four bits set
-                    typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
-                    const u16x2 bias = {2048, 2048};
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const uint32_t v = raw[i][e];     // a value: a bit cast of the element itself reads element 0
-                        big |= __builtin_bit_cast(uint32_t, (u16x2)(__builtin_bit_cast(u16x2, v) + bias));
-                    }
-                    if (big & 0xf000f000u) flags[(k & 1) * NS + sg] = k;
-                }
-            }
-        }
+        for (int i = 0; i < CPT; ++i) store_chunk(k, i);
     };
     load_chunks(0);
 
@@ -280,19 +257,45 @@ LBF_INLINE void item_f32_split(const BlockDesc& d, int item, int nbg, uint32_t* 
     auto epilogue = [&](int k) {
         const int tile = tile_lo + sigma + NS * k;
         const bool ok = k >= 0 && tile < tile_lo + ntiles && beam_ok;
-        split_epilogue<PR>(acc, ors, d.ld_row, T, d.t_int, beam, tile * kTile, h, ok, sc);
+        int bm = beam, hh = h;
+        __asm__ volatile("" : "+v"(bm), "+v"(hh));          // offsets formed anew for each tile
+        split_epilogue<PR>(acc, ors, d.ld_row, T, d.t_int, bm, tile * kTile, hh, ok, sc);
     };
     const bool late = wave >= 4;                           // the second wave of each SIMD
     for (int k = 0; k < nsteps; ++k) {
         load_chunks(k + 1);
         if (!idle) {
             if (late && k > 0) epilogue(k - 1);
-            int rowx = (sigma * 2 + (k & 1)) * kATileWords + 2 * trow * kARow;
-            __asm__ volatile("" : "+v"(rowx));
+            int rowx = (sigma * 2 + (k & 1)) * kATileWords + 2 * trow * kARow, swx = 4 * (h ^ sw);
+            __asm__ volatile("" : "+v"(rowx), "+v"(swx));
             const uint32_t* ax0 = at + rowx;
             __builtin_amdgcn_sched_barrier(0);
+            // operands one K-step ahead from LDS; the next step's samples
+            // staged under the second half of the MFMAs
+            u32x4 ax[2], ay[2];
+            ax[0] = *reinterpret_cast<const u32x4*>(ax0 + swx);
+            ay[0] = *reinterpret_cast<const u32x4*>(ax0 + kARow + swx);
 #pragma unroll
-            for (int q = 0; q < 4; ++q) acc[q] = zero16();
+            for (int kk = 0; kk < NK; ++kk) {
+                if (kk + 1 < NK) {
+                    const int off = swx ^ (8 * (kk + 1));       // 4 ((2 kk + 2 + h) ^ sw)
+                    ax[(kk + 1) & 1] = *reinterpret_cast<const u32x4*>(ax0 + off);
+                    ay[(kk + 1) & 1] = *reinterpret_cast<const u32x4*>(ax0 + kARow + off);
+                }
+                const V a = __builtin_bit_cast(V, ax[kk & 1]), b = __builtin_bit_cast(V, ay[kk & 1]);
+#pragma unroll
+                for (int p = P - 1; p >= 0; --p) {            // the small pieces first
+                    if (kk == 0 && p == P - 1) {
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) acc[q] = zero16();
+                    }
+                    mfma4(a, b, wr[p][kk], wi[p][kk]);
+                }
+#pragma unroll
+                for (int i = 0; i < CPT; ++i)
+                    if (kk == NK / 2 + i * (NK - NK / 2) / CPT) store_chunk(k + 1, i);
+                __builtin_amdgcn_sched_barrier(0);
+            }
             if (XT == XT_CI16 && __builtin_amdgcn_readfirstlane(flags[(k & 1) * NS + sigma]) == k) {
                 // residuals of this tile's samples, straight from HBM (rows past T: its last sample)
                 const int t = min((min(tile_lo + sigma + NS * k, tile_lo + ntiles - 1)) * kTile + trow, T - 1);
@@ -314,19 +317,11 @@ LBF_INLINE void item_f32_split(const BlockDesc& d, int item, int nbg, uint32_t* 
                     __builtin_amdgcn_sched_barrier(0);         // one K-step's loads at a time
                 }
             }
-#pragma unroll
-            for (int kk = 0; kk < NK; ++kk) {
-                const int off = 4 * ((2 * kk + h) ^ sw);
-                const V a = __builtin_bit_cast(V, *reinterpret_cast<const u32x4*>(ax0 + off));
-                const V b = __builtin_bit_cast(V, *reinterpret_cast<const u32x4*>(ax0 + kARow + off));
-#pragma unroll
-                for (int p = P - 1; p >= 0; --p) mfma4(a, b, wr[p][kk], wi[p][kk]);   // the small pieces first
-            }
             __builtin_amdgcn_sched_barrier(0);
             if (!late) epilogue(k);
+        } else {
+            store_chunks(k + 1);
         }
-        __builtin_amdgcn_sched_barrier(0);
-        store_chunks(k + 1);
         __syncthreads();
     }
     if (!idle) {

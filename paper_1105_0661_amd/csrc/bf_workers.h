@@ -283,6 +283,82 @@ template <> LBF_INLINE void unpack2<CT_BF16>(uint32_t w, float& re, float& im) {
     im = __uint_as_float(w & 0xffff0000u);
 }
 
+// The sample loaders of a work group: one step's NS tiles from HBM into
+// registers (16-byte loads), then converted into LDS.  What a step needs of
+// addresses is in scalar registers (the descriptor, moved to the tile) or in
+// immediate offsets, so a wave spends its vector instructions on the
+// conversions: with addresses formed per chunk the loaders took 310 of the
+// 520 vector instructions of a step (ci16, 64 stations), which do not run
+// beside the MFMAs.
+template <int XT, int CT, int NK, int NS>
+struct TileLoader {
+    static constexpr int BYTES = sample_bytes(XT);
+    static constexpr int SPC = Chunk<XT, CT>::samples;     // samples per 16-byte chunk
+    static constexpr int CPS = kTile / SPC;                // chunks per station per tile
+    static constexpr int SP = padded_stations(NK);
+    static constexpr int CPT = chunks_per_thread(NS, SP, CPS);
+    static constexpr int SPI = kLoaders / CPS;             // stations from one chunk of a thread to the next
+    static constexpr bool WIDE = SP * CPS >= kLoaders;     // a tile takes every thread: the stream depends on i only
+    static_assert(SPI % 8 == 0, "a thread's chunks share their place in the station group");
+
+    const void* x;
+    uint32_t stride_bytes, voff;
+    int S, T, c, tile_lo, ntiles, sg0, s0;
+    int w0, w1;                                            // LDS words of chunk 0; of the stations 16 further (SPI = 16)
+
+    LBF_INLINE void init(const BlockDesc& d, const ItemPos& ip) {
+        const int tid = threadIdx.x, q = chunk_q(tid, CPS), s = chunk_station(tid, 0, SP, CPS);
+        x = d.x;
+        S = d.S, T = d.T, c = ip.c, tile_lo = ip.tile_lo, ntiles = ip.ntiles;
+        stride_bytes = (uint32_t)((size_t)d.C * T * BYTES);
+        sg0 = __builtin_amdgcn_readfirstlane(chunk_stream(tid, 0, SP, CPS));
+        s0 = __builtin_amdgcn_readfirstlane(s);            // first station of the wave's first chunk
+        // threads past the step's chunks load nothing
+        voff = sg0 < NS ? chunk_off(s, q, stride_bytes) : kNoStore;
+        const int so = WIDE ? 0 : sg0 * 2 * kATileWords;
+        w0 = so + a_word(q * SPC, 0, s);
+        w1 = SPI == 16 ? so + a_word(q * SPC, 0, s ^ 16) : w0;
+        __asm__ volatile("" : "+v"(w0), "+v"(w1));
+    }
+    LBF_INLINE int stream(int i) const { return WIDE ? chunk_stream(0, i, SP, CPS) : sg0 + chunk_stream(0, i, SP, CPS); }
+    LBF_INLINE int first_station(int i) const { return s0 + (WIDE ? chunk_station(0, i, SP, CPS) : 0); }
+
+    LBF_INLINE void load(int k, u32x4 (&dst)[CPT]) const {
+#pragma unroll
+        for (int i = 0; i < CPT; ++i) {
+            const int g = first_station(i) & ~7;
+            const uint32_t off = tile_off(c, T, stream_tile(stream(i), k, NS, tile_lo, ntiles) * kTile, BYTES);
+            const uint64_t base = reinterpret_cast<uint64_t>(x) + group_base(g, stride_bytes) + off;
+            const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)base);
+            const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(base >> 32));
+            const uint32_t n = __builtin_amdgcn_readfirstlane(tile_range(g, S, stride_bytes, off));
+            const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+                reinterpret_cast<void*>(((uint64_t)hi << 32) | lo), (short)0, (int)n, 0x00020000);
+            dst[i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)voff, 0, 0));
+        }
+    }
+    // chunk i holds a station of the K-steps (uniform): the padded ones are not staged
+    LBF_INLINE bool staged(int i) const {
+        if (NS * SP * CPS < kLoaders && sg0 >= NS) return false;
+        return SP == 8 * NK || first_station(i) < 8 * NK;
+    }
+    LBF_INLINE void store(uint32_t* at, int k, int i, const u32x4 (&src)[CPT]) const {
+        if (!staged(i)) return;
+        // stations SPI further on: 32 words on for 32 stations (the swizzle
+        // works on 32-station blocks), the other base for 16
+        const int ds = WIDE ? chunk_station(0, i, SP, CPS) : 0;
+        const int sg = chunk_stream(0, i, SP, CPS);        // beside the thread's own in w0
+        uint32_t* ab = at + (ds & 16 ? w1 : w0) + (k & 1) * kATileWords + sg * 2 * kATileWords + (ds & ~31);
+#pragma unroll
+        for (int js = 0; js < SPC; ++js) {
+            uint32_t fx, fy;
+            Chunk<XT, CT>::xy(src[i], js, fx, fy);
+            ab[2 * js * kARow] = fx;
+            ab[(2 * js + 1) * kARow] = fy;
+        }
+    }
+};
+
 // Floats of LDS the incoherent-beam form of item_h_fast adds: per step
 // parity, sample stream, wave of the stream and tile sample, four sums.
 constexpr int kIncLdsFloats = 2 * 8 * kTile * 4;
@@ -300,12 +376,9 @@ constexpr int kIncLdsFloats = 2 * 8 * kTile * 4;
 template <int XT, int CT, int PR, int TI, int NK, int NS, bool INC = false>
 LBF_INLINE void item_h_fast(const BlockDesc& d, int item, int nbg, uint32_t* at) {
     typedef typename MfmaH<CT>::vec V;
-    constexpr int BYTES = sample_bytes(XT);
     constexpr int NBT = 8 / NS;                            // beam tiles per item
-    constexpr int SPC = Chunk<XT, CT>::samples;            // samples per 16-byte chunk
-    constexpr int CPS = kTile / SPC;                       // chunks per station per tile
-    constexpr int CPTILE = 8 * NK * CPS;                   // chunks per tile
-    constexpr int CPT = (NS * CPTILE + kThreadsH - 1) / kThreadsH;   // chunks per thread per step
+    typedef TileLoader<XT, CT, NK, NS> Loader;
+    constexpr int CPT = Loader::CPT;                       // chunks per thread per step
     // item = (channel, beam group, segment of sample tiles: seg_tiles)
     const int T = d.T;
     const ItemPos ip = item_pos(d, item, nbg);             // tiles [tile_lo, tile_lo + ntiles)
@@ -320,7 +393,6 @@ LBF_INLINE void item_h_fast(const BlockDesc& d, int item, int nbg, uint32_t* at)
     // the matrix pipe to itself
     const bool idle = d.b0 + (bg * NBT + bt) * kTile >= d.b1;
     const int nsteps = (ntiles + NS - 1) / NS;
-    const uint32_t stride_bytes = (uint32_t)((size_t)d.C * T * BYTES);
     const int T2 = PR == PR_VOLT ? T : T / TI;
     const __amdgpu_buffer_rsrc_t ors = channel_rsrc(d, c, out_channel_bytes(d, PR, T2));
 
@@ -340,39 +412,13 @@ LBF_INLINE void item_h_fast(const BlockDesc& d, int item, int nbg, uint32_t* at)
         }
     }
 
-    // loaders: chunk j = tid + 512 i of a step covers stream j / CPTILE,
-    // station (j % CPTILE) / CPS and samples SPC * (j % CPS) + [0, SPC)
+    Loader ld;
+    ld.init(d, ip);
     u32x4 raw[CPT];
-    auto load_chunks_to = [&](int k, u32x4 (&dst)[CPT]) {
-#pragma unroll
-        for (int i = 0; i < CPT; ++i) {
-            const Chunk16 ch = h_chunk(tid + kThreadsH * i, k, NS, CPTILE, CPS, tile_lo, ntiles);
-            // descriptor over the whole planes of the group's stations, the
-            // channel in the offset: a ragged last tile reads past the end of
-            // the channel into the next one, or past the last valid station
-            // (out of range: zeros), never past the array
-            const __amdgpu_buffer_rsrc_t rs = group_rsrc(d.x, ch.s & ~7, S, stride_bytes);
-            const uint32_t off = sample_off(ch.s & 7, stride_bytes, c, T, ch.tile * kTile + ch.q * SPC, BYTES);
-            dst[i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)off, 0, 0));
-        }
-    };
-    auto load_chunks = [&](int k) { load_chunks_to(k, raw); };
-    auto store_chunk_from = [&](int k, int i, const u32x4 (&src)[CPT]) {
-        const int j = tid + kThreadsH * i;
-        const int sg = j / CPTILE, jt = j % CPTILE, s = jt / CPS, q = jt % CPS;
-        if (NS * CPTILE % kThreadsH == 0 || j < NS * CPTILE) {
-            uint32_t* ab = at + (sg * 2 + (k & 1)) * kATileWords;
-#pragma unroll
-            for (int js = 0; js < SPC; ++js) {
-                uint32_t fx, fy;
-                Chunk<XT, CT>::xy(src[i], js, fx, fy);
-                const int t = q * SPC + js;
-                ab[a_word(t, 0, s)] = fx;
-                ab[a_word(t, 1, s)] = fy;
-            }
-        }
-    };
-    auto store_chunk = [&](int k, int i) { store_chunk_from(k, i, raw); };
+    auto load_chunks_to = [&](int k, u32x4 (&dst)[CPT]) { ld.load(k, dst); };
+    auto load_chunks = [&](int k) { ld.load(k, raw); };
+    auto store_chunk_from = [&](int k, int i, const u32x4 (&src)[CPT]) { ld.store(at, k, i, src); };
+    auto store_chunk = [&](int k, int i) { ld.store(at, k, i, raw); };
 
     // One step k, written out in the order it should run: K-step kk's four
     // MFMAs (operands read one K-step ahead from LDS), then 1/NK of the

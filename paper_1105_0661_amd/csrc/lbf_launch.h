@@ -50,6 +50,13 @@ hipError_t launch_split_ci8(const BlockDesc& d, hipStream_t st);    // FP32, com
 hipError_t launch_split_ci16(const BlockDesc& d, hipStream_t st);
 hipError_t launch_fast_f16(const BlockDesc& d, hipStream_t st);
 hipError_t launch_fast_bf16(const BlockDesc& d, hipStream_t st);
+// FP16/BF16 fast kernels of one block part (n work items, nbg beam groups) by sample type
+hipError_t launch_f16_ci8(const BlockDesc& d, int nbg, int n, hipStream_t st);
+hipError_t launch_f16_ci16(const BlockDesc& d, int nbg, int n, hipStream_t st);
+hipError_t launch_f16_cf32(const BlockDesc& d, int nbg, int n, hipStream_t st);
+hipError_t launch_bf16_ci8(const BlockDesc& d, int nbg, int n, hipStream_t st);
+hipError_t launch_bf16_ci16(const BlockDesc& d, int nbg, int n, hipStream_t st);
+hipError_t launch_bf16_cf32(const BlockDesc& d, int nbg, int n, hipStream_t st);
 // stage == nullptr: staging from the stream-ordered pool; else block j has
 // cap[j] bytes of caller staging at stage[j] (blocks whose staging holds all
 // their channels share the persistent launches, the others run alone in
