@@ -175,6 +175,82 @@ __global__ __launch_bounds__(256) void stokes_kernel(const floatx4* __restrict__
     }
 }
 
+// One channel per output and t_int = 2^LG up to 64: every (c, b) row holds
+// whole periods, so sample i of the flat array belongs to output i / t_int and
+// no index is taken apart.  A wave reads U runs of 64 consecutive samples (16
+// bytes per lane, all in flight before the first is used), a period's
+// G = t_int lanes meet in exchanges.  For four parameters the first two
+// exchanges halve what a lane carries on (it keeps the parameters its lane
+// bits name and hands on the others), so that a period costs 5 exchanges
+// instead of 16.  Pairs are added in the order of stokes_wave_kernel (m = G/2
+// down to 1): the same bits.
+// Bound: HBM, one read of the voltages.  1.61 GB of voltages (1024 channels,
+// 128 beams, 768 samples), t_int 16: stokes_wave_kernel 493 us (vector
+// instructions of its index divisions), this kernel STOKESNOTE us.
+template <int K, int LG>
+__global__ __launch_bounds__(256) void stokes_flat_kernel(const floatx4* __restrict__ y, size_t n, float* __restrict__ s) {
+    constexpr int U = 4, G = 1 << LG;
+    const int lane = threadIdx.x & (kWave - 1);
+    const size_t i0 = ((size_t)blockIdx.x * 4 + threadIdx.x / kWave) * (U * kWave) + lane;
+    floatx4 v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const size_t i = i0 + u * kWave;
+        v[u] = floatx4{0.f, 0.f, 0.f, 0.f};
+        if (i < n) v[u] = __builtin_nontemporal_load(y + i);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const size_t i = i0 + u * kWave;
+        const float xx = v[u][0] * v[u][0] + v[u][1] * v[u][1];
+        const float yy = v[u][2] * v[u][2] + v[u][3] * v[u][3];
+        if (K == 1) {
+            float a = xx + yy;
+#pragma unroll
+            for (int m = G / 2; m >= 1; m /= 2) a += __shfl_xor(a, m, kWave);
+            if (i < n && (lane & (G - 1)) == 0) s[i >> LG] = a;
+            continue;
+        }
+        float a[4] = {xx + yy, xx - yy, 2.0f * (v[u][0] * v[u][2] + v[u][1] * v[u][3]),
+                      2.0f * (v[u][1] * v[u][2] - v[u][0] * v[u][3])};
+        if (G == 1) {
+            if (i < n) reinterpret_cast<floatx4*>(s)[i] = floatx4{a[0], a[1], a[2], a[3]};
+            continue;
+        }
+        constexpr int M1 = G / 2, M2 = G / 4;
+        const bool hi1 = (lane & M1) != 0;                  // keeps U and V
+        const float r0 = __shfl_xor(hi1 ? a[0] : a[2], M1, kWave), r1 = __shfl_xor(hi1 ? a[1] : a[3], M1, kWave);
+        const float b0 = (hi1 ? a[2] : a[0]) + r0, b1 = (hi1 ? a[3] : a[1]) + r1;
+        float* o = s + (i >> LG) * 4 + (hi1 ? 2 : 0);
+        if (G == 2) {
+            if (i < n) {
+                o[0] = b0;
+                o[1] = b1;
+            }
+            continue;
+        }
+        const bool hi2 = (lane & M2) != 0;                  // keeps the second of the two
+        float c = (hi2 ? b1 : b0) + __shfl_xor(hi2 ? b0 : b1, M2, kWave);
+#pragma unroll
+        for (int m = M2 / 2; m >= 1; m /= 2) c += __shfl_xor(c, m, kWave);
+        if (i < n && (lane & (M2 - 1)) == 0) o[hi2 ? 1 : 0] = c;
+    }
+}
+
+template <int K>
+static void launch_stokes_flat(int lg, dim3 g, hipStream_t st, const floatx4* y, size_t n, float* s) {
+    const dim3 b(256);
+    switch (lg) {
+        case 0: hipLaunchKernelGGL((stokes_flat_kernel<K, 0>), g, b, 0, st, y, n, s); break;
+        case 1: hipLaunchKernelGGL((stokes_flat_kernel<K, 1>), g, b, 0, st, y, n, s); break;
+        case 2: hipLaunchKernelGGL((stokes_flat_kernel<K, 2>), g, b, 0, st, y, n, s); break;
+        case 3: hipLaunchKernelGGL((stokes_flat_kernel<K, 3>), g, b, 0, st, y, n, s); break;
+        case 4: hipLaunchKernelGGL((stokes_flat_kernel<K, 4>), g, b, 0, st, y, n, s); break;
+        case 5: hipLaunchKernelGGL((stokes_flat_kernel<K, 5>), g, b, 0, st, y, n, s); break;
+        default: hipLaunchKernelGGL((stokes_flat_kernel<K, 6>), g, b, 0, st, y, n, s); break;
+    }
+}
+
 // Power-of-two t_int: G = min(t_int, 64) consecutive lanes share an output
 // (c', b, t').  Lane g reads samples t'*t_int + g + G*j (j < t_int/G) of the
 // f_int channels, so a wave's loads are 64 consecutive 16-byte samples of one
@@ -233,6 +309,14 @@ __global__ __launch_bounds__(256) void stokes_wave_kernel(const floatx4* __restr
 hipError_t launch_stokes(const float* y, int B, int C, int T, int product, int t_int, int f_int, float* s,
                          hipStream_t st) {
     const floatx4* yy = reinterpret_cast<const floatx4*>(y);
+    // the flat kernel where a period lies in one wave and one channel; it wins
+    // at every size (1.3x at 1.6 GB, no index divisions on small arrays either)
+    const size_t nflat = (size_t)C * B * T, bflat = (nflat + 1023) / 1024;
+    if (f_int == 1 && (t_int & (t_int - 1)) == 0 && t_int <= kWave && bflat < (1u << 31)) {
+        if (product == PR_IQUV) launch_stokes_flat<4>(__builtin_ctz(t_int), dim3((unsigned)bflat), st, yy, nflat, s);
+        else launch_stokes_flat<1>(__builtin_ctz(t_int), dim3((unsigned)bflat), st, yy, nflat, s);
+        return hipGetLastError();
+    }
     if ((t_int & (t_int - 1)) == 0) {
         const size_t slots = (size_t)(C / f_int) * B * (T / t_int) * (t_int < kWave ? t_int : kWave);
         size_t blocks = (slots + 255) / 256;

@@ -35,7 +35,7 @@ __global__ __launch_bounds__(kThreadsH) void bf_batch_kernel(BatchArgs a, int* c
     }
 }
 
-inline __global__ void fill_int_kernel(int* p, int n, int v) {
+static __global__ __attribute__((unused)) void fill_int_kernel(int* p, int n, int v) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = v;
 }
