@@ -186,7 +186,7 @@ __global__ __launch_bounds__(256) void stokes_kernel(const floatx4* __restrict__
 // down to 1): the same bits.
 // Bound: HBM, one read of the voltages.  1.61 GB of voltages (1024 channels,
 // 128 beams, 768 samples), t_int 16: stokes_wave_kernel 493 us (vector
-// instructions of its index divisions), this kernel STOKESNOTE us.
+// instructions of its index divisions), this kernel 313 us.
 template <int K, int LG>
 __global__ __launch_bounds__(256) void stokes_flat_kernel(const floatx4* __restrict__ y, size_t n, float* __restrict__ s) {
     constexpr int U = 4, G = 1 << LG;

@@ -25,7 +25,7 @@ namespace lbf {
 // items remain to keep every compute unit busy to the end.  A block too small
 // to give every compute unit an item takes shorter segments, down to the 4
 // tiles that 4 sample streams work on at once: 16 channels of 1024 samples
-// (8 stations, 4 beams, FP32) took 15.2 us in 32 items of 24 tiles, SEGNOTE us
+// (8 stations, 4 beams, FP32) took 15.2 us in 32 items of 24 tiles, 6.6 us
 // in 128 of 4.
 constexpr int kSegTiles = 24, kSegTilesMax = 192, kMinItems = 2048;
 constexpr int kSegTilesMin = 4, kComputeUnits = kXcds * kCusPerXcd;
@@ -133,6 +133,14 @@ LBF_HD uint64_t out_base(const BlockDesc& d, int c, uint32_t channel_bytes) {
 
 // voltages y[b][t][p] of the channel, 16 bytes per sample
 LBF_HD uint32_t volt_off(int beam, int T, int t) { return ((uint32_t)beam * T + t) * 16u; }
+
+// Stokes straight into the final order [b][k][t'][c] (order 0): parameter 0;
+// the others follow in planes of stokes_plane bytes.  One descriptor over the
+// whole output, which direct_store keeps small.
+LBF_HD uint32_t stokes_plane(const BlockDesc& d, int T2) { return (uint32_t)T2 * (uint32_t)d.C * 4u; }
+LBF_HD uint32_t stokes_off_final(const BlockDesc& d, int c, int T2, int tq, int beam, int K) {
+    return (uint32_t)beam * (uint32_t)K * stokes_plane(d, T2) + ((uint32_t)tq * (uint32_t)d.C + (uint32_t)c) * 4u;
+}
 
 // Stokes s[t'][b][k] of the channel, rows of ld floats: 16 bytes (IQUV) or 4 (I)
 LBF_HD uint32_t stokes_off(int tq, int ld, int beam, int K) {

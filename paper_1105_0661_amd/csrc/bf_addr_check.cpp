@@ -57,6 +57,11 @@ int ti_of(const BlockDesc& d) { return d.product == PR_VOLT ? 1 : d.t_int; }
 // the output descriptor of channel c and its buffer
 void out_desc(const BlockDesc& d, int c, uint64_t* base, uint64_t* range, uint64_t* buf) {
     const int T2 = d.T / ti_of(d);
+    if (d.product != PR_VOLT && d.order == 0) {
+        *base = 0;
+        *range = *buf = (uint64_t)d.B * (d.product == PR_IQUV ? 4 : 1) * T2 * d.C * 4u;
+        return;
+    }
     const uint32_t bpc = out_channel_bytes(d, d.product, T2);
     *base = out_base(d, c, bpc);
     *range = bpc;
@@ -82,6 +87,16 @@ void stores_of_tile(Walk& w, const BlockDesc& d, int c, int beam, int bend, int 
     for (int o = 0; o < 16 / TI; ++o) {
         const int tq = (tile * kTile + 16 * h) / TI + o;
         const bool ok = tile_ok && beam < bend && tq < T2;
+        if (d.order == 0) {                                    // one store per parameter, counted as one access
+            for (int k = 0; k < K; ++k) {
+                const uint32_t off = (ok ? stokes_off_final(d, c, T2, tq, beam, K) : kNoStore) + k * stokes_plane(d, T2);
+                const uint64_t o64 = ok ? (((uint64_t)beam * K + k) * T2 + tq) * d.C * 4u + (uint64_t)c * 4u
+                                        : kNoStore + (uint64_t)k * stokes_plane(d, T2);
+                w.access("Stokes store", base, range, o64, off, 4, buf, ok);
+                w.n -= k > 0;
+            }
+            continue;
+        }
         const uint32_t off = ok ? stokes_off(tq, d.ld_row, beam, K) : kNoStore;
         const uint64_t o64 = ok ? ((uint64_t)tq * d.ld_row + (uint64_t)beam * K) * 4u : kNoStore;
         w.access("Stokes store", base, range, o64, off, 4 * K, buf, ok);
@@ -274,7 +289,7 @@ int check_block_addressing(const BlockDesc& d0, bool channel_major, size_t cap, 
     if (channel_major) d.order = 1;
     BlockDesc passes[1];
     int nc = d.C;
-    const bool staged = needs_staging(d);
+    const bool staged = needs_staging(d) && (cap || !direct_store(d));
     if (staged) {
         // as launch_beamform_staged: channel passes into the staging buffer
         nc = cap ? staging_chunk(d, cap) : d.C;

@@ -468,12 +468,28 @@ LBF_INLINE __amdgpu_buffer_rsrc_t channel_rsrc(const BlockDesc& d, int c, uint32
                                              (int)bytes_per_channel, 0x00020000);
 }
 
-// The Stokes parameters of one (t', beam) into the channel-major s[t'][b][k]
-// of its channel (rows of ld floats per t'): one 16-byte store for IQUV.
+// output descriptor of a Stokes item: its channel of the channel-major
+// staging (order 1), or the whole output in its final order
+LBF_INLINE __amdgpu_buffer_rsrc_t stokes_rsrc(const BlockDesc& d, int c, int PR, int T2) {
+    if (d.order == 1) return channel_rsrc(d, c, out_channel_bytes(d, PR, T2));
+    return __builtin_amdgcn_make_buffer_rsrc(d.out, (short)0, (int)(stokes_plane(d, T2) * (uint32_t)d.B * (PR == PR_IQUV ? 4u : 1u)),
+                                             0x00020000);
+}
+
+// The Stokes parameters of one (t', beam): one 16-byte store for IQUV into
+// the channel-major s[t'][b][k] of its channel (rows of ld_row floats per
+// t'), or one 4-byte store per parameter into the final order.
 template <int PR>
-LBF_INLINE void stokes_store_row(const float (&v)[4], __amdgpu_buffer_rsrc_t rs, int ld, int tq, int beam, bool ok) {
-    if (PR == PR_IQUV) {
-        const uint32_t off = store_off(ok, stokes_off(tq, ld, beam, 4));
+LBF_INLINE void stokes_store_row(const float (&v)[4], __amdgpu_buffer_rsrc_t rs, const BlockDesc& d, int c, int T2, int tq,
+                                 int beam, bool ok) {
+    constexpr int K = PR == PR_IQUV ? 4 : 1;
+    if (d.order == 0) {                                        // uniform
+        const uint32_t off = store_off(ok, stokes_off_final(d, c, T2, tq, beam, K)), pl = stokes_plane(d, T2);
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v[k]), rs, (int)(off + k * pl), 0, 0);
+    } else if (PR == PR_IQUV) {
+        const uint32_t off = store_off(ok, stokes_off(tq, d.ld_row, beam, 4));
         floatx4 w;
         w[0] = v[0];
         w[1] = v[1];
@@ -481,15 +497,15 @@ LBF_INLINE void stokes_store_row(const float (&v)[4], __amdgpu_buffer_rsrc_t rs,
         w[3] = v[3];
         __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, w), rs, (int)off, 0, 0);
     } else {
-        const uint32_t off = store_off(ok, stokes_off(tq, ld, beam, 1));
+        const uint32_t off = store_off(ok, stokes_off(tq, d.ld_row, beam, 1));
         __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v[0]), rs, (int)off, 0, 0);
     }
 }
 
-// Stokes of one 32x32 tile into channel-major s[t'][b][k] of its channel
+// Stokes of one 32x32 tile
 template <int PR, int TI>
-LBF_INLINE void stokes_store_cm(const floatx16 (&acc)[4], __amdgpu_buffer_rsrc_t rs, int ld, int T2, int beam, int t0,
-                                int h, bool ok) {
+LBF_INLINE void stokes_store_cm(const floatx16 (&acc)[4], __amdgpu_buffer_rsrc_t rs, const BlockDesc& d, int c, int T2,
+                                int beam, int t0, int h, bool ok) {
     constexpr int NOUT = 16 / TI;
     const int tq0 = (t0 + 16 * h) / TI;
 #pragma unroll
@@ -498,7 +514,7 @@ LBF_INLINE void stokes_store_cm(const floatx16 (&acc)[4], __amdgpu_buffer_rsrc_t
         stokes_sums<PR, TI>(acc, o * TI, sm);
         stokes_from_sums<PR>(sm, v);
         const int tq = tq0 + o;
-        stokes_store_row<PR>(v, rs, ld, tq, beam, ok && tq < T2);
+        stokes_store_row<PR>(v, rs, d, c, T2, tq, beam, ok && tq < T2);
     }
 }
 
@@ -677,6 +693,16 @@ inline int block_items(const BlockDesc& d, int* nbg) {
 __host__ __device__ constexpr int staging_ld(int B, int K) { return (B * K + 31) & ~31; }
 
 __host__ __device__ constexpr int sample_bytes(int xtype) { return xtype == XT_CI8 ? 4 : xtype == XT_CI16 ? 8 : 16; }
+
+// Stokes outputs of at most this many bytes go from the fast workers straight
+// into the final order: their scattered 4-byte stores still meet in the
+// caches, and the call needs neither staging (15 us of host time to take and
+// give back) nor a reorder.  Whole calls one after the other, staged against
+// direct: 0.02 MB 30.0 / 10.5 us, 1.6 MB 31.4 / 10.5, 6.3 MB 30.8 / 16.4 and
+// 31.0 / 23.7, 12.6 MB 32.9 / 26.0, 25 MB 40.4 / 40.8, with t_int 1 38.2 /
+// 65.2, 8192 channels 748 / 801, 100 MB 164 / 243: the gain is gone between
+// 12 and 25 MB, the earlier the shorter t_int, hence 8 MiB.
+constexpr size_t kDirectBytes = (size_t)8 << 20;
 
 // The fast workers take up to 64 stations of complex int8/int16/f32 samples,
 // voltages or Stokes with t_int <= 16 and no channel integration, and 8

@@ -99,6 +99,11 @@ bool needs_staging(const BlockDesc& d) {
     return (d.order == 0 && fast_path(d)) || fast_path_fint(d);
 }
 
+bool direct_store(const BlockDesc& d) {
+    return needs_staging(d) && d.order == 0 && d.f_int == 1 &&
+           (size_t)d.B * (d.product == PR_IQUV ? 4 : 1) * (d.T / d.t_int) * d.C * sizeof(float) <= kDirectBytes;
+}
+
 bool fuses_incoherent(const BlockDesc& d) {
     return fast_path(d) && d.ctype != CT_F32 && d.product != PR_VOLT && fast_h_streams(d) >= 2;
 }
@@ -194,7 +199,7 @@ hipError_t noalloc_scratch(void** p) {
 // lbf_beamform: the fast workers where they apply, the generic ones
 // otherwise; the staging of a whole block comes from the stream-ordered pool.
 hipError_t launch_beamform(const BlockDesc& d, hipStream_t st) {
-    if (!needs_staging(d)) return launch_beamform_direct(d, st);
+    if (!needs_staging(d) || direct_store(d)) return launch_beamform_direct(d, st);
     const size_t bytes = (size_t)d.C * staging_channel_bytes(d);
     void* stage = nullptr;
     hipError_t e = staging_alloc(&stage, bytes, st);

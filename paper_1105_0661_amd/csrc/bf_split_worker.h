@@ -87,9 +87,10 @@ LBF_INLINE uint32_t residual_i16x2(uint32_t w) {
 // Stokes or voltages of one tile out of scaled accumulators (weights times
 // 2^sc): as stokes_store_cm / volt_store_cm, with the scale taken out exactly
 template <int PR, int TI>
-LBF_INLINE void split_stokes_store(const floatx16 (&acc)[4], __amdgpu_buffer_rsrc_t rs, int ld, int T2, int beam, int t0,
-                                   int h, bool ok, int sc) {
+LBF_INLINE void split_stokes_store(const floatx16 (&acc)[4], __amdgpu_buffer_rsrc_t rs, const BlockDesc& d, int c,
+                                   int beam, int t0, int h, bool ok, int sc) {
     constexpr int NOUT = 16 / TI;
+    const int T2 = d.T / TI;
     const int tq0 = (t0 + 16 * h) / TI;
 #pragma unroll
     for (int o = 0; o < NOUT; ++o) {
@@ -99,14 +100,15 @@ LBF_INLINE void split_stokes_store(const floatx16 (&acc)[4], __amdgpu_buffer_rsr
 #pragma unroll
         for (int q = 0; q < (PR == PR_IQUV ? 4 : 1); ++q) v[q] = __builtin_amdgcn_ldexpf(v[q], -2 * sc);
         const int tq = tq0 + o;
-        stokes_store_row<PR>(v, rs, ld, tq, beam, ok && tq < T2);
+        stokes_store_row<PR>(v, rs, d, c, T2, tq, beam, ok && tq < T2);
         __builtin_amdgcn_sched_barrier(0);                     // one period's temporaries at a time
     }
 }
 
 template <int PR>
-LBF_INLINE void split_epilogue(const floatx16 (&acc)[4], __amdgpu_buffer_rsrc_t rs, int ld, int T, int t_int, int beam,
+LBF_INLINE void split_epilogue(const floatx16 (&acc)[4], __amdgpu_buffer_rsrc_t rs, const BlockDesc& d, int c, int beam,
                                int t0, int h, bool ok, int sc) {
+    const int T = d.T;
     if constexpr (PR == PR_VOLT) {
 #pragma unroll
         for (int k = 0; k < 16; ++k) {
@@ -119,12 +121,12 @@ LBF_INLINE void split_epilogue(const floatx16 (&acc)[4], __amdgpu_buffer_rsrc_t 
             if (k & 1) __builtin_amdgcn_sched_barrier(0);
         }
     } else {
-        switch (t_int) {                                       // uniform
-            case 1: split_stokes_store<PR, 1>(acc, rs, ld, T, beam, t0, h, ok, sc); break;
-            case 2: split_stokes_store<PR, 2>(acc, rs, ld, T / 2, beam, t0, h, ok, sc); break;
-            case 4: split_stokes_store<PR, 4>(acc, rs, ld, T / 4, beam, t0, h, ok, sc); break;
-            case 8: split_stokes_store<PR, 8>(acc, rs, ld, T / 8, beam, t0, h, ok, sc); break;
-            default: split_stokes_store<PR, 16>(acc, rs, ld, T / 16, beam, t0, h, ok, sc); break;
+        switch (d.t_int) {                                       // uniform
+            case 1: split_stokes_store<PR, 1>(acc, rs, d, c, beam, t0, h, ok, sc); break;
+            case 2: split_stokes_store<PR, 2>(acc, rs, d, c, beam, t0, h, ok, sc); break;
+            case 4: split_stokes_store<PR, 4>(acc, rs, d, c, beam, t0, h, ok, sc); break;
+            case 8: split_stokes_store<PR, 8>(acc, rs, d, c, beam, t0, h, ok, sc); break;
+            default: split_stokes_store<PR, 16>(acc, rs, d, c, beam, t0, h, ok, sc); break;
         }
     }
 }
@@ -150,7 +152,8 @@ LBF_INLINE void item_f32_split(const BlockDesc& d, int item, int nbg, uint32_t* 
     const int nsteps = (ntiles + NS - 1) / NS;
     const uint32_t stride_bytes = (uint32_t)((size_t)d.C * T * BYTES);
     const int T2 = PR == PR_VOLT ? T : T / d.t_int;
-    const __amdgpu_buffer_rsrc_t ors = channel_rsrc(d, c, out_channel_bytes(d, PR, T2));
+    const __amdgpu_buffer_rsrc_t ors =
+        PR == PR_VOLT ? channel_rsrc(d, c, out_channel_bytes(d, PR, T2)) : stokes_rsrc(d, c, PR, T2);
     const __amdgpu_buffer_rsrc_t wrs = weight_rsrc(d, c, 8);
 
     // samples one step ahead
@@ -259,7 +262,7 @@ LBF_INLINE void item_f32_split(const BlockDesc& d, int item, int nbg, uint32_t* 
         const bool ok = k >= 0 && tile < tile_lo + ntiles && beam_ok;
         int bm = beam, hh = h;
         __asm__ volatile("" : "+v"(bm), "+v"(hh));          // offsets formed anew for each tile
-        split_epilogue<PR>(acc, ors, d.ld_row, T, d.t_int, bm, tile * kTile, hh, ok, sc);
+        split_epilogue<PR>(acc, ors, d, c, bm, tile * kTile, hh, ok, sc);
     };
     const bool late = wave >= 4;                           // the second wave of each SIMD
     for (int k = 0; k < nsteps; ++k) {

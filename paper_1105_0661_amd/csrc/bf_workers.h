@@ -80,7 +80,7 @@ LBF_INLINE void item_f32_fast(const BlockDesc& d, int item, int nbg, float* pl) 
     const int ngrp = min(8, ((S + 7) / 8 + 1) & ~1);
     const uint32_t stride_bytes = (uint32_t)((size_t)d.C * T * BYTES);
     const int T2 = PR == PR_VOLT ? T : T / TI;
-    const __amdgpu_buffer_rsrc_t ors = channel_rsrc(d, c, out_channel_bytes(d, PR, T2));
+    const __amdgpu_buffer_rsrc_t ors = PR == PR_VOLT ? channel_rsrc(d, c, out_channel_bytes(d, PR, T2)) : stokes_rsrc(d, c, PR, T2);
     const int trow = tile_row_sample(r);
 
     stage_weights_f32_planes(pl, d, c, b0);
@@ -175,7 +175,7 @@ LBF_INLINE void item_f32_fast(const BlockDesc& d, int item, int nbg, float* pl) 
                 float v[4];
                 stokes_from_sums<PR>(sm[o], v);
                 const int tq = tq0 + o;
-                stokes_store_row<PR>(v, ors, d.ld_row, tq, beam, okprev && beam < B && tq < T2);
+                stokes_store_row<PR>(v, ors, d, c, T2, tq, beam, okprev && beam < B && tq < T2);
             }
         }
     };
@@ -183,7 +183,7 @@ LBF_INLINE void item_f32_fast(const BlockDesc& d, int item, int nbg, float* pl) 
         const int tile = tile_of(klast);
         const bool ok = klast >= 0 && beam < B;
         if (PR == PR_VOLT) volt_store_cm(prev, ors, T, beam, tile * kTile, h, ok);
-        else stokes_store_cm<PR, TI>(prev, ors, d.ld_row, T2, beam, tile * kTile, h, ok);
+        else stokes_store_cm<PR, TI>(prev, ors, d, c, T2, beam, tile * kTile, h, ok);
     };
 
     load_quad(0, 0, 0);
@@ -394,7 +394,7 @@ LBF_INLINE void item_h_fast(const BlockDesc& d, int item, int nbg, uint32_t* at)
     const bool idle = d.b0 + (bg * NBT + bt) * kTile >= d.b1;
     const int nsteps = (ntiles + NS - 1) / NS;
     const int T2 = PR == PR_VOLT ? T : T / TI;
-    const __amdgpu_buffer_rsrc_t ors = channel_rsrc(d, c, out_channel_bytes(d, PR, T2));
+    const __amdgpu_buffer_rsrc_t ors = PR == PR_VOLT ? channel_rsrc(d, c, out_channel_bytes(d, PR, T2)) : stokes_rsrc(d, c, PR, T2);
 
     // this wave's weights, both variants, all K-steps
     u32x4 wr[NK], wi[NK];
@@ -559,7 +559,7 @@ LBF_INLINE void item_h_fast(const BlockDesc& d, int item, int nbg, uint32_t* at)
                 float v[4];
                 stokes_from_sums<PR>(sm[o], v);
                 const int tq = tq0 + o;
-                stokes_store_row<PR>(v, ors, d.ld_row, tq, beam, okprev && tq < T2);
+                stokes_store_row<PR>(v, ors, d, c, T2, tq, beam, okprev && tq < T2);
             }
         }
         __syncthreads();
@@ -578,7 +578,7 @@ LBF_INLINE void item_h_fast(const BlockDesc& d, int item, int nbg, uint32_t* at)
         const int tile = tile_lo + sigma + NS * klast;
         const bool ok = klast >= 0 && tile < tile_lo + ntiles && beam < bend;
         if (PR == PR_VOLT) volt_store_cm(prev, ors, T, beam, tile * kTile, h, ok);
-        else stokes_store_cm<PR, TI>(prev, ors, d.ld_row, T2, beam, tile * kTile, h, ok);
+        else stokes_store_cm<PR, TI>(prev, ors, d, c, T2, beam, tile * kTile, h, ok);
     };
 
     load_chunks(0);

@@ -21,6 +21,10 @@ hipError_t launch_beamform(const BlockDesc& d, hipStream_t st);
 // caller-provided buffer of cap bytes (passes of staging_chunk(d, cap)
 // channels; hipErrorInvalidValue if not one channel fits).
 bool needs_staging(const BlockDesc& d);
+// lbf_beamform and lbf_beamform_incoherent store a small block's Stokes
+// straight into the final order instead (the entry points with staging of
+// their own do not)
+bool direct_store(const BlockDesc& d);
 // The block's incoherent beam is formed by its contraction: the fast FP16/BF16
 // worker with several sample streams (items of at most 128 beams, HBM-bound).  With more
 // beams that worker is bound by MFMA and VALU work, and a separate read of

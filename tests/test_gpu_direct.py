@@ -1,0 +1,39 @@
+"""Small blocks store their Stokes straight into the final order (up to 8 MiB
+of output); lbf_beamform_noalloc always goes through staging and the reorder.
+Both run the same worker, so the outputs are equal bit for bit, and nothing
+beside the output is written."""
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_1105_0661_amd import lbf  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+X = {"ci8": torch.int8, "ci16": torch.int16, "cf32": torch.float32}
+W = {"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16}
+
+
+# the last two outputs: 8 MiB exactly (direct), and one channel more (staged)
+@pytest.mark.parametrize("S,C,T,B,t_int", [(1, 1, 1, 1, 1), (13, 5, 112, 70, 4), (37, 33, 100, 33, 2), (64, 3, 1104, 129, 16),
+                                           (9, 7, 40, 300, 8), (5, 64, 1024, 32, 4), (5, 65, 1024, 32, 4)])
+@pytest.mark.parametrize("product", [lbf.STOKES_I, lbf.STOKES_IQUV], ids=["I", "IQUV"])
+@pytest.mark.parametrize("xt,ct", [("ci8", "f32"), ("ci16", "f32"), ("cf32", "f32"), ("ci8", "f16"), ("ci16", "bf16"),
+                                   ("cf32", "f16")])
+def test_direct_equals_staged(S, C, T, B, t_int, product, xt, ct):
+    g = torch.Generator(device="cuda").manual_seed(S * 1000 + B)
+    x = torch.randn((S, C, T, 2, 2), generator=g, device="cuda").mul_(30.0)
+    x = x if xt == "cf32" else x.round_().clamp_(-127, 127)
+    x, w = x.to(X[xt]), torch.randn((C, B, S, 2), generator=g, device="cuda").to(W[ct])
+    shape = lbf.output_shape(product, S, C, T, B, t_int)
+    n = 1
+    for v in shape:
+        n *= v
+    buf = torch.full((n + 128,), -7.0, device="cuda")
+    out = buf[64:64 + n].view(shape)
+    lbf.beamform(x, w, product, t_int, 1, out=out)
+    assert torch.equal(out, lbf.beamform_noalloc(x, w, product, t_int, 1))
+    assert (buf[:64] == -7.0).all() and (buf[64 + n:] == -7.0).all()
+    if ct != "f32":
+        both, inc = lbf.beamform_incoherent(x, w, product, t_int, 1)
+        assert torch.equal(both, out)
