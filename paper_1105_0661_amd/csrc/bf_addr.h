@@ -99,11 +99,14 @@ LBF_HD uint32_t tile_range(int s0, int S, uint32_t stride_bytes, uint32_t off) {
 }
 
 // The sample loaders of the workers that stage tiles in LDS: a tile's 16-byte
-// chunks (spc samples of one station), stations padded to sp (16, 32 or 64),
-// are dealt to the work group's threads, chunk i of thread tid being number
+// chunks (cps of them per station), stations padded to sp (16, 32 or 64), are
+// dealt to the work group's threads, chunk i of thread tid being number
 // tid + kLoaders i of the step's ns tiles.  All the divisors are powers of
 // two, a wave's chunks belong to one group of 8 stations and one stream, and
-// the station's number within its group does not depend on i.
+// the station's number within its group does not depend on i.  (Waves of 8
+// chunks of 8 stations store to LDS with 60 % fewer bank conflicts, which
+// changed no time, and read 128-byte runs instead of 256 or 512: an HBM-bound
+// block, 64 stations and 10 beams as voltages, took 1041 instead of 1006 us.)
 constexpr int kLoaders = 512;
 
 LBF_HD constexpr int padded_stations(int nk) { return nk <= 2 ? 16 : nk <= 4 ? 32 : 64; }

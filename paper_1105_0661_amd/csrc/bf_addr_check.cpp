@@ -144,8 +144,8 @@ void walk_h(Walk& w, const BlockDesc& d, int lo, int hi) {
     }
 }
 
-// items [lo, hi) of the FP32 split worker (complex int8/int16 samples), its
-// residual and exact-path loads included
+// items [lo, hi) of the FP32 split worker, its residual and exact-path loads
+// included
 void walk_split(Walk& w, const BlockDesc& d, int lo, int hi) {
     const int bytes = sample_bytes(d.xtype);
     const uint64_t xbuf = (uint64_t)d.S * d.C * d.T * bytes, wbuf = (uint64_t)d.C * d.B * d.S * 8;
@@ -163,16 +163,20 @@ void walk_split(Walk& w, const BlockDesc& d, int lo, int hi) {
             const int lane = tid & 63, wave = tid / 64, r = lane & 31, h = lane >> 5, trow = tile_row_sample(r);
             const int bt = wave % NBT, sigma = wave / NBT;
             const int beam = d.b0 + (ip.bg * NBT + bt) * kTile + r;
-            for (int s = 0; s < 8 * NK; ++s) {
-                const bool ok = beam < d.b1 && s < d.S;
-                if (ok && ((uint64_t)beam * d.S + s) * 8u + 8u > weight_range(d, 8))
-                    return w.fail("weight load of beam %d station %d past its channel", beam, s);
+            for (int j = 0; j < NBT * kTile / 8; ++j) {        // weight rows: beam by wave, station by lane
+                const int bw = d.b0 + ip.bg * NBT * kTile + wave + 8 * j;
+                const bool ok = bw < d.b1 && lane < d.S;
+                if (ok && ((uint64_t)bw * d.S + lane) * 8u + 8u > weight_range(d, 8))
+                    return w.fail("weight load of beam %d station %d past its channel", bw, lane);
                 w.access("weight load", weight_base(d, ip.c, 8), weight_range(d, 8),
-                         ok ? ((uint64_t)beam * d.S + s) * 8u : kNoLoad, ok ? weight_off(beam, d.S, s, 8) : kNoLoad, 8,
+                         ok ? ((uint64_t)bw * d.S + lane) * 8u : kNoLoad, ok ? weight_off(bw, d.S, lane, 8) : kNoLoad, 8,
                          wbuf, false);
             }
-            // the loaders run one step ahead of the last one
-            for (int k = 0; k < nsteps + 1; ++k)
+            for (int s = 0; s < d.S; ++s)                      // the exact path's
+                w.access("weight load", weight_base(d, ip.c, 8), weight_range(d, 8), ((uint64_t)beam * d.S + s) * 8u,
+                         weight_off(beam, d.S, s, 8), 8, wbuf, false);
+            // the loaders run up to two steps ahead of the last one
+            for (int k = 0; k < nsteps + 2; ++k)
                 for (int i = 0; i < CPT; ++i) {
                     const int sg = chunk_stream(tid, i, SP, CPS), s = chunk_station(tid, i, SP, CPS), s0 = s & ~7;
                     if (sg >= NS) continue;                    // past the step's chunks: an out-of-range offset
@@ -195,7 +199,7 @@ void walk_split(Walk& w, const BlockDesc& d, int lo, int hi) {
     }
 }
 
-// items [lo, hi) of the FP32 worker of complex float samples
+// items [lo, hi) of the FP32 worker (complex float samples of few stations)
 void walk_f32(Walk& w, const BlockDesc& d, int lo, int hi) {
     const int bytes = sample_bytes(d.xtype);
     const uint64_t xbuf = (uint64_t)d.S * d.C * d.T * bytes, wbuf = (uint64_t)d.C * d.B * d.S * 8;
@@ -252,8 +256,8 @@ bool check_fast_addressing(const BlockDesc& d, int threads, uint64_t* accesses, 
     for (int p = 0; p < np; ++p) {
         int nbg;
         items[p] = d.ctype != CT_F32        ? block_items_fast_h(part[p], &nbg)
-                   : d.xtype == XT_CF32 ? block_items_fast_f32(part[p], &nbg)
-                                        : block_items_split(part[p], &nbg);
+                   : split_takes(d)     ? block_items_split(part[p], &nbg)
+                                        : block_items_fast_f32(part[p], &nbg);
     }
     threads = std::max(1, std::min(threads, 64));
     std::vector<Walk> w(threads * np);
@@ -264,7 +268,7 @@ bool check_fast_addressing(const BlockDesc& d, int threads, uint64_t* accesses, 
             Walk* wk = &w[p * threads + i];
             const BlockDesc* dp = &part[p];
             th.emplace_back([=] {
-                if (dp->ctype == CT_F32 && dp->xtype == XT_CF32) walk_f32(*wk, *dp, lo, hi);
+                if (dp->ctype == CT_F32 && !split_takes(*dp)) walk_f32(*wk, *dp, lo, hi);
                 else if (dp->ctype == CT_F32) walk_split(*wk, *dp, lo, hi);
                 else walk_h(*wk, *dp, lo, hi);
             });

@@ -1,7 +1,8 @@
-"""FP32 results of integer samples from FP16 pieces (the split worker): station
-counts at the edges of its K-steps and of its piece counts, samples over the
-whole int16 range (residuals beside the FP16 rounding), and weights the pieces
-cannot hold (the exact path), against 64-bit sums.
+"""FP32 results from FP16 pieces (the split worker): station counts at the
+edges of its K-steps and of its piece counts, samples over the whole int16
+range (residuals beside the FP16 rounding), float samples whose level changes
+by any factor, and weights and samples the pieces cannot hold (the exact
+path), against 64-bit sums.
 
 Bound: a chain of n FP32 operations on terms t_i is off by at most
 n 2^-24 sum |t_i|.  A voltage component sums 2 S products; two roundings per
@@ -100,6 +101,61 @@ def test_weights_outside_the_pieces(xtype, S, B):
     fin = torch.isfinite(ref)
     err = torch.where(fin, got - ref, torch.zeros_like(ref)).abs()
     assert (err <= (4 * S + 2) * 2.0 ** -24 * torch.where(torch.isfinite(mag), mag, torch.zeros_like(mag))).all()
+
+
+def _float_case(S, C, T, B, seed):
+    g = torch.Generator().manual_seed(seed)
+    x = torch.randn((S, C, T, 2, 2), generator=g) * 1000.0
+    a = torch.rand((C, B, S), generator=g, dtype=torch.float64) * (2.0 * math.pi)
+    return x, torch.stack([torch.cos(a), -torch.sin(a)], dim=-1).float()
+
+
+@pytest.mark.parametrize("S", [19, 20, 32, 33, 40, 41, 48, 49, 57, 64])
+def test_float_samples_at_the_edges(S):
+    B, T = (37, 100) if S % 2 else (130, 72)
+    x, w = _float_case(S, 2, T, B, S)
+    ref, mag = _voltages64(x, w)
+    assert ((_voltages(x, w) - ref).abs() <= (4 * S + 2) * 2.0 ** -24 * mag).all()
+    s = lbf.beamform(x.cuda(), w.cuda(), lbf.STOKES_I, 4).cpu().double()[:, 0]
+    i64 = (ref ** 2).sum((-1, -2)).reshape(2, B, T // 4, 4).sum(-1).permute(1, 2, 0)
+    bound = (2.0 * (4 * S + 2) + 16) * 2.0 ** -24 * (mag[..., 0] ** 2).sum(-1).reshape(2, B, T // 4, 4).sum(-1).permute(1, 2, 0)
+    assert ((s - i64).abs() <= bound).all()
+
+
+@pytest.mark.parametrize("S,T", [(20, 1100), (64, 400)])
+def test_float_samples_of_any_level(S, T):
+    # levels from 2^-60 to 2^60 in turn, inside tiles and from tile to tile; a
+    # burst in one sample, one weak station, a dead one, one dead polarisation,
+    # silence over whole tiles, an item that begins with silence
+    x, w = _float_case(S, 3, T, 70, S)
+    level = torch.ones(T)
+    for i, e in enumerate((0, 60, -60, 12, -9, 20)):
+        level[i * 50:i * 50 + 50] = 2.0 ** e
+    x[:, 0] *= level[None, :, None, None]
+    x[:, 1, T // 2, 0, 1] *= 2.0 ** 30
+    x[3] *= 2.0 ** -15
+    x[4] = 0.0
+    x[5, :, :, 1] = 0.0
+    x[:, 2, :130] = 0.0
+    x[:, 2, 200:210] *= 2.0 ** -110
+    ref, mag = _voltages64(x, w)
+    assert ((_voltages(x, w) - ref).abs() <= (4 * S + 2) * 2.0 ** -24 * mag + 2.0 ** -126).all()
+
+
+@pytest.mark.parametrize("S", [24, 64])
+def test_float_samples_not_finite(S):
+    x, w = _float_case(S, 2, 160, 40, S)
+    x[1, 0, 3, 0, 0] = float("inf")
+    x[S - 1, 0, 70, 1, 1] = float("nan")
+    x[2, 1, 159, 1, 0] = -float("inf")
+    x[0, 1, 100] = 3.0e38
+    ref, mag = _voltages64(x, w)
+    got = _voltages(x, w)
+    over = mag > 1.0e38                                     # where FP32 sums may overflow on the way
+    fin = torch.isfinite(ref) & ~over.expand_as(ref)
+    assert torch.equal(torch.isnan(got)[~over.expand_as(ref)], torch.isnan(ref)[~over.expand_as(ref)])
+    assert not torch.isfinite(got)[~torch.isfinite(ref)].any()
+    assert ((got - ref).abs() <= (4 * S + 2) * 2.0 ** -24 * mag)[fin].all()
 
 
 def test_unit_weights_are_exact():
