@@ -124,6 +124,13 @@ LBF_HD int stream_tile(int sg, int k, int ns, int tile_lo, int ntiles) {
     return tile_lo + (i < ntiles - 1 ? i : ntiles - 1);
 }
 
+// The FP16/BF16 worker's weight rows on their way into LDS, in items of at
+// least kRowSteps steps: 16 lanes to a
+// beam's row, 4 stations each; pass j is 32 beams further
+constexpr int kRowSteps = 8;
+LBF_HD constexpr int h_weight_row(int tid, int j) { return tid / 16 + 32 * j; }
+LBF_HD constexpr int h_weight_station(int tid) { return tid % 16 * 4; }
+
 // Output of one channel (order 1 staging, or voltages): one descriptor per
 // channel of the item's block, output index c - c0.
 LBF_HD uint32_t out_channel_bytes(const BlockDesc& d, int product, int T2) {

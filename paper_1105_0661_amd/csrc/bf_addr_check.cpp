@@ -121,10 +121,17 @@ void walk_h(Walk& w, const BlockDesc& d, int lo, int hi) {
             const int lane = tid & 63, wave = tid / 64, r = lane & 31, h = lane >> 5;
             const int bt = wave % NBT, sigma = wave / NBT;
             const int beam = d.b0 + (ip.bg * NBT + bt) * kTile + r;
-            for (int kk = 0; kk < NK; ++kk)
+            auto weights = [&](int bw, int s4) {
+                const bool ok = bw < d.b1 && s4 < d.S;
                 w.access("weight load", weight_base(d, ip.c, 4), weight_range(d, 4),
-                         ((uint64_t)beam * d.S + 8 * kk + 4 * h) * 4u, weight_off(beam, d.S, 8 * kk + 4 * h, 4), 16,
+                         ok ? ((uint64_t)bw * d.S + s4) * 4u : kNoLoad, ok ? weight_off(bw, d.S, s4, 4) : kNoLoad, 16,
                          wbuf, false);
+            };
+            if (nsteps >= kRowSteps)
+                for (int j = 0; j < NBT * kTile / 32; ++j)
+                    weights(d.b0 + ip.bg * NBT * kTile + h_weight_row(tid, j), h_weight_station(tid));
+            else
+                for (int kk = 0; kk < NK; ++kk) weights(beam, 8 * kk + 4 * h);
             // the loaders run up to two steps ahead of the last one
             for (int k = 0; k < nsteps + 2; ++k)
                 for (int i = 0; i < CPT; ++i) {

@@ -20,7 +20,7 @@ hipError_t launch_batch_bf16(int v, const BatchArgs& a, int* counter, hipStream_
 
 template <int XT, int CT, int PR, int NK, int NS>
 __global__ __launch_bounds__(kThreadsH) void bf_batch_kernel(BatchArgs a, int* counter) {
-    __shared__ __attribute__((aligned(16))) uint32_t at[NS * 2 * kATileWords];
+    __shared__ __attribute__((aligned(16))) uint32_t at[h_lds_words(NK, NS)];
     __shared__ int next;
     const int total = a.item_start[a.n];
     for (;;) {

@@ -459,6 +459,17 @@ LBF_INLINE uint32_t store_off(bool ok, uint32_t off) {
     return r;
 }
 
+// An offset past every weight descriptor: the load returns zero
+constexpr uint32_t kNoLoad = 0xfffffff0u;
+
+// a if ok, else b, as a lane select the compiler keeps (a plain ?: becomes a branch around the access)
+LBF_INLINE uint32_t select_off(bool ok, uint32_t a, uint32_t b) {
+    const uint64_t m = __builtin_amdgcn_ballot_w64(ok);
+    uint32_t r;
+    __asm__("v_cndmask_b32_e64 %0, %1, %2, %3" : "=v"(r) : "v"(b), "v"(a), "s"(m));
+    return r;
+}
+
 // output descriptor of channel c of the item's block (index c - c0)
 LBF_INLINE __amdgpu_buffer_rsrc_t channel_rsrc(const BlockDesc& d, int c, uint32_t bytes_per_channel) {
     const uint64_t base = reinterpret_cast<uint64_t>(d.out) + out_base(d, c, bytes_per_channel);

@@ -17,7 +17,7 @@ __global__ __launch_bounds__(kThreadsH) void bf_f32_fast_kernel(BlockDesc d, int
 // incoherent beam's partial sums in the INC form)
 template <int XT, int CT, int PR, int TI, int NK, int NS, bool INC>
 __global__ __launch_bounds__(kThreadsH) void bf_h_fast_kernel(BlockDesc d, int nbg, int nitems) {
-    __shared__ __attribute__((aligned(16))) uint32_t at[NS * 2 * kATileWords + (INC ? kIncLdsFloats : 0)];
+    __shared__ __attribute__((aligned(16))) uint32_t at[h_lds_words(NK, NS) + (INC ? kIncLdsFloats : 0)];
     item_h_fast<XT, CT, PR, TI, NK, NS, INC>(d, xcd_remap(blockIdx.x, nitems), nbg, at);
 }
 

@@ -79,17 +79,6 @@ inline int block_items_split(const BlockDesc& d, int* nbg) {
 // its largest one that the pieces hold to 24 bits
 constexpr float kSplitRange = 16384.0f;
 
-// An offset past every weight descriptor: the load returns zero
-constexpr uint32_t kNoLoad = 0xfffffff0u;
-
-// a if ok, else b, as a lane select the compiler keeps (a plain ?: becomes a branch around the access)
-LBF_INLINE uint32_t select_off(bool ok, uint32_t a, uint32_t b) {
-    const uint64_t m = __builtin_amdgcn_ballot_w64(ok);
-    uint32_t r;
-    __asm__("v_cndmask_b32_e64 %0, %1, %2, %3" : "=v"(r) : "v"(b), "v"(a), "s"(m));
-    return r;
-}
-
 LBF_INLINE uint32_t pack_h(_Float16 lo, _Float16 hi) {
     const halfx2 v = {lo, hi};
     return __builtin_bit_cast(uint32_t, v);

@@ -368,6 +368,12 @@ struct TileLoader {
     }
 };
 
+// Words of LDS of item_h_fast's tiles, or of the item's weights before them
+constexpr int h_lds_words(int NK, int NS) {
+    const int tiles = NS * 2 * kATileWords, weights = 8 / NS * kTile * (8 * NK + 4);
+    return tiles > weights ? tiles : weights;
+}
+
 // Floats of LDS the incoherent-beam form of item_h_fast adds: per step
 // parity, sample stream, wave of the stream and tile sample, four sums.
 constexpr int kIncLdsFloats = 2 * 8 * kTile * 4;
@@ -405,22 +411,6 @@ LBF_INLINE void item_h_fast(const BlockDesc& d, int item, int nbg, uint32_t* at)
     const int T2 = PR == PR_VOLT ? T : T / TI;
     const __amdgpu_buffer_rsrc_t ors = PR == PR_VOLT ? channel_rsrc(d, c, out_channel_bytes(d, PR, T2)) : stokes_rsrc(d, c, PR, T2);
 
-    // this wave's weights, both variants, all K-steps
-    u32x4 wr[NK], wi[NK];
-    {
-        const __amdgpu_buffer_rsrc_t rs = weight_rsrc(d, c, 4);
-#pragma unroll
-        for (int kk = 0; kk < NK; ++kk) {
-            const u32x4 w = __builtin_bit_cast(
-                u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)weight_off(beam, S, 8 * kk + 4 * h, 4), 0, 0));
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                wr[kk][i] = neg_hi(w[i]);
-                wi[kk][i] = swap16(w[i]);
-            }
-        }
-    }
-
     Loader ld;
     ld.init(d, ip);
     u32x4 raw[CPT];
@@ -428,6 +418,54 @@ LBF_INLINE void item_h_fast(const BlockDesc& d, int item, int nbg, uint32_t* at)
     auto load_chunks = [&](int k) { ld.load(k, raw); };
     auto store_chunk_from = [&](int k, int i, const u32x4 (&src)[CPT]) { ld.store(at, k, i, src); };
     auto store_chunk = [&](int k, int i) { ld.store(at, k, i, raw); };
+    load_chunks(0);
+
+    // This wave's weights, both variants, all K-steps; stations >= S and beams
+    // >= the block's as zeros.  A lane's own are 16-byte pieces of rows a
+    // whole beam apart, a cache line per lane and load.  Items of 8 steps and
+    // more read whole rows (16 lanes each) into LDS instead and take them from
+    // there; in shorter ones the two barriers cost more than the loads.
+    // Gathered against through LDS: 8192 channels of ci16, 128 beams, 12 steps
+    // an item 1066 / 1032 us, 1600 channels, 257 beams, 24 steps 502 / 476; 6
+    // steps, 253 beams of ci8 160 / 163, 189 of ci16 499 / 517.
+    u32x4 wr[NK], wi[NK];
+    {
+        const __amdgpu_buffer_rsrc_t rs = weight_rsrc(d, c, 4);
+        auto load_row = [&](int bw, int s4) {              // stations s4 .. s4 + 3 of beam bw
+            u32x4 v = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                rs, (int)select_off(bw < bend && s4 < S, weight_off(bw, S, s4, 4), kNoLoad), 0, 0));
+#pragma unroll
+            for (int i = 1; i < 4; ++i)
+                if (s4 + i >= S) v[i] = 0u;
+            return v;
+        };
+        auto take = [&](int kk, const u32x4& v) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                wr[kk][i] = neg_hi(v[i]);
+                wi[kk][i] = swap16(v[i]);
+            }
+        };
+        if (nsteps >= kRowSteps) {
+            constexpr int NBEAM = NBT * kTile, WROW = 8 * NK + 4;   // words per row: 4 mod 8, rows spread over the banks
+            const int row = h_weight_row(tid, 0), s4 = h_weight_station(tid);
+            u32x4 w[NBEAM / 32];
+#pragma unroll
+            for (int j = 0; j < NBEAM / 32; ++j) w[j] = load_row(d.b0 + bg * NBEAM + row + 32 * j, s4);
+            if (s4 < 8 * NK) {
+#pragma unroll
+                for (int j = 0; j < NBEAM / 32; ++j) *reinterpret_cast<u32x4*>(at + (row + 32 * j) * WROW + s4) = w[j];
+            }
+            __syncthreads();
+#pragma unroll
+            for (int kk = 0; kk < NK; ++kk)
+                take(kk, *reinterpret_cast<const u32x4*>(at + (bt * kTile + r) * WROW + 8 * kk + 4 * h));
+            __syncthreads();                               // the weights' LDS becomes the tiles'
+        } else {
+#pragma unroll
+            for (int kk = 0; kk < NK; ++kk) take(kk, load_row(beam, 8 * kk + 4 * h));
+        }
+    }
 
     // One step k, written out in the order it should run: K-step kk's four
     // MFMAs (operands read one K-step ahead from LDS), then 1/NK of the
@@ -447,7 +485,7 @@ LBF_INLINE void item_h_fast(const BlockDesc& d, int item, int nbg, uint32_t* at)
     // incoherent beam of the item's tiles (INC form, first beam group only)
     constexpr int SPW = 8 * NK / NBT;                      // stations per wave of a stream
     constexpr int SPH = (SPW + 1) / 2;                     // of which lane half 0 takes SPH, half 1 the rest
-    float* incl = reinterpret_cast<float*>(at + NS * 2 * kATileWords);
+    float* incl = reinterpret_cast<float*>(at + h_lds_words(NK, NS));
     const bool inc_on = INC && PR != PR_VOLT && bg == 0 && d.b0 == 0;
     auto inc_partial = [&](int k) {                        // the tile of step k: this wave's share
         const uint32_t* tb = at + (sigma * 2 + (k & 1)) * kATileWords;
@@ -590,7 +628,6 @@ LBF_INLINE void item_h_fast(const BlockDesc& d, int item, int nbg, uint32_t* at)
         else stokes_store_cm<PR, TI>(prev, ors, d, c, T2, beam, tile * kTile, h, ok);
     };
 
-    load_chunks(0);
 #pragma unroll
     for (int i = 0; i < CPT; ++i) store_chunk(0, i);
     __syncthreads();
