@@ -17,7 +17,8 @@ __global__ __launch_bounds__(kThreadsH) void bf_f32_fast_kernel(BlockDesc d, int
 // incoherent beam's partial sums in the INC form)
 template <int XT, int CT, int PR, int TI, int NK, int NS, bool INC>
 __global__ __launch_bounds__(kThreadsH) void bf_h_fast_kernel(BlockDesc d, int nbg, int nitems) {
-    __shared__ __attribute__((aligned(16))) uint32_t at[h_lds_words(NK, NS) + (INC ? kIncLdsFloats : 0)];
+    __shared__ __attribute__((aligned(16))) uint32_t at[h_lds_words(NK, NS) + (INC ? kIncLdsFloats : 0) +
+                                                       (PR == PR_VOLT ? 8 * kVoltWords : 0)];
     item_h_fast<XT, CT, PR, TI, NK, NS, INC>(d, xcd_remap(blockIdx.x, nitems), nbg, at);
 }
 
@@ -30,8 +31,8 @@ inline hipError_t launch_f32_k(const BlockDesc& d, int nbg, int n, hipStream_t s
 
 template <int XT, int PR>
 inline hipError_t launch_f32_pr(const BlockDesc& d, int nbg, int n, hipStream_t st) {
-    if (PR == PR_VOLT) return launch_f32_k<XT, PR, 1>(d, nbg, n, st);
-    switch (d.t_int) {
+    if constexpr (PR == PR_VOLT) return launch_f32_k<XT, PR, 1>(d, nbg, n, st);
+    else switch (d.t_int) {
         case 1: return launch_f32_k<XT, PR, 1>(d, nbg, n, st);
         case 2: return launch_f32_k<XT, PR, 2>(d, nbg, n, st);
         case 4: return launch_f32_k<XT, PR, 4>(d, nbg, n, st);
@@ -79,16 +80,16 @@ inline hipError_t launch_h_k(const BlockDesc& d, int nbg, int n, hipStream_t st)
     } else {
         const int ns = fast_h_streams(d);
         if (ns == 1) launch_h_ns<XT, CT, PR, TI, 1>(d, nbg, n, st);
-        else if (ns == 2) launch_h_ns<XT, CT, PR, TI, 2>(d, nbg, n, st);
-        else launch_h_ns<XT, CT, PR, TI, 4>(d, nbg, n, st);
+        else if (ns == 2 || PR == PR_VOLT) launch_h_ns<XT, CT, PR, TI, 2>(d, nbg, n, st);
+        else if constexpr (PR != PR_VOLT) launch_h_ns<XT, CT, PR, TI, 4>(d, nbg, n, st);
     }
     return hipGetLastError();
 }
 
 template <int XT, int CT, int PR>
 inline hipError_t launch_h_pr(const BlockDesc& d, int nbg, int n, hipStream_t st) {
-    if (PR == PR_VOLT) return launch_h_k<XT, CT, PR, 1>(d, nbg, n, st);
-    switch (d.t_int) {
+    if constexpr (PR == PR_VOLT) return launch_h_k<XT, CT, PR, 1>(d, nbg, n, st);
+    else switch (d.t_int) {
         case 1: return launch_h_k<XT, CT, PR, 1>(d, nbg, n, st);
         case 2: return launch_h_k<XT, CT, PR, 2>(d, nbg, n, st);
         case 4: return launch_h_k<XT, CT, PR, 4>(d, nbg, n, st);

@@ -478,8 +478,9 @@ LBF_INLINE void item_h_fast(const BlockDesc& d, int item, int nbg, uint32_t* at)
     const int trow = tile_row_sample(r);
     const int sw = a_swz(trow);
     // two accumulator sets, unless the loaders' registers leave no room
-    // (complex int16 with several streams, more than two chunks per thread)
-    constexpr bool PIPE = !(XT == XT_CI16 && NS >= 2) && CPT <= 2;
+    // (complex int16 with several streams, more than two chunks per thread) or
+    // there is no arithmetic to overlap (voltages)
+    constexpr bool PIPE = !(XT == XT_CI16 && NS >= 2) && CPT <= 2 && PR != PR_VOLT;
     constexpr int NOUT = PR == PR_VOLT ? 1 : 16 / TI;
 
     // incoherent beam of the item's tiles (INC form, first beam group only)
@@ -567,18 +568,7 @@ LBF_INLINE void item_h_fast(const BlockDesc& d, int item, int nbg, uint32_t* at)
             // epilogue slice: samples [16 kk / NK, 16 (kk + 1) / NK) of the previous tile
 #pragma unroll
             for (int smp = 16 * kk / NK; smp < 16 * (kk + 1) / NK; ++smp) {
-                if (PR == PR_VOLT) {
-                    const int t = tprev * kTile + 16 * h + smp;
-                    const uint32_t off = store_off(okprev && t < T, volt_off(beam, T, t));
-                    floatx4 v;
-                    v[0] = prev[0][smp];
-                    v[1] = prev[1][smp];
-                    v[2] = prev[2][smp];
-                    v[3] = prev[3][smp];
-                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), ors, (int)off, 0, 0);
-                } else {
-                    stokes_add<PR>(prev, smp, sm[smp / TI]);
-                }
+                stokes_add<PR>(prev, smp, sm[smp / TI]);
             }
             if (kk >= NK - 2) {                              // stage step k+1's samples
 #pragma unroll
@@ -624,7 +614,9 @@ LBF_INLINE void item_h_fast(const BlockDesc& d, int item, int nbg, uint32_t* at)
     auto final_epilogue = [&](const floatx16 (&prev)[4], int klast) {
         const int tile = tile_lo + sigma + NS * klast;
         const bool ok = klast >= 0 && tile < tile_lo + ntiles && beam < bend;
-        if (PR == PR_VOLT) volt_store_cm(prev, ors, T, beam, tile * kTile, h, ok);
+        if constexpr (PR == PR_VOLT)
+            volt_store_rows(prev, reinterpret_cast<float*>(at + h_lds_words(NK, NS)) + wave * kVoltWords, ors, T, beam - r, bend,
+                            tile * kTile, klast >= 0 && tile < tile_lo + ntiles, 0);
         else stokes_store_cm<PR, TI>(prev, ors, d, c, T2, beam, tile * kTile, h, ok);
     };
 
