@@ -89,9 +89,10 @@ lbf::BlockDesc to_desc(const lbf_block* b) {
     return d;
 }
 
-// Work counters of the persistent batch kernel: a ring of slots per device so
-// that batches queued on different streams do not share a counter (a slot
+// Work counters of the persistent batch kernels: a ring of slots per device so
+// that batches queued on different streams do not share counters (a slot
 // comes round again after kCounterSlots calls; the header states that limit).
+// A slot holds a counter for each launch of a call.
 constexpr int kCounterSlots = 1024;
 std::mutex g_counter_mu;
 int* g_counters[64] = {nullptr};
@@ -104,10 +105,10 @@ int counter_slot(int** out) {
     if (dev < 0 || dev >= 64) return fail(LBF_E_UNSUPPORTED, "lbf_beamform_batch: device %d", dev);
     std::lock_guard<std::mutex> lk(g_counter_mu);
     if (!g_counters[dev]) {
-        e = hipMalloc((void**)&g_counters[dev], sizeof(int) * kCounterSlots);
+        e = hipMalloc((void**)&g_counters[dev], sizeof(int) * kCounterSlots * lbf::kBatchCounters);
         if (e != hipSuccess) return hip_fail(e, "lbf_beamform_batch: counter allocation");
     }
-    *out = g_counters[dev] + (g_counter_next[dev]++ % kCounterSlots);
+    *out = g_counters[dev] + (g_counter_next[dev]++ % kCounterSlots) * lbf::kBatchCounters;
     return LBF_OK;
 }
 

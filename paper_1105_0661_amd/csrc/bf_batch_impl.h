@@ -14,7 +14,8 @@ struct BatchArgs {
 };
 static_assert(sizeof(BatchArgs) <= 4096, "kernel argument block");
 
-// one persistent launch of batch variant v (batch_variant) over the entries of a
+// one persistent launch of batch variant v (batch_variant) over the entries of
+// a; *counter is zero when it starts
 hipError_t launch_batch_f16(int v, const BatchArgs& a, int* counter, hipStream_t st);
 hipError_t launch_batch_bf16(int v, const BatchArgs& a, int* counter, hipStream_t st);
 
@@ -35,11 +36,6 @@ __global__ __launch_bounds__(kThreadsH) void bf_batch_kernel(BatchArgs a, int* c
     }
 }
 
-static __global__ __attribute__((unused)) void fill_int_kernel(int* p, int n, int v) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = v;
-}
-
 // One persistent launch of variant <XT, CT, PR, NK, NS>: one resident work
 // group per slot the hardware offers; the queue, not the grid, spreads the
 // uneven items.
@@ -51,9 +47,6 @@ hipError_t launch_batch_k(const BatchArgs& a, int* counter, hipStream_t st) {
     if (per_cu < 1) per_cu = 1;
     const int total = a.item_start[a.n];
     const int slots = cus * per_cu;
-    hipLaunchKernelGGL(fill_int_kernel, dim3(1), dim3(64), 0, st, counter, 1, 0);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
     hipLaunchKernelGGL((bf_batch_kernel<XT, CT, PR, NK, NS>), dim3(total < slots ? total : slots), dim3(kThreadsH), 0,
                        st, a, counter);
     return hipGetLastError();

@@ -8,6 +8,7 @@
 namespace lbf {
 
 constexpr int kMaxBatch = 32;   // equals LBF_MAX_BATCH in include/lbf.h
+constexpr int kBatchCounters = 64;   // work counters of one batch call: one per kernel variant
 
 // Set the calling thread's lbf_last_error() text; returns code.
 int set_error(int code, const char* fmt, ...);
