@@ -119,7 +119,9 @@ typedef struct {
  * stations with t_int <= 16 (the fast workers) form them channel-major in a
  * staging buffer taken from the device's stream-ordered memory pool, then
  * reorder them into the final order: the same two steps as
- * lbf_beamform_channel_major + lbf_beam_major.  With channel integration
+ * lbf_beamform_channel_major + lbf_beam_major.  Outputs of up to 8 MiB that
+ * share no memory with the samples or weights are stored in the final order
+ * by the contraction itself, with the same bits.  With channel integration
  * (f_int a power of two up to 64) the fast workers stage each channel
  * integrated in time, and the reorder sums each group of f_int channels in
  * channel order.  Other blocks store the final order from the epilogue
@@ -377,7 +379,8 @@ typedef struct {
     double flops;          /* 8 flops per complex multiply-add, both polarisations */
     uint64_t staging_bytes;          /* Stokes staging lbf_beamform takes for the whole block
                                         (the channel-major products before the reorder, one row
-                                        per channel before any channel sums); 0 if none        */
+                                        per channel before any channel sums; an output of up to
+                                        8 MiB needs none there); 0 if none                     */
     uint64_t staging_channel_bytes;  /* the same for one channel (a channel pass needs f_int of
                                         them with channel integration)                        */
 } lbf_block_sizes;

@@ -676,10 +676,15 @@ LBF_INLINE WaveTiles wave_tiles(int wave, int T, int t_int) {
 // K-steps of 8 stations of the fast FP16/BF16 worker: 4 to 8, the fewest that hold the stations (at least 4)
 __host__ __device__ inline int fast_h_ksteps(int S) { return S <= 32 ? 4 : (S + 7) / 8; }
 
-// Sample streams for voltages: at most 2, whose tiles leave LDS for volt_store_rows.
-inline int fast_h_volt_streams(const BlockDesc& d) {
-    if (d.ns_force) return d.ns_force < 2 ? 1 : 2;
-    return d.b1 - d.b0 > 128 ? 1 : 2;
+// Voltages of more beams than this take at most 2 sample streams, whose tiles
+// leave LDS for volt_store_rows; fewer take 4 where Stokes would, and store
+// straight from the lanes: there the loads bound the block, and a store
+// touches only the lanes' beams.  2 streams against 4, ci8, 52 stations, 932
+// channels x 1356 samples: 2 beams 214 / 141 us, 8 217 / 167, 16 219 / 203, 32
+// 256 / 310; 64 stations, 512 x 3072: 8 beams 243 / 257, 16 250 / 294; ci16,
+// 40 stations: 8 beams 197 / 191, 16 209 / 238.
+inline int volt_straight_beams(const BlockDesc& d) {
+    return d.xtype == XT_CI8 && fast_h_ksteps(d.S) < 8 ? 16 : 8;
 }
 
 // Sample streams of the fast FP16/BF16 worker, the tile shape of its work
@@ -694,12 +699,12 @@ inline int fast_h_volt_streams(const BlockDesc& d) {
 // BlockDesc once (ns_force), so every part of one call sees the same value.
 inline int fast_h_streams(const BlockDesc& d) {
     if (d.xtype == XT_CF32) return 1;
-    if (d.product == PR_VOLT) return fast_h_volt_streams(d);
     if (d.ns_force) return d.ns_force;
     const int nb = d.b1 - d.b0;
     int bucket = 0;
     while (bucket < 4 && nb > kTileBeamMax[bucket]) ++bucket;
-    return kTileStreams[d.xtype == XT_CI8 ? 0 : 1][d.product == PR_I ? 0 : 1][fast_h_ksteps(d.S) - 4][bucket];
+    const int ns = kTileStreams[d.xtype == XT_CI8 ? 0 : 1][d.product == PR_I ? 0 : 1][fast_h_ksteps(d.S) - 4][bucket];
+    return d.product == PR_VOLT && ns > 2 && nb > volt_straight_beams(d) ? 2 : ns;
 }
 
 // A block whose beams beyond the last whole 256-beam group number at most 128

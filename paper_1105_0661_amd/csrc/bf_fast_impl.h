@@ -18,7 +18,7 @@ __global__ __launch_bounds__(kThreadsH) void bf_f32_fast_kernel(BlockDesc d, int
 template <int XT, int CT, int PR, int TI, int NK, int NS, bool INC>
 __global__ __launch_bounds__(kThreadsH) void bf_h_fast_kernel(BlockDesc d, int nbg, int nitems) {
     __shared__ __attribute__((aligned(16))) uint32_t at[h_lds_words(NK, NS) + (INC ? kIncLdsFloats : 0) +
-                                                       (PR == PR_VOLT ? 8 * kVoltWords : 0)];
+                                                       (PR == PR_VOLT && NS <= 2 ? 8 * kVoltWords : 0)];
     item_h_fast<XT, CT, PR, TI, NK, NS, INC>(d, xcd_remap(blockIdx.x, nitems), nbg, at);
 }
 
@@ -80,8 +80,8 @@ inline hipError_t launch_h_k(const BlockDesc& d, int nbg, int n, hipStream_t st)
     } else {
         const int ns = fast_h_streams(d);
         if (ns == 1) launch_h_ns<XT, CT, PR, TI, 1>(d, nbg, n, st);
-        else if (ns == 2 || PR == PR_VOLT) launch_h_ns<XT, CT, PR, TI, 2>(d, nbg, n, st);
-        else if constexpr (PR != PR_VOLT) launch_h_ns<XT, CT, PR, TI, 4>(d, nbg, n, st);
+        else if (ns == 2) launch_h_ns<XT, CT, PR, TI, 2>(d, nbg, n, st);
+        else launch_h_ns<XT, CT, PR, TI, 4>(d, nbg, n, st);
     }
     return hipGetLastError();
 }

@@ -196,10 +196,20 @@ hipError_t noalloc_scratch(void** p) {
     return hipSuccess;
 }
 
+// With staging the output is written after all samples and weights are read,
+// so it may share their memory; a direct store may not.
+static bool out_overlaps_inputs(const BlockDesc& d) {
+    const size_t out = (size_t)d.B * (d.product == PR_IQUV ? 4 : 1) * (d.T / d.t_int) * d.C * sizeof(float);
+    const size_t x = (size_t)d.S * d.C * d.T * sample_bytes(d.xtype);
+    const size_t w = (size_t)d.C * d.B * d.S * (d.ctype == CT_F32 ? 8 : 4);
+    const uintptr_t o0 = (uintptr_t)d.out, x0 = (uintptr_t)d.x, w0 = (uintptr_t)d.w;
+    return (o0 < x0 + x && x0 < o0 + out) || (o0 < w0 + w && w0 < o0 + out);
+}
+
 // lbf_beamform: the fast workers where they apply, the generic ones
 // otherwise; the staging of a whole block comes from the stream-ordered pool.
 hipError_t launch_beamform(const BlockDesc& d, hipStream_t st) {
-    if (!needs_staging(d) || direct_store(d)) return launch_beamform_direct(d, st);
+    if (!needs_staging(d) || (direct_store(d) && !out_overlaps_inputs(d))) return launch_beamform_direct(d, st);
     const size_t bytes = (size_t)d.C * staging_channel_bytes(d);
     void* stage = nullptr;
     hipError_t e = staging_alloc(&stage, bytes, st);

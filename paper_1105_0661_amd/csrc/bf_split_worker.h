@@ -61,9 +61,9 @@ __host__ __device__ inline bool split_takes(const BlockDesc& d) { return d.xtype
 // Sample streams: 4 (items of 64 beams) for at most 64 beams, where an item of
 // 128 would leave half its waves idle, else 2; complex int16 from 6 K-steps up
 // and complex float always 2 (the loaders of 4 streams beside the weight
-// pieces would spill), and voltages (volt_store_rows's LDS).
+// pieces would spill); voltages by volt_straight_beams.
 inline int split_streams(const BlockDesc& d) {
-    if (d.b1 - d.b0 > 64 || d.xtype == XT_CF32 || d.product == PR_VOLT) return 2;
+    if (d.b1 - d.b0 > (d.product == PR_VOLT ? volt_straight_beams(d) : 64) || d.xtype == XT_CF32) return 2;
     return d.xtype == XT_CI16 && split_ksteps(d.S) >= 6 ? 2 : 4;
 }
 
@@ -138,8 +138,8 @@ LBF_INLINE void split_epilogue(const floatx16 (&acc)[4], __amdgpu_buffer_rsrc_t 
     }
 }
 
-// vbuf: kVoltWords floats per wave for the voltages of integer samples (the
-// two planes of complex float samples leave no room)
+// vbuf: kVoltWords floats per wave for the voltages of integer samples in two
+// streams (two planes of complex float samples or four streams leave no room)
 template <int XT, int PR, int NK, int NS>
 LBF_INLINE void item_f32_split(const BlockDesc& d, int item, int nbg, uint32_t* at, int* flags, float* vbuf) {
     typedef MfmaH<CT_F16> M;
@@ -378,7 +378,7 @@ LBF_INLINE void item_f32_split(const BlockDesc& d, int item, int nbg, uint32_t* 
         const bool ok = k >= 0 && tile < tile_lo + ntiles && beam_ok && !redo(k);
         int bm = beam, hh = h;
         __asm__ volatile("" : "+v"(bm), "+v"(hh));          // offsets formed anew for each tile
-        if constexpr (PR == PR_VOLT && !XF) {
+        if constexpr (PR == PR_VOLT && !XF && NS <= 2) {
             // the scale is the beam's: taken out before the lanes exchange
             volt_store_rows(acc, vbuf + wave * kVoltWords, ors, T, beam - r, d.b1, tile * kTile, k >= 0 && tile < tile_lo + ntiles,
                             esc);
@@ -532,7 +532,7 @@ template <int XT, int PR, int NK, int NS>
 __global__ __launch_bounds__(kThreadsH) void bf_f32_split_kernel(BlockDesc d, int nbg, int nitems) {
     __shared__ __attribute__((aligned(16))) uint32_t at[NS * 2 * kATileWords * (XT == XT_CF32 ? 2 : 1)];
     __shared__ __attribute__((aligned(16))) int flags[(XT == XT_CF32 ? 20 : 2) * NS];
-    constexpr bool rows = PR == PR_VOLT && XT != XT_CF32;
+    constexpr bool rows = PR == PR_VOLT && XT != XT_CF32 && NS <= 2;
     __shared__ __attribute__((aligned(16))) float vbuf[rows ? 8 * kVoltWords : 1];
     item_f32_split<XT, PR, NK, NS>(d, xcd_remap(blockIdx.x, nitems), nbg, at, flags, vbuf);
 }
@@ -540,7 +540,7 @@ __global__ __launch_bounds__(kThreadsH) void bf_f32_split_kernel(BlockDesc d, in
 template <int XT, int PR, int NK>
 inline void launch_split_nk(const BlockDesc& d, int ns, int nbg, int n, hipStream_t st) {
     const dim3 g(n), b(kThreadsH);
-    if constexpr (PR != PR_VOLT && (XT == XT_CI8 || (XT == XT_CI16 && NK < 6))) {
+    if constexpr (XT == XT_CI8 || (XT == XT_CI16 && NK < 6)) {
         if (ns == 4) {
             hipLaunchKernelGGL((bf_f32_split_kernel<XT, PR, NK, 4>), g, b, 0, st, d, nbg, n);
             return;

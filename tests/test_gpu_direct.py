@@ -37,3 +37,15 @@ def test_direct_equals_staged(S, C, T, B, t_int, product, xt, ct):
     if ct != "f32":
         both, inc = lbf.beamform_incoherent(x, w, product, t_int, 1)
         assert torch.equal(both, out)
+
+
+def test_output_in_the_samples_memory():
+    # an output that overlaps its block's samples is written after they are read
+    S, C, T, B = 20, 8, 256, 33
+    g = torch.Generator(device="cuda").manual_seed(5)
+    x = torch.randn((S, C, T, 2, 2), generator=g, device="cuda").mul_(30.0).round_().to(torch.int16)
+    w = torch.randn((C, B, S, 2), generator=g, device="cuda").half()
+    ref = lbf.beamform_noalloc(x, w, lbf.STOKES_IQUV, 16)
+    out = x.view(-1).view(torch.float32)[:ref.numel()].view(ref.shape)
+    lbf.beamform(x, w, lbf.STOKES_IQUV, 16, out=out)
+    assert torch.equal(out, ref)

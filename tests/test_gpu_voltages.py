@@ -22,7 +22,7 @@ def streams():
 
 
 @pytest.mark.parametrize("ns", [0, 1, 2, 4])
-@pytest.mark.parametrize("S,T,B", [(1, 1, 1), (8, 7, 33), (33, 100, 129), (64, 41, 300), (20, 800, 65)])
+@pytest.mark.parametrize("S,T,B", [(1, 1, 1), (8, 7, 33), (40, 70, 8), (52, 70, 16), (64, 70, 9), (33, 100, 129), (64, 41, 300), (20, 800, 65)])
 @pytest.mark.parametrize("xt", [torch.int8, torch.int16], ids=["ci8", "ci16"])
 @pytest.mark.parametrize("wt", [torch.float16, torch.bfloat16], ids=["f16", "bf16"])
 def test_stores(S, T, B, xt, wt, ns, streams):
