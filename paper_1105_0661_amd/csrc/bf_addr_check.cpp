@@ -136,7 +136,6 @@ void walk_h(Walk& w, const BlockDesc& d, int lo, int hi) {
             for (int k = 0; k < nsteps + 2; ++k)
                 for (int i = 0; i < CPT; ++i) {
                     const int sg = chunk_stream(tid, i, SP, CPS), s = chunk_station(tid, i, SP, CPS), s0 = s & ~7;
-                    if (sg >= NS) continue;                    // past the step's chunks: an out-of-range offset
                     const int t = stream_tile(sg, k, NS, ip.tile_lo, ip.ntiles) * kTile, q = chunk_q(tid, CPS);
                     const uint32_t off = tile_off(ip.c, d.T, t, bytes);
                     if (off != ((uint64_t)ip.c * d.T + t) * bytes) return w.fail("the tile's offset wraps");
@@ -186,7 +185,6 @@ void walk_split(Walk& w, const BlockDesc& d, int lo, int hi) {
             for (int k = 0; k < nsteps + 2; ++k)
                 for (int i = 0; i < CPT; ++i) {
                     const int sg = chunk_stream(tid, i, SP, CPS), s = chunk_station(tid, i, SP, CPS), s0 = s & ~7;
-                    if (sg >= NS) continue;                    // past the step's chunks: an out-of-range offset
                     const int t = stream_tile(sg, k, NS, ip.tile_lo, ip.ntiles) * kTile, q = chunk_q(tid, CPS);
                     const uint32_t off = tile_off(ip.c, d.T, t, bytes);
                     if (off != ((uint64_t)ip.c * d.T + t) * bytes) return w.fail("the tile's offset wraps");
