@@ -204,7 +204,7 @@ void walk_split(Walk& w, const BlockDesc& d, int lo, int hi) {
     }
 }
 
-// items [lo, hi) of the FP32 worker (complex float samples of few stations)
+// items [lo, hi) of the FP32 worker (complex float samples)
 void walk_f32(Walk& w, const BlockDesc& d, int lo, int hi) {
     const int bytes = sample_bytes(d.xtype);
     const uint64_t xbuf = (uint64_t)d.S * d.C * d.T * bytes, wbuf = (uint64_t)d.C * d.B * d.S * 8;
@@ -260,8 +260,8 @@ bool check_fast_addressing(const BlockDesc& d, int threads, uint64_t* accesses, 
     if (d.ctype != CT_F32) np = split_fast_h(d, part);
     for (int p = 0; p < np; ++p) {
         int nbg;
-        items[p] = d.ctype != CT_F32        ? block_items_fast_h(part[p], &nbg)
-                   : split_takes(d)     ? block_items_split(part[p], &nbg)
+        items[p] = d.ctype != CT_F32    ? block_items_fast_h(part[p], &nbg)
+                   : d.xtype != XT_CF32 ? block_items_split(part[p], &nbg)
                                         : block_items_fast_f32(part[p], &nbg);
     }
     threads = std::max(1, std::min(threads, 64));
@@ -273,7 +273,7 @@ bool check_fast_addressing(const BlockDesc& d, int threads, uint64_t* accesses, 
             Walk* wk = &w[p * threads + i];
             const BlockDesc* dp = &part[p];
             th.emplace_back([=] {
-                if (dp->ctype == CT_F32 && !split_takes(*dp)) walk_f32(*wk, *dp, lo, hi);
+                if (dp->ctype == CT_F32 && dp->xtype == XT_CF32) walk_f32(*wk, *dp, lo, hi);
                 else if (dp->ctype == CT_F32) walk_split(*wk, *dp, lo, hi);
                 else walk_h(*wk, *dp, lo, hi);
             });

@@ -1,6 +1,6 @@
 // bf_fast_f32.hip -- fast contraction kernels with FP32 operands: the split
-// worker (FP16 matrix instructions, FP32 results), and FP32 matrix
-// instructions for complex float samples of few stations.
+// worker (FP16 matrix instructions, FP32 results) for integer samples, FP32
+// matrix instructions for complex float ones.
 #include "bf_fast_impl.h"
 #include "bf_split_worker.h"
 
@@ -8,7 +8,6 @@ namespace lbf {
 hipError_t launch_fast_f32(const BlockDesc& d, hipStream_t st) {
     if (d.xtype == XT_CI8) return launch_split_ci8(d, st);
     if (d.xtype == XT_CI16) return launch_split_ci16(d, st);
-    if (split_takes(d)) return launch_split_cf32(d, st);
     int nbg;
     const int n = block_items_fast_f32(d, &nbg);
     return launch_f32_xt<XT_CF32>(d, nbg, n, st);

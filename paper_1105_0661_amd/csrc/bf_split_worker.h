@@ -1,5 +1,5 @@
-// bf_split_worker.h -- the FP32 contraction worker: FP32 results from FP16
-// matrix instructions.
+// bf_split_worker.h -- the FP32 contraction worker of integer samples: FP32
+// results from FP16 matrix instructions.
 //
 // The FP32 matrix instruction runs at 1/16 of the FP16 rate.  The operands
 // of this contraction split without loss into FP16 pieces, and FP16 products
@@ -19,17 +19,9 @@
 // 2.9e-8 at 4 stations, 1.02e-7 -> 4.7e-8 at 16, 1.06e-7 -> 6.2e-8 at 17,
 // 2.03e-7 -> 9.6e-8 at 64; no station count from 1 to 64 is further off.
 //
-// Complex float samples (20 stations and more) take two pieces too, x 2^s =
-// x1 + x2, and three products, x1 w1 + x1 w2 + x2 w1 (x2 w2 is below 2^-24 of
-// the first).  s is one exponent per 32-sample tile of a channel, from the
-// largest component of the stream's previous tile (the item's first tile: its
-// own), which it puts into [2^13, 2^14).  A tile takes the exact path when a
-// component of it would leave the FP16 range, is not finite, or when a sample
-// other than zero has both components of a polarisation below 1/2, where its
-// pieces would lose bits: one tile in 10^4 of Gaussian noise.
-// Relative rms error of the voltages (FP32 matrix instructions -> this
-// worker): 1.14e-7 -> 9.3e-8 at 20 stations, 1.45e-7 -> 1.07e-7 at 32, 2.04e-7
-// -> 1.38e-7 at 64.
+// Complex float samples stay on the FP32 instructions: as many bits in both
+// operands take six products of three pieces each at the least, and a third
+// plane of samples that LDS has no room for.
 //
 // What P pieces cannot hold takes the exact path, FP32 matrix instructions
 // over the same samples (one station each, in station order): a wave one of
@@ -53,17 +45,12 @@ namespace lbf {
 __host__ __device__ constexpr int split_ksteps(int S) { return S <= 16 ? 2 : S <= 32 ? 4 : (S + 7) / 8; }
 __host__ __device__ constexpr int split_pieces(int NK) { return NK == 2 ? 3 : 2; }
 
-// Complex float blocks the split worker takes: with fewer stations the FP32
-// chain's own roundings come down to what two pieces of both operands leave
-// out (1.06e-7 against 9.6e-8 at 17 stations, 1.03e-7 at 16)
-__host__ __device__ inline bool split_takes(const BlockDesc& d) { return d.xtype != XT_CF32 || d.S >= 20; }
-
 // Sample streams: 4 (items of 64 beams) for at most 64 beams, where an item of
 // 128 would leave half its waves idle, else 2; complex int16 from 6 K-steps up
-// and complex float always 2 (the loaders of 4 streams beside the weight
-// pieces would spill); voltages by volt_straight_beams.
+// always 2 (the loaders of 4 streams beside the weight pieces would spill);
+// voltages by volt_straight_beams.
 inline int split_streams(const BlockDesc& d) {
-    if (d.b1 - d.b0 > (d.product == PR_VOLT ? volt_straight_beams(d) : 64) || d.xtype == XT_CF32) return 2;
+    if (d.b1 - d.b0 > (d.product == PR_VOLT ? volt_straight_beams(d) : 64)) return 2;
     return d.xtype == XT_CI16 && split_ksteps(d.S) >= 6 ? 2 : 4;
 }
 
@@ -138,8 +125,8 @@ LBF_INLINE void split_epilogue(const floatx16 (&acc)[4], __amdgpu_buffer_rsrc_t 
     }
 }
 
-// vbuf: kVoltWords floats per wave for the voltages of integer samples in two
-// streams (two planes of complex float samples or four streams leave no room)
+// vbuf: kVoltWords floats per wave for voltages in two streams (four leave no
+// room)
 template <int XT, int PR, int NK, int NS>
 LBF_INLINE void item_f32_split(const BlockDesc& d, int item, int nbg, uint32_t* at, int* flags, float* vbuf) {
     typedef MfmaH<CT_F16> M;
@@ -148,9 +135,7 @@ LBF_INLINE void item_f32_split(const BlockDesc& d, int item, int nbg, uint32_t* 
     constexpr int P = split_pieces(NK);
     constexpr int BYTES = sample_bytes(XT);
     constexpr int NBT = 8 / NS;                            // beam tiles per item
-    constexpr bool XF = XT == XT_CF32;                     // two sample pieces
-    constexpr int PL = XF ? 2 : 1;
-    typedef TileLoader<XT, CT_F16, NK, NS, PL> Loader;
+    typedef TileLoader<XT, CT_F16, NK, NS> Loader;
     constexpr int CPT = Loader::CPT;                       // chunks per thread per step
     const int T = d.T, S = d.S;
     const ItemPos ip = item_pos(d, item, nbg);
@@ -167,75 +152,12 @@ LBF_INLINE void item_f32_split(const BlockDesc& d, int item, int nbg, uint32_t* 
         PR == PR_VOLT ? channel_rsrc(d, c, out_channel_bytes(d, PR, T2)) : stokes_rsrc(d, c, PR, T2);
     const __amdgpu_buffer_rsrc_t wrs = weight_rsrc(d, c, 8);
 
-    // Integer samples: one step ahead.  Complex float samples, one per
-    // 16-byte chunk, half a step ahead, one stream's tile after the other in
-    // the same registers.
-    constexpr int HC = XF ? CPT / NS : CPT;
     Loader ld;
     ld.init(d, ip);
-    u32x4 raw[HC];
-    int* tscale = flags + 2 * NS;                          // [parity][stream]: s of the tile staged there
-    uint32_t* wmax = reinterpret_cast<uint32_t*>(flags + 4 * NS);     // [parity][stream][wave]: largest component
-    auto load_chunks = [&](int k) {
-        if constexpr (!XF) ld.load(k, raw);
-    };
-    auto load_half = [&](int k, auto sg) { ld.template load_part<sg * HC, HC>(k, raw); };
-    auto wave_max = [&](uint32_t m) {                      // over the lanes of the wave, uniform
-#define LBF_DPP_MAX(ctrl, rows) m = max(m, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)m, ctrl, rows, 0xf, false))
-        LBF_DPP_MAX(0x111, 0xf);                           // row_shr:1, 2, 4, 8: lane 15 of each row
-        LBF_DPP_MAX(0x112, 0xf);
-        LBF_DPP_MAX(0x114, 0xf);
-        LBF_DPP_MAX(0x118, 0xf);
-        LBF_DPP_MAX(0x142, 0xa);                           // row_bcast:15 into rows 1 and 3
-        LBF_DPP_MAX(0x143, 0xc);                           // row_bcast:31 into rows 2 and 3
-#undef LBF_DPP_MAX
-        return (uint32_t)__builtin_amdgcn_readlane((int)m, 63);
-    };
-    // the two components of a polarisation: the larger magnitude, as an integer
-    auto pol_mag = [&](uint32_t a, uint32_t b) { return max(a & 0x7fffffffu, b & 0x7fffffffu); };
-    // the largest component of the stream's tile in raw, for the item's first tile
-    auto first_max = [&](int sg) {
-        uint32_t mx = 0u;
-#pragma unroll
-        for (int i = 0; i < HC; ++i) mx = max(mx, max(pol_mag(raw[i][0], raw[i][1]), pol_mag(raw[i][2], raw[i][3])));
-        mx = wave_max(mx);
-        if (lane == 0) wmax[sg * 8 + wave] = mx;
-    };
-    // complex float: stream sg's tile of step k from raw into both planes
-    auto stage_half = [&](int k, int sg) {
-        const u32x4* pm = reinterpret_cast<const u32x4*>(wmax + ((k == 0 ? 0 : (k - 1) & 1) * NS + sg) * 8);
-        const u32x4 m0 = pm[0], m1 = pm[1];
-        const uint32_t big = (uint32_t)__builtin_amdgcn_readfirstlane(
-            (int)max(max(max(m0[0], m0[1]), max(m0[2], m0[3])), max(max(m1[0], m1[1]), max(m1[2], m1[3]))));
-        int sx = big ? 14 - ((int)(big >> 23) - 126) : 0;  // the largest component to [2^13, 2^14)
-        sx = sx > 100 ? 100 : sx < -100 ? -100 : sx;
-        const float f = __uint_as_float((uint32_t)(127 + sx) << 23);
-        const uint32_t hi = ((uint32_t)(142 - sx) << 23) | 0x600000u, lo = (uint32_t)(126 - sx) << 23;   // 1.75 2^15, 2^-1
-        uint32_t mx = 0u, mn = 0xffffffffu;                // mn: the smallest non-zero magnitude minus one
-#pragma unroll
-        for (int i = 0; i < HC; ++i) {
-            if (!ld.staged(sg * HC + i)) continue;
-            const uint32_t mxx = pol_mag(raw[i][0], raw[i][1]), myy = pol_mag(raw[i][2], raw[i][3]);
-            mx = max(mx, max(mxx, myy));
-            mn = min(mn, min(mxx - 1u, myy - 1u));
-            const floatx4 v = __builtin_bit_cast(floatx4, raw[i]) * f;
-            uint32_t* ab = at + ld.word(k, sg * HC + i);
-#pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                const halfx2 p1 = {(_Float16)v[2 * q], (_Float16)v[2 * q + 1]};
-                ab[q * kARow] = __builtin_bit_cast(uint32_t, p1);
-                ab[q * kARow + kATileWords] = pack_h((_Float16)(v[2 * q] - (float)p1[0]), (_Float16)(v[2 * q + 1] - (float)p1[1]));
-            }
-        }
-        if (__builtin_amdgcn_ballot_w64(mx > hi || mn < lo - 1u) != 0 && lane == 0) flags[(k & 1) * NS + sg] = k;
-        mx = wave_max(mx);
-        if (lane == 0) wmax[((k & 1) * NS + sg) * 8 + wave] = mx;
-        if (tid == 0) tscale[(k & 1) * NS + sg] = sx;
-    };
-    typedef std::integral_constant<int, 0> Half0;
-    typedef std::integral_constant<int, NS - 1> Half1;
+    u32x4 raw[CPT];
+    auto load_chunks = [&](int k) { ld.load(k, raw); };
     auto store_chunk = [&](int k, int i) {
-        if constexpr (!XF) ld.store(at, k, i, raw);
+        ld.store(at, k, i, raw);
         if constexpr (XT == XT_CI16) {
             // any component outside [-2048, 2047]: x + 2048 has one of its top four bits set
             typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
@@ -253,15 +175,14 @@ LBF_INLINE void item_f32_split(const BlockDesc& d, int item, int nbg, uint32_t* 
 #pragma unroll
         for (int i = 0; i < CPT; ++i) store_chunk(k, i);
     };
-    if constexpr (XF) load_half(0, Half0{});
-    else load_chunks(0);
+    load_chunks(0);
 
     // The item's weights, through LDS: a lane's own are 32-byte pieces of rows
     // a whole beam apart, a cache line per lane and load.  Whole rows instead:
     // 8192 channels of ci16, 64 stations, 128 beams 2100 -> 1930 us.
     // Stations >= S and beams >= B as zeros.
     constexpr int NBEAM = NBT * kTile, WROW = 16 * NK + 4;  // words per row: 4 mod 64 banks
-    static_assert(NBEAM * WROW <= NS * 2 * PL * kATileWords, "the weights fit the tiles' LDS");
+    static_assert(NBEAM * WROW <= NS * 2 * kATileWords, "the weights fit the tiles' LDS");
     float* wl = reinterpret_cast<float*>(at);
     {
         float2v w[NBEAM / 8];
@@ -337,24 +258,11 @@ LBF_INLINE void item_f32_split(const BlockDesc& d, int item, int nbg, uint32_t* 
     const int trow = tile_row_sample(r);
     const int sw = a_swz(trow);
 
-    if (XT != XT_CI8) {
+    if constexpr (XT == XT_CI16) {
         if (tid < 2 * NS) flags[tid] = -1;
-        if constexpr (XF) {                                // the first tiles' own scale: read twice, the second from cache
-            first_max(0);
-            load_half(0, Half1{});
-            first_max(1);
-            load_half(0, Half0{});
-        }
         __syncthreads();
     }
-    if constexpr (XF) {
-        stage_half(0, 0);
-        load_half(0, Half1{});
-        stage_half(0, 1);
-        load_half(1, Half0{});
-    } else {
-        store_chunks(0);
-    }
+    store_chunks(0);
     __syncthreads();
 
     floatx16 acc[4];
@@ -368,17 +276,12 @@ LBF_INLINE void item_f32_split(const BlockDesc& d, int item, int nbg, uint32_t* 
         acc[2] = M::mfma(b, br, acc[2]);
         acc[3] = M::mfma(b, bi, acc[3]);
     };
-    // complex float: the steps (at most 96) whose tile takes the exact path,
-    // after the others
-    uint64_t redo0 = 0ull, redo1 = 0ull;
-    static_assert(kSegTilesMax / NS <= 128, "a bit per step");
-    auto redo = [&](int k) { return XF && ((k < 64 ? redo0 >> (k & 63) : redo1 >> (k & 63)) & 1ull) != 0; };
     auto epilogue = [&](int k) {
         const int tile = tile_lo + sigma + NS * k;
-        const bool ok = k >= 0 && tile < tile_lo + ntiles && beam_ok && !redo(k);
+        const bool ok = k >= 0 && tile < tile_lo + ntiles && beam_ok;
         int bm = beam, hh = h;
         __asm__ volatile("" : "+v"(bm), "+v"(hh));          // offsets formed anew for each tile
-        if constexpr (PR == PR_VOLT && !XF && NS <= 2) {
+        if constexpr (PR == PR_VOLT && NS <= 2) {
             // the scale is the beam's: taken out before the lanes exchange
             volt_store_rows(acc, vbuf + wave * kVoltWords, ors, T, beam - r, d.b1, tile * kTile, k >= 0 && tile < tile_lo + ntiles,
                             esc);
@@ -413,70 +316,35 @@ LBF_INLINE void item_f32_split(const BlockDesc& d, int item, int nbg, uint32_t* 
         load_chunks(k + 1);
         if (!idle) {
             if (late && k > 0) epilogue(k - 1);
-            int rowx = (sigma * 2 + (k & 1)) * PL * kATileWords + 2 * trow * kARow, swx = 4 * (h ^ sw);
+            int rowx = (sigma * 2 + (k & 1)) * kATileWords + 2 * trow * kARow, swx = 4 * (h ^ sw);
             __asm__ volatile("" : "+v"(rowx), "+v"(swx));
             const uint32_t* ax0 = at + rowx;
             __builtin_amdgcn_sched_barrier(0);
-            if constexpr (XF) {
-                // x2 w1, then x1 w2 and x1 w1 (the small products first); each
-                // plane's operands are read under the other's MFMAs
-                u32x4 bx, by, ax, ay;                       // planes 2 and 1
-                bx = *reinterpret_cast<const u32x4*>(ax0 + kATileWords + swx);
-                by = *reinterpret_cast<const u32x4*>(ax0 + kATileWords + kARow + swx);
+            // operands one K-step ahead from LDS; the next step's samples
+            // staged under the second half of the MFMAs
+            u32x4 ax[2], ay[2];
+            ax[0] = *reinterpret_cast<const u32x4*>(ax0 + swx);
+            ay[0] = *reinterpret_cast<const u32x4*>(ax0 + kARow + swx);
 #pragma unroll
-                for (int kk = 0; kk < NK; ++kk) {
-                    const int off = swx ^ (8 * kk), offn = swx ^ (8 * (kk + 1));
-                    ax = *reinterpret_cast<const u32x4*>(ax0 + off);
-                    ay = *reinterpret_cast<const u32x4*>(ax0 + kARow + off);
-                    if (kk == 0) {
+            for (int kk = 0; kk < NK; ++kk) {
+                if (kk + 1 < NK) {
+                    const int off = swx ^ (8 * (kk + 1));       // 4 ((2 kk + 2 + h) ^ sw)
+                    ax[(kk + 1) & 1] = *reinterpret_cast<const u32x4*>(ax0 + off);
+                    ay[(kk + 1) & 1] = *reinterpret_cast<const u32x4*>(ax0 + kARow + off);
+                }
+                const V a = __builtin_bit_cast(V, ax[kk & 1]), b = __builtin_bit_cast(V, ay[kk & 1]);
+#pragma unroll
+                for (int p = P - 1; p >= 0; --p) {            // the small pieces first
+                    if (kk == 0 && p == P - 1) {
 #pragma unroll
                         for (int q = 0; q < 4; ++q) acc[q] = zero16();
                     }
-                    mfma4(__builtin_bit_cast(V, bx), __builtin_bit_cast(V, by), wr[0][kk], wi[0][kk]);
-                    if (kk + 1 < NK) {
-                        bx = *reinterpret_cast<const u32x4*>(ax0 + kATileWords + offn);
-                        by = *reinterpret_cast<const u32x4*>(ax0 + kATileWords + kARow + offn);
-                    }
-#pragma unroll
-                    for (int p = P - 1; p >= 0; --p) mfma4(__builtin_bit_cast(V, ax), __builtin_bit_cast(V, ay), wr[p][kk], wi[p][kk]);
-                    if (kk == NK / 2) {
-                        stage_half(k + 1, 0);
-                        load_half(k + 1, Half1{});
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
+                    mfma4(a, b, wr[p][kk], wi[p][kk]);
                 }
-                esc = sc + __builtin_amdgcn_readfirstlane(tscale[(k & 1) * NS + sigma]);
-                if (__builtin_amdgcn_readfirstlane(flags[(k & 1) * NS + sigma]) == k) {
-                    if (k < 64) redo0 |= 1ull << k;
-                    else redo1 |= 1ull << (k - 64);
-                }
-            } else {
-                // operands one K-step ahead from LDS; the next step's samples
-                // staged under the second half of the MFMAs
-                u32x4 ax[2], ay[2];
-                ax[0] = *reinterpret_cast<const u32x4*>(ax0 + swx);
-                ay[0] = *reinterpret_cast<const u32x4*>(ax0 + kARow + swx);
 #pragma unroll
-                for (int kk = 0; kk < NK; ++kk) {
-                    if (kk + 1 < NK) {
-                        const int off = swx ^ (8 * (kk + 1));       // 4 ((2 kk + 2 + h) ^ sw)
-                        ax[(kk + 1) & 1] = *reinterpret_cast<const u32x4*>(ax0 + off);
-                        ay[(kk + 1) & 1] = *reinterpret_cast<const u32x4*>(ax0 + kARow + off);
-                    }
-                    const V a = __builtin_bit_cast(V, ax[kk & 1]), b = __builtin_bit_cast(V, ay[kk & 1]);
-#pragma unroll
-                    for (int p = P - 1; p >= 0; --p) {            // the small pieces first
-                        if (kk == 0 && p == P - 1) {
-#pragma unroll
-                            for (int q = 0; q < 4; ++q) acc[q] = zero16();
-                        }
-                        mfma4(a, b, wr[p][kk], wi[p][kk]);
-                    }
-#pragma unroll
-                    for (int i = 0; i < CPT; ++i)
-                        if (kk == NK / 2 + i * (NK - NK / 2) / CPT) store_chunk(k + 1, i);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
+                for (int i = 0; i < CPT; ++i)
+                    if (kk == NK / 2 + i * (NK - NK / 2) / CPT) store_chunk(k + 1, i);
+                __builtin_amdgcn_sched_barrier(0);
             }
             if (XT == XT_CI16 && __builtin_amdgcn_readfirstlane(flags[(k & 1) * NS + sigma]) == k) {
                 // residuals of this tile's samples, straight from HBM (rows past T: its last sample)
@@ -501,38 +369,27 @@ LBF_INLINE void item_f32_split(const BlockDesc& d, int item, int nbg, uint32_t* 
             }
             __builtin_amdgcn_sched_barrier(0);
             if (!late) epilogue(k);
-        } else if constexpr (XF) {
-            stage_half(k + 1, 0);
-            load_half(k + 1, Half1{});
         } else {
             store_chunks(k + 1);
-        }
-        if constexpr (XF) {
-            stage_half(k + 1, 1);
-            load_half(k + 2, Half0{});
         }
         __syncthreads();
     }
     if (!idle && late) epilogue(nsteps - 1);
-    if (!exact && redo0 == 0ull && redo1 == 0ull) return;
-    const uint64_t again0 = exact ? ~0ull : redo0, again1 = exact ? ~0ull : redo1;
-    redo0 = redo1 = 0ull;
+    if (!exact) return;
     for (int k = 0; k < nsteps; ++k) {                     // the exact path
         const int tile = tile_lo + sigma + NS * k;
         if (tile >= tile_lo + ntiles) break;
-        if (((k < 64 ? again0 >> (k & 63) : again1 >> (k & 63)) & 1ull) == 0) continue;
         exact_tile(tile);
         epilogue(k);
     }
 }
 
-// 8 waves, two per SIMD; LDS: NS streams x 2 buffers of one A tile (two
-// planes of it for complex float samples, and their scales)
+// 8 waves, two per SIMD; LDS: NS streams x 2 buffers of one A tile
 template <int XT, int PR, int NK, int NS>
 __global__ __launch_bounds__(kThreadsH) void bf_f32_split_kernel(BlockDesc d, int nbg, int nitems) {
-    __shared__ __attribute__((aligned(16))) uint32_t at[NS * 2 * kATileWords * (XT == XT_CF32 ? 2 : 1)];
-    __shared__ __attribute__((aligned(16))) int flags[(XT == XT_CF32 ? 20 : 2) * NS];
-    constexpr bool rows = PR == PR_VOLT && XT != XT_CF32 && NS <= 2;
+    __shared__ __attribute__((aligned(16))) uint32_t at[NS * 2 * kATileWords];
+    __shared__ __attribute__((aligned(16))) int flags[2 * NS];
+    constexpr bool rows = PR == PR_VOLT && NS <= 2;
     __shared__ __attribute__((aligned(16))) float vbuf[rows ? 8 * kVoltWords : 1];
     item_f32_split<XT, PR, NK, NS>(d, xcd_remap(blockIdx.x, nitems), nbg, at, flags, vbuf);
 }
@@ -553,9 +410,7 @@ template <int XT, int PR>
 inline void launch_split_pr(const BlockDesc& d, int nbg, int n, hipStream_t st) {
     const int ns = split_streams(d);
     switch (split_ksteps(d.S)) {
-        case 2:                                            // (complex float: split_takes)
-            if constexpr (XT != XT_CF32) launch_split_nk<XT, PR, 2>(d, ns, nbg, n, st);
-            break;
+        case 2: launch_split_nk<XT, PR, 2>(d, ns, nbg, n, st); break;
         case 4: launch_split_nk<XT, PR, 4>(d, ns, nbg, n, st); break;
         case 5: launch_split_nk<XT, PR, 5>(d, ns, nbg, n, st); break;
         case 6: launch_split_nk<XT, PR, 6>(d, ns, nbg, n, st); break;

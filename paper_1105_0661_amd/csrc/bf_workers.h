@@ -290,9 +290,7 @@ template <> LBF_INLINE void unpack2<CT_BF16>(uint32_t w, float& re, float& im) {
 // conversions: with addresses formed per chunk the loaders took 310 of the
 // 520 vector instructions of a step (ci16, 64 stations), which do not run
 // beside the MFMAs.
-// PL: planes of operand words a tile is staged as (the caller stores the
-// second, kATileWords behind the first).
-template <int XT, int CT, int NK, int NS, int PL = 1>
+template <int XT, int CT, int NK, int NS>
 struct TileLoader {
     static constexpr int BYTES = sample_bytes(XT);
     static constexpr int SPC = Chunk<XT, CT>::samples;     // samples per 16-byte chunk
@@ -319,7 +317,7 @@ struct TileLoader {
         // warms the cache for it (without: 1500 channels of ci8, 30 stations,
         // 200 beams 293 us instead of 279), and stage nothing
         voff = chunk_off(s, q, stride_bytes);
-        const int so = WIDE ? 0 : sg0 * 2 * PL * kATileWords;
+        const int so = WIDE ? 0 : sg0 * 2 * kATileWords;
         w0 = so + a_word(q * SPC, 0, s);
         w1 = SPI == 16 ? so + a_word(q * SPC, 0, s ^ 16) : w0;
         __asm__ volatile("" : "+v"(w0), "+v"(w1));
@@ -327,12 +325,9 @@ struct TileLoader {
     LBF_INLINE int stream(int i) const { return WIDE ? chunk_stream(0, i, SP, CPS) : sg0 + chunk_stream(0, i, SP, CPS); }
     LBF_INLINE int first_station(int i) const { return s0 + (WIDE ? chunk_station(0, i, SP, CPS) : 0); }
 
-    LBF_INLINE void load(int k, u32x4 (&dst)[CPT]) const { load_part<0, CPT>(k, dst); }
-    // chunks [LO, LO + N) of step k
-    template <int LO, int N>
-    LBF_INLINE void load_part(int k, u32x4 (&dst)[N]) const {
+    LBF_INLINE void load(int k, u32x4 (&dst)[CPT]) const {
 #pragma unroll
-        for (int i = LO; i < LO + N; ++i) {
+        for (int i = 0; i < CPT; ++i) {
             const int g = first_station(i) & ~7;
             const uint32_t off = tile_off(c, T, stream_tile(stream(i), k, NS, tile_lo, ntiles) * kTile, BYTES);
             const uint64_t base = reinterpret_cast<uint64_t>(x) + group_base(g, stride_bytes) + off;
@@ -341,7 +336,7 @@ struct TileLoader {
             const uint32_t n = __builtin_amdgcn_readfirstlane(tile_range(g, S, stride_bytes, off));
             const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
                 reinterpret_cast<void*>(((uint64_t)hi << 32) | lo), (short)0, (int)n, 0x00020000);
-            dst[i - LO] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)voff, 0, 0));
+            dst[i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)voff, 0, 0));
         }
     }
     // chunk i holds a station of the K-steps (uniform): the padded ones are not staged
@@ -355,7 +350,7 @@ struct TileLoader {
         // works on 32-station blocks), the other base for 16
         const int ds = WIDE ? chunk_station(0, i, SP, CPS) : 0;
         const int sg = chunk_stream(0, i, SP, CPS);        // beside the thread's own in w0
-        return (ds & 16 ? w1 : w0) + ((k & 1) + sg * 2) * PL * kATileWords + (ds & ~31);
+        return (ds & 16 ? w1 : w0) + ((k & 1) + sg * 2) * kATileWords + (ds & ~31);
     }
     LBF_INLINE void store(uint32_t* at, int k, int i, const u32x4 (&src)[CPT]) const {
         if (!staged(i)) return;

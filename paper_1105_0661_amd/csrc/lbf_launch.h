@@ -53,7 +53,6 @@ hipError_t launch_beamform_generic(const BlockDesc& d, hipStream_t st);
 hipError_t launch_fast_f32(const BlockDesc& d, hipStream_t st);
 hipError_t launch_split_ci8(const BlockDesc& d, hipStream_t st);    // FP32 split worker, by sample type
 hipError_t launch_split_ci16(const BlockDesc& d, hipStream_t st);
-hipError_t launch_split_cf32(const BlockDesc& d, hipStream_t st);
 hipError_t launch_fast_f16(const BlockDesc& d, hipStream_t st);
 hipError_t launch_fast_bf16(const BlockDesc& d, hipStream_t st);
 // FP16/BF16 fast kernels of one block part (n work items, nbg beam groups) by sample type

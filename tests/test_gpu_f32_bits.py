@@ -1,0 +1,90 @@
+"""FP32 blocks hold every bit of their weights and samples: what one live
+station leaves of a product that FP32 holds exactly is that product."""
+import math
+
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_1105_0661_amd import lbf  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+X = {"ci8": torch.int8, "ci16": torch.int16, "cf32": torch.float32}
+
+
+def _phases(shape, seed, amplitude=1.0):
+    g = torch.Generator().manual_seed(seed)
+    a = torch.rand(shape, generator=g, dtype=torch.float64) * (2.0 * math.pi)
+    return torch.stack([torch.cos(a), -torch.sin(a)], dim=-1).mul(amplitude).float()
+
+
+def _voltages(x, w):
+    return lbf.beamform(x.cuda(), w.cuda().contiguous(), lbf.VOLTAGES).cpu()          # [C][B][T][2][2]
+
+
+@pytest.mark.parametrize("xt", ["cf32"])
+@pytest.mark.parametrize("S", [1, 16, 17, 32, 40, 64])
+def test_a_weight_keeps_its_24_bits(S, xt):
+    # station s sends 2^k in one component of its own sample, all else is
+    # silent: each voltage is one weight component times 2^k, exactly
+    C, B = 2, 70
+    x = torch.zeros((S, C, S, 2, 2), dtype=X[xt])
+    k = torch.arange(S) % 7
+    for s in range(S):
+        x[s, :, s, 0, 0] = 2.0 ** k[s]
+        x[s, :, s, 1, 1] = -(2.0 ** k[s])
+    w = _phases((C, B, S), S, 0.7)
+    got = _voltages(x, w)
+    p = (2.0 ** k)[None, None, :, None]
+    assert torch.equal(got[:, :, :, 0], w * p)
+    assert torch.equal(got[:, :, :, 1], torch.stack([w[..., 1], -w[..., 0]], dim=-1) * p)
+
+
+@pytest.mark.parametrize("S", [1, 16, 20, 40, 64])
+def test_a_float_sample_keeps_its_24_bits(S):
+    # one station's weight is 2^k, the others' are zero: each voltage is that
+    # station's sample times 2^k, exactly
+    C, T = 2, 70
+    g = torch.Generator().manual_seed(S)
+    x = torch.randn((S, C, T, 2, 2), generator=g) * 100.0
+    w = torch.zeros((C, S, S, 2))
+    k = torch.arange(S) % 5
+    for s in range(S):
+        w[:, s, s, 0] = 2.0 ** k[s]
+    got = _voltages(x, w)                                                               # beam s: station s
+    assert torch.equal(got, x.permute(1, 0, 2, 3, 4) * (2.0 ** k)[None, :, None, None, None])
+
+
+def _levels(S, C, T, seed):
+    """Float samples whose level jumps between 32-sample tiles by factors beyond any shared exponent."""
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    x = torch.randn((S, C, T, 2, 2), generator=g, device="cuda")
+    e = torch.tensor([0, 0, 0, 0, 9, 9, -14, 3, 3, 20, -3, -3], device="cuda").repeat_interleave(32)
+    x.mul_(torch.exp2(e.float()).repeat((T + e.numel() - 1) // e.numel())[:T, None, None])
+    x[S // 2].mul_(2.0 ** -13)
+    return x
+
+
+@pytest.mark.parametrize("S,product,t_int", [(20, lbf.STOKES_IQUV, 1), (64, lbf.STOKES_IQUV, 4)])
+def test_float_results_do_not_depend_on_the_passes(S, product, t_int):
+    # the whole block's staging is larger than the 64 MiB scratch: passes of
+    # fewer channels, whose items are cut into other time segments
+    C, T, B = 256, 768, 128
+    fp = lbf.block_footprint(S, C, T, B, lbf.CF32, lbf.F32, product, t_int)
+    assert fp.staging_bytes > (64 << 20)
+    x = _levels(S, C, T, S)
+    w = _phases((C, B, S), S).cuda()
+    assert torch.equal(lbf.beamform(x, w, product, t_int), lbf.beamform_noalloc(x, w, product, t_int))
+
+
+def test_a_channel_does_not_see_its_neighbour():
+    # a ragged last tile reads on into the next channel: its level, or NaN there, changes no bit
+    S, T, B = 32, 75, 40
+    x = _levels(S, 2, T, 3).cpu()
+    w = _phases((2, B, S), 3)
+    want = _voltages(x, w)[0]
+    for v in (2.0 ** 30, 2.0 ** -30, float("nan")):
+        y = x.clone()
+        y[:, 1] *= v
+        assert torch.equal(_voltages(y, w)[0], want)
