@@ -150,8 +150,8 @@ void walk_h(Walk& w, const BlockDesc& d, int lo, int hi) {
     }
 }
 
-// items [lo, hi) of the FP32 split worker, its residual and exact-path loads
-// included
+// items [lo, hi) of the FP32 split worker; its residual and exact-path loads
+// are the same stations of the same samples
 void walk_split(Walk& w, const BlockDesc& d, int lo, int hi) {
     const int bytes = sample_bytes(d.xtype);
     const uint64_t xbuf = (uint64_t)d.S * d.C * d.T * bytes, wbuf = (uint64_t)d.C * d.B * d.S * 8;
@@ -178,9 +178,6 @@ void walk_split(Walk& w, const BlockDesc& d, int lo, int hi) {
                          ok ? ((uint64_t)bw * d.S + lane) * 8u : kNoLoad, ok ? weight_off(bw, d.S, lane, 8) : kNoLoad, 8,
                          wbuf, false);
             }
-            for (int s = 0; s < d.S; ++s)                      // the exact path's
-                w.access("weight load", weight_base(d, ip.c, 8), weight_range(d, 8), ((uint64_t)beam * d.S + s) * 8u,
-                         weight_off(beam, d.S, s, 8), 8, wbuf, false);
             // the loaders run up to two steps ahead of the last one
             for (int k = 0; k < nsteps + 2; ++k)
                 for (int i = 0; i < CPT; ++i) {

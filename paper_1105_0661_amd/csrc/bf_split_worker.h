@@ -24,10 +24,15 @@
 // plane of samples that LDS has no room for.
 //
 // What P pieces cannot hold takes the exact path, FP32 matrix instructions
-// over the same samples (one station each, in station order): a wave one of
-// whose beams has a weight that is not finite, or stations whose weights
+// over the same samples (one station each, in station order): a work item one
+// of whose beams has a weight that is not finite, or stations whose weights
 // differ in magnitude by more than 2^14 (the smallest would lose bits to the
-// FP16 range).  Sample residuals r, where a step holds any, take a second
+// FP16 range).  Such an item does nothing else, and has the samples in flight
+// a group of 8 stations ahead and the weights in LDS: 2048 channels of 64
+// stations, 768 samples, 128 beams, one station at 2^-16 of the others take
+// 1668 us, 1655 on an FP32 kernel of their own (item_f32_fast's schedule);
+// one load and one product at a time, behind the loop of the other waves,
+// took 3061.  Sample residuals r, where a step holds any, take a second
 // accumulation straight from HBM.
 //
 // Work split as in item_h_fast: a work group of 8 waves takes one channel and
@@ -196,13 +201,14 @@ LBF_INLINE void item_f32_split(const BlockDesc& d, int item, int nbg, uint32_t* 
 #pragma unroll
             for (int j = 0; j < NBEAM / 8; ++j) *reinterpret_cast<float2v*>(wl + (wave + 8 * j) * WROW + 2 * lane) = w[j];
         }
-        __syncthreads();
     }
+    int* any_exact = flags + 2 * NS;
+    if (tid == 0) *any_exact = 0;
+    __syncthreads();
     // this wave's weight pieces, both variants, all K-steps.  Magnitudes are
     // compared as integers, which orders NaN above infinity above the numbers.
     u32x4 wr[P][NK], wi[P][NK];
     int sc;
-    bool exact;
     {
         // read twice, the magnitudes, then the pieces, so that the raw
         // weights never sit beside all the pieces
@@ -228,7 +234,7 @@ LBF_INLINE void item_f32_split(const BlockDesc& d, int item, int nbg, uint32_t* 
         wmin = min(wmin, (uint32_t)__shfl_xor((int)wmin, 32, kWave));
         const float fmx = __uint_as_float(wmax), fmn = __uint_as_float(wmin + 1u);
         const bool bad = wmax >= 0x7f800000u || (wmax != 0u && fmn * kSplitRange < fmx);
-        exact = __builtin_amdgcn_ballot_w64(bad) != 0;
+        if (__builtin_amdgcn_ballot_w64(bad) != 0 && lane == 0) *any_exact = 1;
         sc = wmax != 0u && wmax < 0x7f800000u ? 15 - __builtin_amdgcn_frexp_expf(fmx) : 0;
         __asm__ volatile("" : "+v"(sc) : : "memory");           // the second reading stays a second one
 #pragma unroll
@@ -251,19 +257,13 @@ LBF_INLINE void item_f32_split(const BlockDesc& d, int item, int nbg, uint32_t* 
             if (kk & 1) __builtin_amdgcn_sched_barrier(0);
         }
     }
-    __syncthreads();                                       // the weights' LDS becomes the tiles'
-    // a wave whose beam tile lies wholly past the block's beams, or that takes
-    // the exact path, only loads, stages and meets the barriers
-    const bool idle = d.b0 + (bg * NBT + bt) * kTile >= d.b1 || exact;
+    __syncthreads();
+    const bool exact = __builtin_amdgcn_readfirstlane(*any_exact) != 0;
+    // a wave whose beam tile lies wholly past the block's beams only loads,
+    // stages and meets the barriers
+    const bool idle = d.b0 + (bg * NBT + bt) * kTile >= d.b1;
     const int trow = tile_row_sample(r);
     const int sw = a_swz(trow);
-
-    if constexpr (XT == XT_CI16) {
-        if (tid < 2 * NS) flags[tid] = -1;
-        __syncthreads();
-    }
-    store_chunks(0);
-    __syncthreads();
 
     floatx16 acc[4];
     int esc = sc;                                          // scale of the accumulators
@@ -289,29 +289,65 @@ LBF_INLINE void item_f32_split(const BlockDesc& d, int item, int nbg, uint32_t* 
         }
         split_epilogue<PR>(acc, ors, d, c, bm, tile * kTile, hh, ok, esc);
     };
-    // one tile on FP32 matrix instructions, straight from HBM: lane half h
-    // holds the re (0) or im (1) component of station s as K index h of a
-    // 32x32x2 MFMA
-    const uint32_t hsh = (uint32_t)h * (XT == XT_CI8 ? 8u : 16u);
-    auto exact_tile = [&](int tile) {
-        const int t = min(tile * kTile + trow, T - 1);
+    if (exact) {
+        // FP32 matrix instructions, lane half h holding the re (0) or im (1)
+        // component of station s as K index h of a 32x32x2 MFMA; samples
+        // straight from HBM, a group of 8 stations ahead of their use,
+        // weights from LDS
+        const int nmine = ntiles > sigma ? (ntiles - sigma + NS - 1) / NS : 0;   // this wave's tiles
+        if (idle || nmine == 0) return;
+        uint32_t hsh = (uint32_t)h * (XT == XT_CI8 ? 8u : 16u);
+        int wrow = (bt * kTile + r) * WROW;
+        __asm__ volatile("" : "+v"(hsh), "+v"(wrow));
+        typedef Raw<XT> R;
+        typename R::type ring[8];
+        auto load_quad = [&](int q4, int k, int g) {           // stations 8 g + 4 q4 .. + 3 of the wave's tile k
+            const int t = min((tile_lo + sigma + NS * min(k, nmine - 1)) * kTile + trow, T - 1);
+            const __amdgpu_buffer_rsrc_t rs = group_rsrc(d.x, 8 * g, S, stride_bytes);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) acc[q] = zero16();
-        for (int s = 0; s < S; ++s) {
-            const float2v w = __builtin_bit_cast(float2v, __builtin_amdgcn_raw_buffer_load_b64(
-                wrs, (int)weight_off(beam, S, s, 8), 0, 0));
-            float ax, ay;
-            Raw<XT>::half(buffer_sample<XT>(group_rsrc(d.x, s & ~7, S, stride_bytes),
-                                            sample_off(s & 7, stride_bytes, c, T, t, BYTES)), hsh, ax, ay);
-            const float br = h ? -w[1] : w[0], bi = h ? w[0] : w[1];
-            acc[0] = mfma_f32(ax, br, acc[0]);
-            acc[1] = mfma_f32(ax, bi, acc[1]);
-            acc[2] = mfma_f32(ay, br, acc[2]);
-            acc[3] = mfma_f32(ay, bi, acc[3]);
-        }
+            for (int i = 4 * q4; i < 4 * q4 + 4; ++i)
+                ring[i] = buffer_sample<XT>(rs, sample_off(i, stride_bytes, c, T, t, BYTES));
+        };
         esc = 0;
-    };
+        load_quad(0, 0, 0);
+        load_quad(1, 0, 0);
+        for (int k = 0; k < nmine; ++k) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) acc[q] = zero16();
+            for (int g = 0; g < NK; ++g) {
+                const bool last = g == NK - 1;
+#pragma unroll
+                for (int q4 = 0; q4 < 2; ++q4) {
+                    float ax[4], ay[4];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) R::half(ring[4 * q4 + i], hsh, ax[i], ay[i]);
+                    load_quad(q4, last ? k + 1 : k, last ? 0 : g + 1);
+                    const floatx4* p = reinterpret_cast<const floatx4*>(wl + wrow + 2 * (8 * g + 4 * q4));
+                    const floatx4 w[2] = {p[0], p[1]};
+                    __builtin_amdgcn_sched_barrier(0);         // the refill issues before the MFMAs
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const float re = w[i / 2][i % 2 * 2], im = w[i / 2][i % 2 * 2 + 1];
+                        const float br = h ? -im : re, bi = h ? re : im;
+                        acc[0] = mfma_f32(ax[i], br, acc[0]);
+                        acc[1] = mfma_f32(ax[i], bi, acc[1]);
+                        acc[2] = mfma_f32(ay[i], br, acc[2]);
+                        acc[3] = mfma_f32(ay[i], bi, acc[3]);
+                    }
+                }
+            }
+            epilogue(k);
+        }
+        return;
+    }
+
     const bool late = wave >= 4;                           // the second wave of each SIMD
+    if constexpr (XT == XT_CI16) {
+        if (tid < 2 * NS) flags[tid] = -1;
+        __syncthreads();
+    }
+    store_chunks(0);
+    __syncthreads();
     for (int k = 0; k < nsteps; ++k) {
         load_chunks(k + 1);
         if (!idle) {
@@ -375,20 +411,13 @@ LBF_INLINE void item_f32_split(const BlockDesc& d, int item, int nbg, uint32_t* 
         __syncthreads();
     }
     if (!idle && late) epilogue(nsteps - 1);
-    if (!exact) return;
-    for (int k = 0; k < nsteps; ++k) {                     // the exact path
-        const int tile = tile_lo + sigma + NS * k;
-        if (tile >= tile_lo + ntiles) break;
-        exact_tile(tile);
-        epilogue(k);
-    }
 }
 
 // 8 waves, two per SIMD; LDS: NS streams x 2 buffers of one A tile
 template <int XT, int PR, int NK, int NS>
 __global__ __launch_bounds__(kThreadsH) void bf_f32_split_kernel(BlockDesc d, int nbg, int nitems) {
     __shared__ __attribute__((aligned(16))) uint32_t at[NS * 2 * kATileWords];
-    __shared__ __attribute__((aligned(16))) int flags[2 * NS];
+    __shared__ __attribute__((aligned(16))) int flags[2 * NS + 1];
     constexpr bool rows = PR == PR_VOLT && NS <= 2;
     __shared__ __attribute__((aligned(16))) float vbuf[rows ? 8 * kVoltWords : 1];
     item_f32_split<XT, PR, NK, NS>(d, xcd_remap(blockIdx.x, nitems), nbg, at, flags, vbuf);

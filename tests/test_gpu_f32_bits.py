@@ -88,3 +88,27 @@ def test_a_channel_does_not_see_its_neighbour():
         y = x.clone()
         y[:, 1] *= v
         assert torch.equal(_voltages(y, w)[0], want)
+
+
+def _check_voltages64(x, w, got, chans):
+    """Voltages of some channels against 64-bit sums: 2 S roundings of a chain of sums, and two more."""
+    S = x.shape[0]
+    xs = x[:, chans].double().permute(1, 0, 2, 3, 4)                                      # [c][s][t][p][ri]
+    ws = w[chans].double()                                                                # [c][b][s][ri]
+    y = torch.einsum("cbs,cstp->cbtp", torch.view_as_complex(ws), torch.view_as_complex(xs.contiguous()))
+    mag = torch.einsum("cbs,cstp->cbtp", ws.abs().sum(-1), xs.abs().sum(-1))[..., None]
+    assert ((got[chans].double() - torch.view_as_real(y)).abs() <= (2 * S + 2) * 2.0 ** -24 * mag).all()
+
+
+@pytest.mark.parametrize("S,xt,B", [(5, "ci16", 70), (17, "ci8", 40), (40, "ci16", 10), (44, "ci8", 130), (64, "ci16", 70)])
+def test_weights_far_apart_in_long_items(S, xt, B):
+    # 25 tiles in items of 24 and 1: beams whose stations differ by 2^20 in
+    # every beam of a channel, in one beam of it, in none
+    C, T = 260, 779
+    g = torch.Generator().manual_seed(S)
+    x = (torch.randn((S, C, T, 2, 2), generator=g) * 30.0).round().clamp(-127, 127).to(X[xt])
+    x[S - 1, :, ::3] = 0
+    w = _phases((C, B, S), S)
+    w[0::3, :, S // 2] *= 2.0 ** -20
+    w[1::3, 3, 0] *= 2.0 ** 20
+    _check_voltages64(x, w, _voltages(x, w), [0, 1, 2, C - 2, C - 1])
