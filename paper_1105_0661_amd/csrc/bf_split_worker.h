@@ -7,48 +7,60 @@
 //  - int8 samples are FP16 numbers; an int16 sample is h + r with h its
 //    FP16 rounding and |r| <= 8, and r = 0 for every |x| <= 2048;
 //  - a weight is scaled by a power of two per beam (largest component of the
-//    beam to [2^14, 2^15)) and cut into P pieces w1 = f16(w), w2 = f16(w - w1),
-//    (w3 = f16(w - w1 - w2)).  Two pieces hold 22 bits and two signs, an error
-//    of at most one unit in the 24th bit; three pieces hold all 24 bits.  The
-//    scale leaves with the epilogue (2^-s for voltages, 2^-2s for Stokes).
-// P = 2 from 17 stations up (K-steps of 8 stations: 4 to 8), where the FP32
-// chain's own roundings, 2 S of them, are far above that error; P = 3 below
-// (2 K-steps), where they are not and the few K-steps cost little.
-// Relative rms error of the voltages against 64 bits, unit-modulus weights,
-// Gaussian int16 samples (FP32 matrix instructions -> this worker): 5.3e-8 ->
-// 2.9e-8 at 4 stations, 1.02e-7 -> 4.7e-8 at 16, 1.06e-7 -> 6.2e-8 at 17,
-// 2.03e-7 -> 9.6e-8 at 64; no station count from 1 to 64 is further off.
+//    beam to [2^14, 2^15)) and cut into three pieces w1 = f16(w), w2 =
+//    f16(w - w1), w3 = w - w1 - w2, together its 24 bits.  (A component below
+//    2^-15 of the beam's largest is held to 2^-39 of that.)  The scale leaves
+//    with the epilogue (2^-s for voltages, 2^-2s for Stokes).
+// Two pieces hold 22 bits and two signs, and drop the last bit of a weight in
+// four: the block named below took 405 us with two (ci8 360), 590 (540) with
+// three, 1655 on FP32 instructions.
+//
+// A tile is summed small terms first: over all K-steps the products with w3
+// and w2, sums 2^-11 of the result whose roundings vanish beside its own, then
+// over all K-steps those with w1.  So a result is rounded at its full size
+// once or twice per 8 stations, whichever stations are live; a chain of FP32
+// instructions rounds it twice per live station.
+// Relative rms error of the voltages against 64 bits, weights of modulus one,
+// Gaussian int16 samples of sigma 64 (FP32 matrix instructions -> this
+// worker): 5.4e-8 -> 2.9e-8 at 4 stations, 1.03e-7 -> 3.5e-8 at 16, 1.44e-7 ->
+// 4.1e-8 at 32, 2.02e-7 -> 5.1e-8 at 64 (7.5e-8 over the whole int16 range).
+// Of 64 stations with 3, 4 or 8 live, in one K-step or one in each, with
+// random, equal, real and uneven weights: 0.43 to 0.97 of the chain's error.
 //
 // Complex float samples stay on the FP32 instructions: as many bits in both
 // operands take six products of three pieces each at the least, and a third
 // plane of samples that LDS has no room for.
 //
-// What P pieces cannot hold takes the exact path, FP32 matrix instructions
+// What the pieces cannot hold takes the exact path, FP32 matrix instructions
 // over the same samples (one station each, in station order): a work item one
-// of whose beams has a weight that is not finite, or stations whose weights
+// of whose beams has a weight that is not finite, stations whose weights
 // differ in magnitude by more than 2^14 (the smallest would lose bits to the
-// FP16 range).  Such an item does nothing else, and has the samples in flight
-// a group of 8 stations ahead and the weights in LDS: 2048 channels of 64
-// stations, 768 samples, 128 beams, one station at 2^-16 of the others take
-// 1668 us, 1655 on an FP32 kernel of their own (item_f32_fast's schedule);
-// one load and one product at a time, behind the loop of the other waves,
-// took 3061.  Sample residuals r, where a step holds any, take a second
-// accumulation straight from HBM.
+// FP16 range), or fewer than kSplitLive stations with a weight.  Such an item
+// does nothing else, and has the samples in flight a group of 8 stations ahead
+// and the weights in LDS: 2048 channels of 64 stations, 768 samples, 128
+// beams, one station at 2^-16 of the others take 1660 us, 1650 on an FP32
+// kernel of their own (item_f32_fast's schedule); one load and one product at
+// a time, behind the loop of the other waves, took 3061.
+// Sample residuals r, where a tile holds any, are summed before the rest,
+// straight from HBM.
 //
 // Work split as in item_h_fast: a work group of 8 waves takes one channel and
 // 8/NS beam tiles of 32, its 32-sample tiles dealt to NS streams; samples are
 // staged once per work group in LDS, a wave keeps its beam tile's weight
-// pieces in registers (16 P NK of them), one accumulator set, the two waves
-// of a SIMD staggered so that one's epilogue meets the other's MFMAs.
+// pieces in registers, one accumulator set, the two waves of a SIMD staggered
+// so that one's epilogue meets the other's MFMAs.  With a piece as words (re,
+// -im), Re y = (x_re, x_im) . w and Im y = (x_im, -x_re) . w: a piece takes 4 NK
+// registers and the sample operand is turned, one packed multiplication a
+// word.  w1 is kept as (im, re) too where that fits without spills: 2048
+// channels of ci16, 48 stations, 300 beams 1236 -> 1183 us.
 #pragma once
 #include "bf_common.h"
 #include "bf_workers.h"
 
 namespace lbf {
 
-// K-steps of 8 stations and weight pieces of the split worker
+// K-steps of 8 stations of the split worker
 __host__ __device__ constexpr int split_ksteps(int S) { return S <= 16 ? 2 : S <= 32 ? 4 : (S + 7) / 8; }
-__host__ __device__ constexpr int split_pieces(int NK) { return NK == 2 ? 3 : 2; }
 
 // Sample streams: 4 (items of 64 beams) for at most 64 beams, where an item of
 // 128 would leave half its waves idle, else 2; complex int16 from 6 K-steps up
@@ -71,9 +83,29 @@ inline int block_items_split(const BlockDesc& d, int* nbg) {
 // its largest one that the pieces hold to 24 bits
 constexpr float kSplitRange = 16384.0f;
 
+// Fewest stations with a weight, in a beam that has any: a result of one or
+// two stations is rounded once or twice by the FP32 chain, and the FP16
+// instruction's sum of 8 stations and the accumulator is not the nearest FP32
+// number in every case.  rms error against 64 bits, FP32 chain / pieces: one
+// station of any weight 3.09e-8 / 3.24e-8, of real weight 2.5e-8 / 3.4e-8,
+// two 3.1e-8 / 3.4e-8, three 3.57e-8 / 3.4e-8 and from there on lower.
+constexpr int kSplitLive = 3;
+
 LBF_INLINE uint32_t pack_h(_Float16 lo, _Float16 hi) {
     const halfx2 v = {lo, hi};
     return __builtin_bit_cast(uint32_t, v);
+}
+
+// (x_re, x_im) -> (x_im, -x_re), four stations
+LBF_INLINE u32x4 turn(const u32x4& v) {
+    u32x4 r;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const uint32_t w = v[i];
+        const halfx2 x = __builtin_bit_cast(halfx2, w), sign = {(_Float16)1.0f, (_Float16)-1.0f};
+        r[i] = __builtin_bit_cast(uint32_t, (halfx2)(__builtin_shufflevector(x, x, 1, 0) * sign));
+    }
+    return r;
 }
 
 // The residuals x - f16(x) of a complex int16 value, as a packed f16 word
@@ -137,7 +169,6 @@ LBF_INLINE void item_f32_split(const BlockDesc& d, int item, int nbg, uint32_t* 
     typedef MfmaH<CT_F16> M;
     typedef M::vec V;
     typedef float float2v __attribute__((ext_vector_type(2)));
-    constexpr int P = split_pieces(NK);
     constexpr int BYTES = sample_bytes(XT);
     constexpr int NBT = 8 / NS;                            // beam tiles per item
     typedef TileLoader<XT, CT_F16, NK, NS> Loader;
@@ -205,9 +236,10 @@ LBF_INLINE void item_f32_split(const BlockDesc& d, int item, int nbg, uint32_t* 
     int* any_exact = flags + 2 * NS;
     if (tid == 0) *any_exact = 0;
     __syncthreads();
-    // this wave's weight pieces, both variants, all K-steps.  Magnitudes are
-    // compared as integers, which orders NaN above infinity above the numbers.
-    u32x4 wr[P][NK], wi[P][NK];
+    // this wave's weight pieces, all K-steps.  Magnitudes are compared as
+    // integers, which orders NaN above infinity above the numbers.
+    constexpr bool BOTH = NK <= (XT == XT_CI8 ? 7 : 6);    // w1 as (im, re) too, where it fits without spills
+    u32x4 wr[3][NK], wi[BOTH ? NK : 1];
     int sc;
     {
         // read twice, the magnitudes, then the pieces, so that the raw
@@ -218,6 +250,7 @@ LBF_INLINE void item_f32_split(const BlockDesc& d, int item, int nbg, uint32_t* 
             w[1] = p[1];
         };
         uint32_t wmax = 0u, wmin = 0xffffffffu;               // wmin: the smallest non-zero magnitude minus one
+        int live = 0;                                         // stations with a weight
 #pragma unroll
         for (int kk = 0; kk < NK; ++kk) {
             floatx4 w[2];
@@ -228,12 +261,14 @@ LBF_INLINE void item_f32_split(const BlockDesc& d, int item, int nbg, uint32_t* 
                 const uint32_t m = max(__float_as_uint(re) & 0x7fffffffu, __float_as_uint(im) & 0x7fffffffu);
                 wmax = max(wmax, m);
                 wmin = min(wmin, m - 1u);
+                live += m != 0u;
             }
         }
         wmax = max(wmax, (uint32_t)__shfl_xor((int)wmax, 32, kWave));
         wmin = min(wmin, (uint32_t)__shfl_xor((int)wmin, 32, kWave));
+        live += __shfl_xor(live, 32, kWave);
         const float fmx = __uint_as_float(wmax), fmn = __uint_as_float(wmin + 1u);
-        const bool bad = wmax >= 0x7f800000u || (wmax != 0u && fmn * kSplitRange < fmx);
+        const bool bad = wmax >= 0x7f800000u || (wmax != 0u && (fmn * kSplitRange < fmx || live < kSplitLive));
         if (__builtin_amdgcn_ballot_w64(bad) != 0 && lane == 0) *any_exact = 1;
         sc = wmax != 0u && wmax < 0x7f800000u ? 15 - __builtin_amdgcn_frexp_expf(fmx) : 0;
         __asm__ volatile("" : "+v"(sc) : : "memory");           // the second reading stays a second one
@@ -246,12 +281,12 @@ LBF_INLINE void item_f32_split(const BlockDesc& d, int item, int nbg, uint32_t* 
                 float re = __builtin_amdgcn_ldexpf(w[i / 2][i % 2 * 2], sc);
                 float im = __builtin_amdgcn_ldexpf(w[i / 2][i % 2 * 2 + 1], sc);
 #pragma unroll
-                for (int p = 0; p < P; ++p) {
+                for (int p = 0; p < 3; ++p) {
                     const _Float16 pr = (_Float16)re, pi = (_Float16)im;
                     re -= (float)pr;                       // exact
                     im -= (float)pi;
                     wr[p][kk][i] = pack_h(pr, -pi);
-                    wi[p][kk][i] = pack_h(pi, pr);
+                    if (BOTH && p == 0) wi[kk][i] = pack_h(pi, pr);
                 }
             }
             if (kk & 1) __builtin_amdgcn_sched_barrier(0);
@@ -269,8 +304,17 @@ LBF_INLINE void item_f32_split(const BlockDesc& d, int item, int nbg, uint32_t* 
     int esc = sc;                                          // scale of the accumulators
 #pragma unroll
     for (int q = 0; q < 4; ++q) acc[q] = zero16();
-    auto mfma4 = [&](const V& a, const V& b, const u32x4& r4, const u32x4& i4) {
-        const V br = __builtin_bit_cast(V, r4), bi = __builtin_bit_cast(V, i4);
+    // one operand pair (both polarisations) with a piece kept once, and with w1
+    auto mfma_turned = [&](const u32x4& x, const u32x4& y, const u32x4& tx, const u32x4& ty, const u32x4& w4) {
+        const V w = __builtin_bit_cast(V, w4);
+        acc[0] = M::mfma(__builtin_bit_cast(V, x), w, acc[0]);
+        acc[1] = M::mfma(__builtin_bit_cast(V, tx), w, acc[1]);
+        acc[2] = M::mfma(__builtin_bit_cast(V, y), w, acc[2]);
+        acc[3] = M::mfma(__builtin_bit_cast(V, ty), w, acc[3]);
+    };
+    auto mfma_first = [&](const u32x4& x, const u32x4& y, int kk) {
+        const V a = __builtin_bit_cast(V, x), b = __builtin_bit_cast(V, y);
+        const V br = __builtin_bit_cast(V, wr[0][kk]), bi = __builtin_bit_cast(V, wi[BOTH ? kk : 0]);
         acc[0] = M::mfma(a, br, acc[0]);
         acc[1] = M::mfma(a, bi, acc[1]);
         acc[2] = M::mfma(b, br, acc[2]);
@@ -352,36 +396,8 @@ LBF_INLINE void item_f32_split(const BlockDesc& d, int item, int nbg, uint32_t* 
         load_chunks(k + 1);
         if (!idle) {
             if (late && k > 0) epilogue(k - 1);
-            int rowx = (sigma * 2 + (k & 1)) * kATileWords + 2 * trow * kARow, swx = 4 * (h ^ sw);
-            __asm__ volatile("" : "+v"(rowx), "+v"(swx));
-            const uint32_t* ax0 = at + rowx;
-            __builtin_amdgcn_sched_barrier(0);
-            // operands one K-step ahead from LDS; the next step's samples
-            // staged under the second half of the MFMAs
-            u32x4 ax[2], ay[2];
-            ax[0] = *reinterpret_cast<const u32x4*>(ax0 + swx);
-            ay[0] = *reinterpret_cast<const u32x4*>(ax0 + kARow + swx);
 #pragma unroll
-            for (int kk = 0; kk < NK; ++kk) {
-                if (kk + 1 < NK) {
-                    const int off = swx ^ (8 * (kk + 1));       // 4 ((2 kk + 2 + h) ^ sw)
-                    ax[(kk + 1) & 1] = *reinterpret_cast<const u32x4*>(ax0 + off);
-                    ay[(kk + 1) & 1] = *reinterpret_cast<const u32x4*>(ax0 + kARow + off);
-                }
-                const V a = __builtin_bit_cast(V, ax[kk & 1]), b = __builtin_bit_cast(V, ay[kk & 1]);
-#pragma unroll
-                for (int p = P - 1; p >= 0; --p) {            // the small pieces first
-                    if (kk == 0 && p == P - 1) {
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) acc[q] = zero16();
-                    }
-                    mfma4(a, b, wr[p][kk], wi[p][kk]);
-                }
-#pragma unroll
-                for (int i = 0; i < CPT; ++i)
-                    if (kk == NK / 2 + i * (NK - NK / 2) / CPT) store_chunk(k + 1, i);
-                __builtin_amdgcn_sched_barrier(0);
-            }
+            for (int q = 0; q < 4; ++q) acc[q] = zero16();
             if (XT == XT_CI16 && __builtin_amdgcn_readfirstlane(flags[(k & 1) * NS + sigma]) == k) {
                 // residuals of this tile's samples, straight from HBM (rows past T: its last sample)
                 const int t = min((min(tile_lo + sigma + NS * k, tile_lo + ntiles - 1)) * kTile + trow, T - 1);
@@ -397,11 +413,46 @@ LBF_INLINE void item_f32_split(const BlockDesc& d, int item, int nbg, uint32_t* 
                         ux[i] = residual_i16x2(v[0]);
                         uy[i] = residual_i16x2(v[1]);
                     }
-                    const V a = __builtin_bit_cast(V, ux), b = __builtin_bit_cast(V, uy);
+                    const u32x4 tx = turn(ux), ty = turn(uy);
 #pragma unroll
-                    for (int p = P - 1; p >= 0; --p) mfma4(a, b, wr[p][kk], wi[p][kk]);
+                    for (int p = 2; p >= 0; --p) mfma_turned(ux, uy, tx, ty, wr[p][kk]);
                     __builtin_amdgcn_sched_barrier(0);         // one K-step's loads at a time
                 }
+            }
+            int rowx = (sigma * 2 + (k & 1)) * kATileWords + 2 * trow * kARow, swx = 4 * (h ^ sw);
+            __asm__ volatile("" : "+v"(rowx), "+v"(swx));
+            const uint32_t* ax0 = at + rowx;
+            __builtin_amdgcn_sched_barrier(0);
+            // operands one K-step ahead from LDS, K-steps 0 .. NK - 1 with the
+            // small pieces, then again with w1; the next step's samples staged
+            // under the later MFMAs
+            u32x4 ax[2], ay[2];
+            ax[0] = *reinterpret_cast<const u32x4*>(ax0 + swx);
+            ay[0] = *reinterpret_cast<const u32x4*>(ax0 + kARow + swx);
+#pragma unroll
+            for (int j = 0; j < 2 * NK; ++j) {
+                const int kk = j % NK;
+                if (j + 1 < 2 * NK) {
+                    const int off = swx ^ (8 * ((j + 1) % NK));    // 4 ((2 kk + h) ^ sw)
+                    ax[(j + 1) & 1] = *reinterpret_cast<const u32x4*>(ax0 + off);
+                    ay[(j + 1) & 1] = *reinterpret_cast<const u32x4*>(ax0 + kARow + off);
+                }
+                const u32x4 &a = ax[j & 1], &b = ay[j & 1];
+                if (BOTH && j >= NK) {
+                    mfma_first(a, b, kk);
+                } else {
+                    const u32x4 ta = turn(a), tb = turn(b);
+                    if (j < NK) {
+                        mfma_turned(a, b, ta, tb, wr[2][kk]);
+                        mfma_turned(a, b, ta, tb, wr[1][kk]);
+                    } else {
+                        mfma_turned(a, b, ta, tb, wr[0][kk]);
+                    }
+                }
+#pragma unroll
+                for (int i = 0; i < CPT; ++i)
+                    if (j == NK + i * NK / CPT) store_chunk(k + 1, i);
+                __builtin_amdgcn_sched_barrier(0);
             }
             __builtin_amdgcn_sched_barrier(0);
             if (!late) epilogue(k);

@@ -23,7 +23,7 @@ def _voltages(x, w):
     return lbf.beamform(x.cuda(), w.cuda().contiguous(), lbf.VOLTAGES).cpu()          # [C][B][T][2][2]
 
 
-@pytest.mark.parametrize("xt", ["cf32"])
+@pytest.mark.parametrize("xt", ["ci8", "ci16", "cf32"])
 @pytest.mark.parametrize("S", [1, 16, 17, 32, 40, 64])
 def test_a_weight_keeps_its_24_bits(S, xt):
     # station s sends 2^k in one component of its own sample, all else is
@@ -112,3 +112,40 @@ def test_weights_far_apart_in_long_items(S, xt, B):
     w[0::3, :, S // 2] *= 2.0 ** -20
     w[1::3, 3, 0] *= 2.0 ** 20
     _check_voltages64(x, w, _voltages(x, w), [0, 1, 2, C - 2, C - 1])
+
+
+def _rms(S, xt, live, weights, seed):
+    """Relative rms error of the voltages against 64 bits, and what a chain of FP32 products and sums leaves."""
+    C, T, B = 4, 256, 48
+    g = torch.Generator().manual_seed(seed)
+    x = (torch.randn((S, C, T, 2, 2), generator=g) * 20.0).round().clamp(-127, 127).to(X[xt])
+    w = _phases((C, B, S), seed)
+    if weights == "equal":
+        w = (torch.rand((C, B, 1, 1), generator=g) + 0.5) * torch.tensor([1.0, 0.0]).expand_as(w)
+    mask = torch.zeros(S)
+    mask[live] = 1.0
+    w = w * mask[:, None]
+    xs = x.float().permute(1, 0, 2, 3, 4)
+    y = torch.view_as_real(torch.einsum("cbs,cstp->cbtp", torch.view_as_complex(w.double()),
+                                        torch.view_as_complex(xs.double().contiguous())))
+    re, im = torch.zeros(y.shape[:-1]), torch.zeros(y.shape[:-1])
+    for s in live:                                                # products and sums each rounded once
+        wr, wi = w[:, :, s, 0, None, None], w[:, :, s, 1, None, None]
+        xr, xi = xs[:, None, s, ..., 0], xs[:, None, s, ..., 1]
+        re = (re.double() + wr.double() * xr.double()).float()
+        re = (re.double() - wi.double() * xi.double()).float()
+        im = (im.double() + wi.double() * xr.double()).float()
+        im = (im.double() + wr.double() * xi.double()).float()
+    chain = torch.stack([re, im], dim=-1).double()
+    return ((_voltages(x, w).double() - y).norm() / y.norm()).item(), ((chain - y).norm() / y.norm()).item()
+
+
+@pytest.mark.parametrize("xt", ["ci8", "ci16"])
+@pytest.mark.parametrize("weights", ["phases", "equal"])
+@pytest.mark.parametrize("S,live", [(1, [0]), (3, [0, 1, 2]), (17, list(range(17))), (64, [9]), (64, [3, 59]),
+                                    (64, [5, 21, 37]), (64, list(range(0, 64, 8))), (64, list(range(8))), (64, list(range(64)))],
+                         ids=lambda v: str(v) if isinstance(v, int) else "%d live" % len(v))
+def test_no_further_off_than_a_chain_of_fp32_sums(S, live, weights, xt):
+    # over 98304 values; 2 % for the spread of an rms over them
+    got, chain = _rms(S, xt, live, weights, 7 * S + len(live))
+    assert got <= 1.02 * chain
