@@ -41,10 +41,11 @@ LBF_HD int seg_tiles(const BlockDesc& d, int nbg) {
     return seg;
 }
 
-// "no store": an offset past every output descriptor, which the hardware
-// drops.  2^31, not 2^32 - 1: the range check adds the access size to the
-// offset, and the latter would wrap around to an in-range value.
-constexpr uint32_t kNoStore = 0x80000000u;
+// "no access": an offset past every output and weight descriptor (fast_path
+// bounds both), where the hardware drops a store and a load reads zeros.
+// 2^31, not an offset next to 2^32: the range check adds the access size to
+// the offset, and such a sum could wrap around to an in-range value.
+constexpr uint32_t kNoAccess = 0x80000000u;
 
 // A work item of the fast workers: channel c (of [c0, c0 + nc)), beam group
 // bg, sample tiles [tile_lo, tile_lo + ntiles) (nbg beam groups).

@@ -44,11 +44,13 @@ struct Walk {
                         (unsigned long long)(base + range), (unsigned long long)buf);
         if (off64 != off32)
             return fail("%s: 32-bit offset wraps (%llu != %u)", what, (unsigned long long)off64, off32);
+        if (off32 + (uint32_t)size < off32)
+            return fail("%s: offset %u and access size %d wrap in 32 bits", what, off32, size);
         const bool in_range = off64 + (uint64_t)size <= range;
         if (land && !in_range)
             return fail("%s: a store meant to land at offset %llu is outside its descriptor of %llu bytes", what,
                         (unsigned long long)off64, (unsigned long long)range);
-        if (!land && off32 == kNoStore && in_range) return fail("%s: the no-store offset is in range", what);
+        if (!land && off32 == kNoAccess && in_range) return fail("%s: the no-access offset is in range", what);
     }
 };
 
@@ -77,8 +79,8 @@ void stores_of_tile(Walk& w, const BlockDesc& d, int c, int beam, int bend, int 
         for (int smp = 0; smp < 16; ++smp) {
             const int t = tile * kTile + 16 * h + smp;
             const bool ok = tile_ok && beam < bend && t < T;
-            const uint32_t off = ok ? volt_off(beam, T, t) : kNoStore;
-            const uint64_t o64 = ok ? ((uint64_t)beam * T + t) * 16u : kNoStore;
+            const uint32_t off = ok ? volt_off(beam, T, t) : kNoAccess;
+            const uint64_t o64 = ok ? ((uint64_t)beam * T + t) * 16u : kNoAccess;
             w.access("voltage store", base, range, o64, off, 16, buf, ok);
         }
         return;
@@ -89,16 +91,16 @@ void stores_of_tile(Walk& w, const BlockDesc& d, int c, int beam, int bend, int 
         const bool ok = tile_ok && beam < bend && tq < T2;
         if (d.order == 0) {                                    // one store per parameter, counted as one access
             for (int k = 0; k < K; ++k) {
-                const uint32_t off = (ok ? stokes_off_final(d, c, T2, tq, beam, K) : kNoStore) + k * stokes_plane(d, T2);
+                const uint32_t off = (ok ? stokes_off_final(d, c, T2, tq, beam, K) : kNoAccess) + k * stokes_plane(d, T2);
                 const uint64_t o64 = ok ? (((uint64_t)beam * K + k) * T2 + tq) * d.C * 4u + (uint64_t)c * 4u
-                                        : kNoStore + (uint64_t)k * stokes_plane(d, T2);
+                                        : kNoAccess + (uint64_t)k * stokes_plane(d, T2);
                 w.access("Stokes store", base, range, o64, off, 4, buf, ok);
                 w.n -= k > 0;
             }
             continue;
         }
-        const uint32_t off = ok ? stokes_off(tq, d.ld_row, beam, K) : kNoStore;
-        const uint64_t o64 = ok ? ((uint64_t)tq * d.ld_row + (uint64_t)beam * K) * 4u : kNoStore;
+        const uint32_t off = ok ? stokes_off(tq, d.ld_row, beam, K) : kNoAccess;
+        const uint64_t o64 = ok ? ((uint64_t)tq * d.ld_row + (uint64_t)beam * K) * 4u : kNoAccess;
         w.access("Stokes store", base, range, o64, off, 4 * K, buf, ok);
     }
 }
@@ -124,7 +126,7 @@ void walk_h(Walk& w, const BlockDesc& d, int lo, int hi) {
             auto weights = [&](int bw, int s4) {
                 const bool ok = bw < d.b1 && s4 < d.S;
                 w.access("weight load", weight_base(d, ip.c, 4), weight_range(d, 4),
-                         ok ? ((uint64_t)bw * d.S + s4) * 4u : kNoLoad, ok ? weight_off(bw, d.S, s4, 4) : kNoLoad, 16,
+                         ok ? ((uint64_t)bw * d.S + s4) * 4u : kNoAccess, ok ? weight_off(bw, d.S, s4, 4) : kNoAccess, 16,
                          wbuf, false);
             };
             if (nsteps >= kRowSteps)
@@ -175,7 +177,7 @@ void walk_split(Walk& w, const BlockDesc& d, int lo, int hi) {
                 if (ok && ((uint64_t)bw * d.S + lane) * 8u + 8u > weight_range(d, 8))
                     return w.fail("weight load of beam %d station %d past its channel", bw, lane);
                 w.access("weight load", weight_base(d, ip.c, 8), weight_range(d, 8),
-                         ok ? ((uint64_t)bw * d.S + lane) * 8u : kNoLoad, ok ? weight_off(bw, d.S, lane, 8) : kNoLoad, 8,
+                         ok ? ((uint64_t)bw * d.S + lane) * 8u : kNoAccess, ok ? weight_off(bw, d.S, lane, 8) : kNoAccess, 8,
                          wbuf, false);
             }
             // the loaders run up to two steps ahead of the last one

@@ -445,22 +445,19 @@ LBF_INLINE void epilogue_tile(const floatx16 (&acc)[4], const EpiCtx& e, int bea
 
 // Branch-free stores of the fast workers.  The descriptor covers one channel
 // of the output; a lane with nothing to store (beam >= B, sample past the
-// end, no tile) uses the offset kNoStore, past the end of every output
+// end, no tile) uses the offset kNoAccess, past the end of every output
 // descriptor, which the hardware drops, so the epilogue has no control flow
 // and interleaves freely with the MFMAs of the next tile.  Per-channel outputs
 // are below 2^31 bytes (fast_path).
 
-// off if ok, else kNoStore, as a lane select the compiler keeps (a plain ?:
+// off if ok, else kNoAccess, as a lane select the compiler keeps (a plain ?:
 // is turned into a branch around the store)
 LBF_INLINE uint32_t store_off(bool ok, uint32_t off) {
     const uint64_t m = __builtin_amdgcn_ballot_w64(ok);
     uint32_t r;
-    __asm__("v_cndmask_b32_e64 %0, %1, %2, %3" : "=v"(r) : "v"(kNoStore), "v"(off), "s"(m));
+    __asm__("v_cndmask_b32_e64 %0, %1, %2, %3" : "=v"(r) : "v"(kNoAccess), "v"(off), "s"(m));
     return r;
 }
-
-// An offset past every weight descriptor: the load returns zero
-constexpr uint32_t kNoLoad = 0xfffffff0u;
 
 // a if ok, else b, as a lane select the compiler keeps (a plain ?: becomes a branch around the access)
 LBF_INLINE uint32_t select_off(bool ok, uint32_t a, uint32_t b) {
@@ -771,10 +768,11 @@ constexpr size_t kDirectBytes = (size_t)8 << 20;
 __host__ __device__ inline bool fast_path(const BlockDesc& d) {
     if (d.S > kStationChunk) return false;
     if (d.product != PR_VOLT && (d.t_int > 16 || d.f_int != 1)) return false;
-    // one channel's output (addressed with 32-bit buffer offsets, 2^31 = "no store")
+    // one channel's output and weights (32-bit buffer offsets, kNoAccess = 2^31)
     const double out_ch = d.product == PR_VOLT ? 16.0 * d.B * (double)d.T
                                                : 4.0 * staging_ld(d.B, d.product) * (double)(d.T / d.t_int);
-    if (out_ch >= 2147483648.0 - 4096.0) return false;
+    const double w_ch = (double)d.B * d.S * (d.ctype == CT_F32 ? 8 : 4);
+    if (out_ch >= 2147483648.0 - 4096.0 || w_ch >= 2147483648.0 - 4096.0) return false;
     return 8.0 * (double)d.C * (double)d.T * sample_bytes(d.xtype) < 2147483648.0 - 4096.0;
 }
 

@@ -226,7 +226,7 @@ LBF_INLINE void item_f32_split(const BlockDesc& d, int item, int nbg, uint32_t* 
         for (int j = 0; j < NBEAM / 8; ++j) {
             const int bw = d.b0 + bg * NBEAM + wave + 8 * j;
             w[j] = __builtin_bit_cast(float2v, __builtin_amdgcn_raw_buffer_load_b64(
-                wrs, (int)select_off(bw < d.b1 && lane < S, weight_off(bw, S, lane, 8), kNoLoad), 0, 0));
+                wrs, (int)select_off(bw < d.b1 && lane < S, weight_off(bw, S, lane, 8), kNoAccess), 0, 0));
         }
         if (lane < 8 * NK) {
 #pragma unroll

@@ -430,7 +430,7 @@ LBF_INLINE void item_h_fast(const BlockDesc& d, int item, int nbg, uint32_t* at)
         const __amdgpu_buffer_rsrc_t rs = weight_rsrc(d, c, 4);
         auto load_row = [&](int bw, int s4) {              // stations s4 .. s4 + 3 of beam bw
             u32x4 v = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(
-                rs, (int)select_off(bw < bend && s4 < S, weight_off(bw, S, s4, 4), kNoLoad), 0, 0));
+                rs, (int)select_off(bw < bend && s4 < S, weight_off(bw, S, s4, 4), kNoAccess), 0, 0));
 #pragma unroll
             for (int i = 1; i < 4; ++i)
                 if (s4 + i >= S) v[i] = 0u;

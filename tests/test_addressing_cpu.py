@@ -126,3 +126,10 @@ def test_set_tile_streams_takes_only_item_shapes(streams):
         assert ei.value.code == lbf.E_INVAL
     for ok in (0, 1, 2, 4):
         streams(ok)
+
+
+@pytest.mark.parametrize("ctype,B", [(lbf.F32, 1 << 22), (lbf.F16, 1 << 23)], ids=["f32", "f16"])
+def test_weights_of_a_channel_stay_below_the_no_access_offset(ctype, B):
+    # 64 stations x B beams of one channel: 2^31 bytes of weights, which the
+    # offset of a dropped load would be inside of; the generic workers take them
+    assert lbf.check_addressing(64, 1, 1, B, lbf.CI8, ctype, lbf.STOKES_I, 1, 1) == 0
