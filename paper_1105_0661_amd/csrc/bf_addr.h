@@ -100,25 +100,34 @@ LBF_HD uint32_t tile_range(int s0, int S, uint32_t stride_bytes, uint32_t off) {
 }
 
 // The sample loaders of the workers that stage tiles in LDS: a tile's 16-byte
-// chunks (cps of them per station), stations padded to sp (16, 32 or 64), are
-// dealt to the work group's threads, chunk i of thread tid being number
-// tid + kLoaders i of the step's ns tiles.  All the divisors are powers of
-// two, a wave's chunks belong to one group of 8 stations and one stream, and
-// the station's number within its group does not depend on i.  (Waves of 8
-// chunks of 8 stations store to LDS with 60 % fewer bank conflicts, which
-// changed no time, and read 128-byte runs instead of 256 or 512: an HBM-bound
-// block, 64 stations and 10 beams as voltages, took 1041 instead of 1006 us.)
-constexpr int kLoaders = 512;
+// chunks (cps of them per station, 8, 16 or 32), stations padded to the 8 nk
+// of the K-steps, are dealt to the work group's waves 64 at a time: 8, 4 or 2
+// stations of one group of 8, so wave_loads of them to a group.  Load i of a
+// wave is number wave + kLoaderWaves i of the step's ns tiles; its group and
+// stream are uniform, and the station within the group does not depend on i.
+// (Stations padded to 32 or 64 instead, for divisors that are powers of two,
+// cost a step up to 24 stations' loads: 16384 channels of ci8, 38 stations, 192
+// samples, 3 beams 396 -> 470 us.  Waves of 8 chunks of 8 stations store to
+// LDS with 60 % fewer bank conflicts, which changed no time, and read 128-byte
+// runs instead of 256 or 512: an HBM-bound block, 64 stations and 10 beams as
+// voltages, took 1041 instead of 1006 us.)
+constexpr int kLoaderWaves = 8;
 
-LBF_HD constexpr int padded_stations(int nk) { return nk <= 2 ? 16 : nk <= 4 ? 32 : 64; }
-LBF_HD constexpr int chunks_per_thread(int ns, int sp, int cps) {
-    return (ns * sp * cps + kLoaders - 1) / kLoaders;
+LBF_HD constexpr int wave_loads(int cps) { return cps / 8; }
+LBF_HD constexpr int chunks_per_thread(int ns, int nk, int cps) {
+    return (ns * nk * wave_loads(cps) + kLoaderWaves - 1) / kLoaderWaves;
 }
-LBF_HD constexpr int chunk_stream(int tid, int i, int sp, int cps) { return (tid + kLoaders * i) / (sp * cps); }
-LBF_HD constexpr int chunk_station(int tid, int i, int sp, int cps) { return (tid + kLoaders * i) / cps % sp; }
+// number of the wave's load i among the groups of the step's tiles: group n % nk of stream n / nk
+LBF_HD constexpr int chunk_group(int tid, int i, int cps) {
+    return tid / kWave / wave_loads(cps) + kLoaderWaves / wave_loads(cps) * i;
+}
+// station within the group
+LBF_HD constexpr int chunk_station(int tid, int cps) {
+    return tid / kWave % wave_loads(cps) * (kWave / cps) + tid % kWave / cps;
+}
 LBF_HD constexpr int chunk_q(int tid, int cps) { return tid % cps; }
 // bytes of a thread's offset into the descriptor: station of the group, chunk of the tile
-LBF_HD uint32_t chunk_off(int s, int q, uint32_t stride_bytes) { return (uint32_t)(s & 7) * stride_bytes + 16u * (uint32_t)q; }
+LBF_HD uint32_t chunk_off(int s, int q, uint32_t stride_bytes) { return (uint32_t)s * stride_bytes + 16u * (uint32_t)q; }
 // the stream's tile of step k, or the item's last tile once it has run out
 LBF_HD int stream_tile(int sg, int k, int ns, int tile_lo, int ntiles) {
     const int i = sg + ns * k;

@@ -113,7 +113,7 @@ void walk_h(Walk& w, const BlockDesc& d, int lo, int hi) {
     const uint32_t stride = (uint32_t)stride64;
     if (stride != stride64) return w.fail("station stride does not fit 32 bits");
     const int NS = fast_h_streams(d), NK = fast_h_ksteps(d.S), NBT = 8 / NS;
-    const int CPS = kTile * bytes / 16, SP = padded_stations(NK), CPT = chunks_per_thread(NS, SP, CPS);
+    const int CPS = kTile * bytes / 16, CPT = chunks_per_thread(NS, NK, CPS);
     int nbg;
     const int items = block_items_fast_h(d, &nbg);
     for (int item = lo; item < std::min(hi, items) && !w.bad; ++item) {
@@ -137,12 +137,12 @@ void walk_h(Walk& w, const BlockDesc& d, int lo, int hi) {
             // the loaders run up to two steps ahead of the last one
             for (int k = 0; k < nsteps + 2; ++k)
                 for (int i = 0; i < CPT; ++i) {
-                    const int sg = chunk_stream(tid, i, SP, CPS), s = chunk_station(tid, i, SP, CPS), s0 = s & ~7;
+                    const int n = chunk_group(tid, i, CPS), sg = n / NK, s = chunk_station(tid, CPS), s0 = 8 * (n % NK);
                     const int t = stream_tile(sg, k, NS, ip.tile_lo, ip.ntiles) * kTile, q = chunk_q(tid, CPS);
                     const uint32_t off = tile_off(ip.c, d.T, t, bytes);
                     if (off != ((uint64_t)ip.c * d.T + t) * bytes) return w.fail("the tile's offset wraps");
                     w.access("sample load", group_base(s0, stride) + off, tile_range(s0, d.S, stride, off),
-                             (uint64_t)(s & 7) * stride64 + 16u * q, chunk_off(s, q, stride), 16, xbuf, false);
+                             (uint64_t)s * stride64 + 16u * q, chunk_off(s, q, stride), 16, xbuf, false);
                 }
             for (int k = 0; k < nsteps; ++k) {
                 const int tile = ip.tile_lo + sigma + NS * k;
@@ -161,7 +161,7 @@ void walk_split(Walk& w, const BlockDesc& d, int lo, int hi) {
     const uint32_t stride = (uint32_t)stride64;
     if (stride != stride64) return w.fail("station stride does not fit 32 bits");
     const int NS = split_streams(d), NK = split_ksteps(d.S), NBT = 8 / NS;
-    const int CPS = kTile * bytes / 16, SP = padded_stations(NK), CPT = chunks_per_thread(NS, SP, CPS);
+    const int CPS = kTile * bytes / 16, CPT = chunks_per_thread(NS, NK, CPS);
     int nbg;
     const int items = block_items_split(d, &nbg);
     for (int item = lo; item < std::min(hi, items) && !w.bad; ++item) {
@@ -183,12 +183,12 @@ void walk_split(Walk& w, const BlockDesc& d, int lo, int hi) {
             // the loaders run up to two steps ahead of the last one
             for (int k = 0; k < nsteps + 2; ++k)
                 for (int i = 0; i < CPT; ++i) {
-                    const int sg = chunk_stream(tid, i, SP, CPS), s = chunk_station(tid, i, SP, CPS), s0 = s & ~7;
+                    const int n = chunk_group(tid, i, CPS), sg = n / NK, s = chunk_station(tid, CPS), s0 = 8 * (n % NK);
                     const int t = stream_tile(sg, k, NS, ip.tile_lo, ip.ntiles) * kTile, q = chunk_q(tid, CPS);
                     const uint32_t off = tile_off(ip.c, d.T, t, bytes);
                     if (off != ((uint64_t)ip.c * d.T + t) * bytes) return w.fail("the tile's offset wraps");
                     w.access("sample load", group_base(s0, stride) + off, tile_range(s0, d.S, stride, off),
-                             (uint64_t)(s & 7) * stride64 + 16u * q, chunk_off(s, q, stride), 16, xbuf, false);
+                             (uint64_t)s * stride64 + 16u * q, chunk_off(s, q, stride), 16, xbuf, false);
                 }
             for (int k = 0; k < nsteps; ++k) {
                 const int tile = ip.tile_lo + sigma + NS * k;

@@ -193,6 +193,7 @@ LBF_INLINE void item_f32_split(const BlockDesc& d, int item, int nbg, uint32_t* 
     u32x4 raw[CPT];
     auto load_chunks = [&](int k) { ld.load(k, raw); };
     auto store_chunk = [&](int k, int i) {
+        if (!ld.staged(i)) return;
         ld.store(at, k, i, raw);
         if constexpr (XT == XT_CI16) {
             // any component outside [-2048, 2047]: x + 2048 has one of its top four bits set

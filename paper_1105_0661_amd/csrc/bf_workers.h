@@ -295,62 +295,53 @@ struct TileLoader {
     static constexpr int BYTES = sample_bytes(XT);
     static constexpr int SPC = Chunk<XT, CT>::samples;     // samples per 16-byte chunk
     static constexpr int CPS = kTile / SPC;                // chunks per station per tile
-    static constexpr int SP = padded_stations(NK);
-    static constexpr int CPT = chunks_per_thread(NS, SP, CPS);
-    static constexpr int SPI = kLoaders / CPS;             // stations from one chunk of a thread to the next
-    static constexpr bool WIDE = SP * CPS >= kLoaders;     // a tile takes every thread: the stream depends on i only
-    static_assert(SPI % 8 == 0, "a thread's chunks share their place in the station group");
+    static constexpr int CPT = chunks_per_thread(NS, NK, CPS);
+    static constexpr bool EVEN = NS * NK * wave_loads(CPS) % kLoaderWaves == 0;   // every wave has CPT chunks to stage
 
     const void* x;
     uint32_t stride_bytes, voff;
-    int S, T, c, tile_lo, ntiles, sg0, s0;
-    int w0, w1;                                            // LDS words of chunk 0; of the stations 16 further (SPI = 16)
+    int S, T, c, tile_lo, ntiles;
+    int g[CPT], sg[CPT];                                   // station group and stream of the wave's chunks (uniform)
+    int row, swz;                                          // LDS words of the thread's place in a tile and a group
 
     LBF_INLINE void init(const BlockDesc& d, const ItemPos& ip) {
-        const int tid = threadIdx.x, q = chunk_q(tid, CPS), s = chunk_station(tid, 0, SP, CPS);
+        const int tid = threadIdx.x, q = chunk_q(tid, CPS), s = chunk_station(tid, CPS);
         x = d.x;
         S = d.S, T = d.T, c = ip.c, tile_lo = ip.tile_lo, ntiles = ip.ntiles;
         stride_bytes = (uint32_t)((size_t)d.C * T * BYTES);
-        sg0 = __builtin_amdgcn_readfirstlane(chunk_stream(tid, 0, SP, CPS));
-        s0 = __builtin_amdgcn_readfirstlane(s);            // first station of the wave's first chunk
-        // threads past the step's chunks load the tile of a later step, which
-        // warms the cache for it (without: 1500 channels of ci8, 30 stations,
-        // 200 beams 293 us instead of 279), and stage nothing
+        // waves past the step's chunks load the tile of a later step, which
+        // warms the cache for it, and stage nothing
+#pragma unroll
+        for (int i = 0; i < CPT; ++i) {
+            const int n = __builtin_amdgcn_readfirstlane(chunk_group(tid, i, CPS));
+            g[i] = n % NK;
+            sg[i] = n / NK;
+        }
         voff = chunk_off(s, q, stride_bytes);
-        const int so = WIDE ? 0 : sg0 * 2 * kATileWords;
-        w0 = so + a_word(q * SPC, 0, s);
-        w1 = SPI == 16 ? so + a_word(q * SPC, 0, s ^ 16) : w0;
-        __asm__ volatile("" : "+v"(w0), "+v"(w1));
+        row = 2 * q * SPC * kARow + (s & 3);
+        swz = 4 * ((s >> 2) ^ a_swz(q * SPC));
+        __asm__ volatile("" : "+v"(row), "+v"(swz));
     }
-    LBF_INLINE int stream(int i) const { return WIDE ? chunk_stream(0, i, SP, CPS) : sg0 + chunk_stream(0, i, SP, CPS); }
-    LBF_INLINE int first_station(int i) const { return s0 + (WIDE ? chunk_station(0, i, SP, CPS) : 0); }
+    LBF_INLINE int stream(int i) const { return sg[i]; }
 
     LBF_INLINE void load(int k, u32x4 (&dst)[CPT]) const {
 #pragma unroll
         for (int i = 0; i < CPT; ++i) {
-            const int g = first_station(i) & ~7;
-            const uint32_t off = tile_off(c, T, stream_tile(stream(i), k, NS, tile_lo, ntiles) * kTile, BYTES);
-            const uint64_t base = reinterpret_cast<uint64_t>(x) + group_base(g, stride_bytes) + off;
+            const uint32_t off = tile_off(c, T, stream_tile(sg[i], k, NS, tile_lo, ntiles) * kTile, BYTES);
+            const uint64_t base = reinterpret_cast<uint64_t>(x) + group_base(8 * g[i], stride_bytes) + off;
             const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)base);
             const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(base >> 32));
-            const uint32_t n = __builtin_amdgcn_readfirstlane(tile_range(g, S, stride_bytes, off));
+            const uint32_t n = __builtin_amdgcn_readfirstlane(tile_range(8 * g[i], S, stride_bytes, off));
             const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
                 reinterpret_cast<void*>(((uint64_t)hi << 32) | lo), (short)0, (int)n, 0x00020000);
             dst[i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)voff, 0, 0));
         }
     }
-    // chunk i holds a station of the K-steps (uniform): the padded ones are not staged
-    LBF_INLINE bool staged(int i) const {
-        if (NS * SP * CPS < kLoaders && sg0 >= NS) return false;
-        return SP == 8 * NK || first_station(i) < 8 * NK;
-    }
-    // LDS word of chunk i's first sample, polarisation X, in step k's buffer
+    LBF_INLINE bool staged(int i) const { return EVEN || sg[i] < NS; }            // uniform
+    // LDS word of chunk i's first sample, polarisation X, in step k's buffer:
+    // a_word of station 8 g + s (the group turns bits of the swizzled part)
     LBF_INLINE int word(int k, int i) const {
-        // stations SPI further on: 32 words on for 32 stations (the swizzle
-        // works on 32-station blocks), the other base for 16
-        const int ds = WIDE ? chunk_station(0, i, SP, CPS) : 0;
-        const int sg = chunk_stream(0, i, SP, CPS);        // beside the thread's own in w0
-        return (ds & 16 ? w1 : w0) + ((k & 1) + sg * 2) * kATileWords + (ds & ~31);
+        return (swz ^ (8 * g[i])) + (row + ((k & 1) + sg[i] * 2) * kATileWords);
     }
     LBF_INLINE void store(uint32_t* at, int k, int i, const u32x4 (&src)[CPT]) const {
         if (!staged(i)) return;
