@@ -30,7 +30,7 @@ namespace lbf {
 constexpr int kSegTiles = 24, kSegTilesMax = 192, kMinItems = 2048;
 constexpr int kSegTilesMin = 4, kComputeUnits = kXcds * kCusPerXcd;
 
-LBF_HD int seg_tiles(const BlockDesc& d, int nbg) {
+inline int seg_tiles(const BlockDesc& d, int nbg) {
     const int ntiles = (d.T + kTile - 1) / kTile;
     int seg = kSegTiles;
     while (seg > kSegTilesMin && (int64_t)d.nc * nbg * ((ntiles + seg - 1) / seg) < kComputeUnits) seg /= 2;   // 24, 12, 6, 3
@@ -48,21 +48,53 @@ LBF_HD int seg_tiles(const BlockDesc& d, int nbg) {
 constexpr uint32_t kNoAccess = 0x80000000u;
 
 // A work item of the fast workers: channel c (of [c0, c0 + nc)), beam group
-// bg, sample tiles [tile_lo, tile_lo + ntiles) (nbg beam groups).
+// bg of `per` beams (a power of two), sample tiles [tile_lo, tile_lo + ntiles).
 struct ItemPos {
     int c, bg, tile_lo, ntiles;
 };
 
-LBF_HD ItemPos item_pos(const BlockDesc& d, int item, int nbg) {
-    const int ntiles_all = (d.T + kTile - 1) / kTile;
-    const int seg = seg_tiles(d, nbg);
-    const int nseg = (ntiles_all + seg - 1) / seg;
+// How a launch's items are numbered, chosen once on the host: the work groups
+// take a number apart with multiplications.  Their prologue is a chain of
+// scalar instructions that nothing overlaps in an item of one or two steps;
+// the segment rule and four divisions in it cost 16384 channels of ci8, 19
+// stations, 64 samples, 3 beams 15 us of 226.
+struct ItemGrid {
+    uint32_t nseg;                 // segments of the block's samples
+    uint32_t mseg, mbg;            // n / nseg = n mseg >> (31 + shift) for n < 2^31, n / beam groups likewise
+    uint8_t seg, sseg, sbg, pad;   // tiles per segment, the shifts
+};
+
+// m, s with n / d = n m >> (31 + s) for every n < 2^31: m = floor(2^(31 + s) /
+// d) + 1 with 2^s >= d fits 32 bits and is too large by at most d / 2^(31 + s)
+// of itself, less than 1 / n
+inline uint32_t div_magic(uint32_t d, uint8_t* s) {
+    *s = 0;
+    while ((1ull << *s) < d) ++*s;
+    return (uint32_t)((1ull << (31 + *s)) / d) + 1u;
+}
+LBF_HD uint32_t div_by(uint32_t n, uint32_t m, uint32_t s) { return (uint32_t)(((uint64_t)n * m) >> (31 + s)); }
+
+// The items of a block part; returns their number
+inline int item_grid(const BlockDesc& d, int per, ItemGrid* g) {
+    const int nbg = (d.b1 - d.b0 + per - 1) / per, seg = seg_tiles(d, nbg);
+    const int ntiles = (d.T + kTile - 1) / kTile, nseg = (ntiles + seg - 1) / seg;
+    g->nseg = (uint32_t)nseg;
+    g->seg = (uint8_t)seg;
+    g->mseg = div_magic((uint32_t)nseg, &g->sseg);
+    g->mbg = div_magic((uint32_t)nbg, &g->sbg);
+    g->pad = 0;
+    return d.nc * nbg * nseg;
+}
+
+LBF_HD ItemPos item_pos(const BlockDesc& d, const ItemGrid& g, int item, int per) {
+    const uint32_t nbg = (uint32_t)(d.b1 - d.b0 + per - 1) / (uint32_t)per;
+    const uint32_t cb = div_by((uint32_t)item, g.mseg, g.sseg), c = div_by(cb, g.mbg, g.sbg);
     ItemPos p;
-    p.c = d.c0 + item / nseg / nbg;
-    p.bg = item / nseg % nbg;
-    p.tile_lo = item % nseg * seg;
-    const int left = ntiles_all - p.tile_lo;
-    p.ntiles = left < seg ? left : seg;
+    p.c = d.c0 + (int)c;
+    p.bg = (int)(cb - c * nbg);
+    p.tile_lo = (int)(((uint32_t)item - cb * g.nseg) * g.seg);
+    const int left = (int)((uint32_t)(d.T + kTile - 1) / kTile) - p.tile_lo;
+    p.ntiles = left < g.seg ? left : g.seg;
     return p;
 }
 
@@ -74,9 +106,8 @@ LBF_HD ItemPos item_pos(const BlockDesc& d, int item, int nbg) {
 LBF_HD uint64_t group_base(int s0, uint32_t stride_bytes) { return (uint64_t)s0 * stride_bytes; }
 
 LBF_HD uint32_t group_range(int s0, int S, uint32_t stride_bytes) {
-    int n = S - s0;
-    n = n < 0 ? 0 : (n > 8 ? 8 : n);
-    return (uint32_t)n * stride_bytes;
+    const int n = S - s0;                                  // (selects, not a clamp: scalar instructions)
+    return n >= 8 ? 8u * stride_bytes : n <= 0 ? 0u : (uint32_t)n * stride_bytes;
 }
 
 // station s0 + i of a group, channel c, sample t
@@ -118,14 +149,14 @@ LBF_HD constexpr int chunks_per_thread(int ns, int nk, int cps) {
     return (ns * nk * wave_loads(cps) + kLoaderWaves - 1) / kLoaderWaves;
 }
 // number of the wave's load i among the groups of the step's tiles: group n % nk of stream n / nk
-LBF_HD constexpr int chunk_group(int tid, int i, int cps) {
-    return tid / kWave / wave_loads(cps) + kLoaderWaves / wave_loads(cps) * i;
+LBF_HD constexpr uint32_t chunk_group(uint32_t wave, uint32_t i, uint32_t cps) {
+    return wave / (cps / 8) + kLoaderWaves / (cps / 8) * i;
 }
-// station within the group
-LBF_HD constexpr int chunk_station(int tid, int cps) {
-    return tid / kWave % wave_loads(cps) * (kWave / cps) + tid % kWave / cps;
+// station within the group, chunk of the station
+LBF_HD constexpr uint32_t chunk_station(uint32_t wave, uint32_t lane, uint32_t cps) {
+    return wave % (cps / 8) * (kWave / cps) + lane / cps;
 }
-LBF_HD constexpr int chunk_q(int tid, int cps) { return tid % cps; }
+LBF_HD constexpr uint32_t chunk_q(uint32_t lane, uint32_t cps) { return lane % cps; }
 // bytes of a thread's offset into the descriptor: station of the group, chunk of the tile
 LBF_HD uint32_t chunk_off(int s, int q, uint32_t stride_bytes) { return (uint32_t)s * stride_bytes + 16u * (uint32_t)q; }
 // the stream's tile of step k, or the item's last tile once it has run out

@@ -105,6 +105,17 @@ void stores_of_tile(Walk& w, const BlockDesc& d, int c, int beam, int bend, int 
     }
 }
 
+// item_pos, its divisions by multiplication checked against plain ones
+ItemPos checked_pos(Walk& w, const BlockDesc& d, const ItemGrid& grid, int item, int per) {
+    const ItemPos p = item_pos(d, grid, item, per);
+    const int ntiles = (d.T + kTile - 1) / kTile, nbg = (d.b1 - d.b0 + per - 1) / per, seg = seg_tiles(d, nbg);
+    const int nseg = (ntiles + seg - 1) / seg;
+    if (p.c != d.c0 + item / nseg / nbg || p.bg != item / nseg % nbg || p.tile_lo != item % nseg * seg ||
+        p.ntiles != std::min(seg, ntiles - p.tile_lo))
+        w.fail("item %d's place in the block", item);
+    return p;
+}
+
 // items [lo, hi) of the FP16/BF16 worker
 void walk_h(Walk& w, const BlockDesc& d, int lo, int hi) {
     const int bytes = sample_bytes(d.xtype);
@@ -114,10 +125,10 @@ void walk_h(Walk& w, const BlockDesc& d, int lo, int hi) {
     if (stride != stride64) return w.fail("station stride does not fit 32 bits");
     const int NS = fast_h_streams(d), NK = fast_h_ksteps(d.S), NBT = 8 / NS;
     const int CPS = kTile * bytes / 16, CPT = chunks_per_thread(NS, NK, CPS);
-    int nbg;
-    const int items = block_items_fast_h(d, &nbg);
+    ItemGrid grid;
+    const int items = block_items_fast_h(d, &grid);
     for (int item = lo; item < std::min(hi, items) && !w.bad; ++item) {
-        const ItemPos ip = item_pos(d, item, nbg);
+        const ItemPos ip = checked_pos(w, d, grid, item, NBT * kTile);
         const int nsteps = (ip.ntiles + NS - 1) / NS;
         for (int tid = 0; tid < kThreadsH; ++tid) {
             const int lane = tid & 63, wave = tid / 64, r = lane & 31, h = lane >> 5;
@@ -133,12 +144,15 @@ void walk_h(Walk& w, const BlockDesc& d, int lo, int hi) {
                 for (int j = 0; j < NBT * kTile / 32; ++j)
                     weights(d.b0 + ip.bg * NBT * kTile + h_weight_row(tid, j), h_weight_station(tid));
             else
-                for (int kk = 0; kk < NK; ++kk) weights(beam, 8 * kk + 4 * h);
+                for (int kk = 0; kk < NK; ++kk)
+                    w.access("weight load", weight_base(d, ip.c, 4), weight_range(d, 4),
+                             ((uint64_t)beam * d.S + 8 * kk + 4 * h) * 4u, weight_off(beam, d.S, 8 * kk + 4 * h, 4), 16, wbuf,
+                             false);
             // the loaders run up to two steps ahead of the last one
             for (int k = 0; k < nsteps + 2; ++k)
                 for (int i = 0; i < CPT; ++i) {
-                    const int n = chunk_group(tid, i, CPS), sg = n / NK, s = chunk_station(tid, CPS), s0 = 8 * (n % NK);
-                    const int t = stream_tile(sg, k, NS, ip.tile_lo, ip.ntiles) * kTile, q = chunk_q(tid, CPS);
+                    const int n = chunk_group(wave, i, CPS), sg = n / NK, s = chunk_station(wave, lane, CPS), s0 = 8 * (n % NK);
+                    const int t = stream_tile(sg, k, NS, ip.tile_lo, ip.ntiles) * kTile, q = chunk_q(lane, CPS);
                     const uint32_t off = tile_off(ip.c, d.T, t, bytes);
                     if (off != ((uint64_t)ip.c * d.T + t) * bytes) return w.fail("the tile's offset wraps");
                     w.access("sample load", group_base(s0, stride) + off, tile_range(s0, d.S, stride, off),
@@ -162,10 +176,10 @@ void walk_split(Walk& w, const BlockDesc& d, int lo, int hi) {
     if (stride != stride64) return w.fail("station stride does not fit 32 bits");
     const int NS = split_streams(d), NK = split_ksteps(d.S), NBT = 8 / NS;
     const int CPS = kTile * bytes / 16, CPT = chunks_per_thread(NS, NK, CPS);
-    int nbg;
-    const int items = block_items_split(d, &nbg);
+    ItemGrid grid;
+    const int items = block_items_split(d, &grid);
     for (int item = lo; item < std::min(hi, items) && !w.bad; ++item) {
-        const ItemPos ip = item_pos(d, item, nbg);
+        const ItemPos ip = checked_pos(w, d, grid, item, NBT * kTile);
         const int nsteps = (ip.ntiles + NS - 1) / NS;
         for (int tid = 0; tid < kThreadsH; ++tid) {
             const int lane = tid & 63, wave = tid / 64, r = lane & 31, h = lane >> 5, trow = tile_row_sample(r);
@@ -183,8 +197,8 @@ void walk_split(Walk& w, const BlockDesc& d, int lo, int hi) {
             // the loaders run up to two steps ahead of the last one
             for (int k = 0; k < nsteps + 2; ++k)
                 for (int i = 0; i < CPT; ++i) {
-                    const int n = chunk_group(tid, i, CPS), sg = n / NK, s = chunk_station(tid, CPS), s0 = 8 * (n % NK);
-                    const int t = stream_tile(sg, k, NS, ip.tile_lo, ip.ntiles) * kTile, q = chunk_q(tid, CPS);
+                    const int n = chunk_group(wave, i, CPS), sg = n / NK, s = chunk_station(wave, lane, CPS), s0 = 8 * (n % NK);
+                    const int t = stream_tile(sg, k, NS, ip.tile_lo, ip.ntiles) * kTile, q = chunk_q(lane, CPS);
                     const uint32_t off = tile_off(ip.c, d.T, t, bytes);
                     if (off != ((uint64_t)ip.c * d.T + t) * bytes) return w.fail("the tile's offset wraps");
                     w.access("sample load", group_base(s0, stride) + off, tile_range(s0, d.S, stride, off),
@@ -211,10 +225,10 @@ void walk_f32(Walk& w, const BlockDesc& d, int lo, int hi) {
     const uint32_t stride = (uint32_t)stride64;
     if (stride != stride64) return w.fail("station stride does not fit 32 bits");
     const int ngrp = std::min(8, ((d.S + 7) / 8 + 1) & ~1);
-    int nbg;
-    const int items = block_items_fast_f32(d, &nbg);
+    ItemGrid grid;
+    const int items = block_items_fast_f32(d, &grid);
     for (int item = lo; item < std::min(hi, items) && !w.bad; ++item) {
-        const ItemPos ip = item_pos(d, item, nbg);
+        const ItemPos ip = checked_pos(w, d, grid, item, kBeamGroup);
         const int b0 = ip.bg * kBeamGroup;
         for (int tid = 0; tid < kThreadsH; ++tid) {        // weight planes: beam b0 + tid/64 + 8k, station tid % 64
             for (int k = 0; k < kStationChunk * kBeamGroup / kThreadsH; ++k) {
@@ -258,10 +272,10 @@ bool check_fast_addressing(const BlockDesc& d, int threads, uint64_t* accesses, 
     part[0] = d;
     if (d.ctype != CT_F32) np = split_fast_h(d, part);
     for (int p = 0; p < np; ++p) {
-        int nbg;
-        items[p] = d.ctype != CT_F32    ? block_items_fast_h(part[p], &nbg)
-                   : d.xtype != XT_CF32 ? block_items_split(part[p], &nbg)
-                                        : block_items_fast_f32(part[p], &nbg);
+        ItemGrid grid;
+        items[p] = d.ctype != CT_F32    ? block_items_fast_h(part[p], &grid)
+                   : d.xtype != XT_CF32 ? block_items_split(part[p], &grid)
+                                        : block_items_fast_f32(part[p], &grid);
     }
     threads = std::max(1, std::min(threads, 64));
     std::vector<Walk> w(threads * np);

@@ -58,9 +58,7 @@ static hipError_t run_batch_group(const BlockDesc* blks, const int* idx, int n, 
         a.blk[j].out = stage[entry_src[j]];
         a.blk[j].order = 1;
         a.blk[j].ld_row = staging_ld(a.blk[j].B, a.blk[j].product == PR_IQUV ? 4 : 1);
-        int nbg;
-        const int items = block_items_fast_h(a.blk[j], &nbg);
-        a.nbg[j] = nbg;
+        const int items = block_items_fast_h(a.blk[j], &a.grid[j]);
         a.item_start[j + 1] = a.item_start[j] + items;
     }
     // one launch per variant present, in variant order, on the same stream,
@@ -76,7 +74,7 @@ static hipError_t run_batch_group(const BlockDesc* blks, const int* idx, int n, 
         for (int j = 0; j < a.n; ++j) {
             if (batch_variant(a.blk[j]) != v) continue;
             g.blk[g.n] = a.blk[j];
-            g.nbg[g.n] = a.nbg[j];
+            g.grid[g.n] = a.grid[j];
             g.item_start[g.n + 1] = g.item_start[g.n] + (a.item_start[j + 1] - a.item_start[j]);
             g.n++;
         }

@@ -9,7 +9,7 @@ namespace lbf {
 struct BatchArgs {
     BlockDesc blk[kMaxBatch];
     int item_start[kMaxBatch + 1];   // prefix sums of items per block
-    int nbg[kMaxBatch];
+    ItemGrid grid[kMaxBatch];
     int n;
 };
 static_assert(sizeof(BatchArgs) <= 4096, "kernel argument block");
@@ -32,7 +32,7 @@ __global__ __launch_bounds__(kThreadsH) void bf_batch_kernel(BatchArgs a, int* c
         if (it >= total) break;     // every work group leaves once the list is exhausted
         int j = 0;
         while (j + 1 < a.n && a.item_start[j + 1] <= it) ++j;
-        item_h_fast<XT, CT, PR, 16, NK, NS>(a.blk[j], it - a.item_start[j], a.nbg[j], at);
+        item_h_fast<XT, CT, PR, 16, NK, NS>(a.blk[j], it - a.item_start[j], a.grid[j], at);
     }
 }
 

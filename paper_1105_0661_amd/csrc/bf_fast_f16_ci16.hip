@@ -2,7 +2,7 @@
 #include "bf_fast_impl.h"
 
 namespace lbf {
-hipError_t launch_f16_ci16(const BlockDesc& d, int nbg, int n, hipStream_t st) {
-    return launch_h_xt<XT_CI16, CT_F16>(d, nbg, n, st);
+hipError_t launch_f16_ci16(const BlockDesc& d, const ItemGrid& grid, int n, hipStream_t st) {
+    return launch_h_xt<XT_CI16, CT_F16>(d, grid, n, st);
 }
 }  // namespace lbf

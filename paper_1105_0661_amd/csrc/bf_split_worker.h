@@ -72,11 +72,8 @@ inline int split_streams(const BlockDesc& d) {
 }
 
 // Work items: (channel of [c0, c0 + nc), group of 256/NS beams, segment)
-inline int block_items_split(const BlockDesc& d, int* nbg) {
-    const int per = 8 / split_streams(d) * kTile;
-    *nbg = (d.b1 - d.b0 + per - 1) / per;
-    const int ntiles = (d.T + kTile - 1) / kTile, seg = seg_tiles(d, *nbg);
-    return d.nc * *nbg * ((ntiles + seg - 1) / seg);
+inline int block_items_split(const BlockDesc& d, ItemGrid* grid) {
+    return item_grid(d, 8 / split_streams(d) * kTile, grid);
 }
 
 // Smallest ratio of a beam's station weights (larger component of each) to
@@ -165,7 +162,7 @@ LBF_INLINE void split_epilogue(const floatx16 (&acc)[4], __amdgpu_buffer_rsrc_t 
 // vbuf: kVoltWords floats per wave for voltages in two streams (four leave no
 // room)
 template <int XT, int PR, int NK, int NS>
-LBF_INLINE void item_f32_split(const BlockDesc& d, int item, int nbg, uint32_t* at, int* flags, float* vbuf) {
+LBF_INLINE void item_f32_split(const BlockDesc& d, int item, const ItemGrid& grid, uint32_t* at, int* flags, float* vbuf) {
     typedef MfmaH<CT_F16> M;
     typedef M::vec V;
     typedef float float2v __attribute__((ext_vector_type(2)));
@@ -174,7 +171,7 @@ LBF_INLINE void item_f32_split(const BlockDesc& d, int item, int nbg, uint32_t* 
     typedef TileLoader<XT, CT_F16, NK, NS> Loader;
     constexpr int CPT = Loader::CPT;                       // chunks per thread per step
     const int T = d.T, S = d.S;
-    const ItemPos ip = item_pos(d, item, nbg);
+    const ItemPos ip = item_pos(d, grid, item, NBT * kTile);
     const int c = ip.c, bg = ip.bg, tile_lo = ip.tile_lo, ntiles = ip.ntiles;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
     const int r = lane & 31, h = lane >> 5;
@@ -467,46 +464,46 @@ LBF_INLINE void item_f32_split(const BlockDesc& d, int item, int nbg, uint32_t* 
 
 // 8 waves, two per SIMD; LDS: NS streams x 2 buffers of one A tile
 template <int XT, int PR, int NK, int NS>
-__global__ __launch_bounds__(kThreadsH) void bf_f32_split_kernel(BlockDesc d, int nbg, int nitems) {
+__global__ __launch_bounds__(kThreadsH) void bf_f32_split_kernel(BlockDesc d, ItemGrid grid, int nitems) {
     __shared__ __attribute__((aligned(16))) uint32_t at[NS * 2 * kATileWords];
     __shared__ __attribute__((aligned(16))) int flags[2 * NS + 1];
     constexpr bool rows = PR == PR_VOLT && NS <= 2;
     __shared__ __attribute__((aligned(16))) float vbuf[rows ? 8 * kVoltWords : 1];
-    item_f32_split<XT, PR, NK, NS>(d, xcd_remap(blockIdx.x, nitems), nbg, at, flags, vbuf);
+    item_f32_split<XT, PR, NK, NS>(d, xcd_remap(blockIdx.x, nitems), grid, at, flags, vbuf);
 }
 
 template <int XT, int PR, int NK>
-inline void launch_split_nk(const BlockDesc& d, int ns, int nbg, int n, hipStream_t st) {
+inline void launch_split_nk(const BlockDesc& d, int ns, const ItemGrid& grid, int n, hipStream_t st) {
     const dim3 g(n), b(kThreadsH);
     if constexpr (XT == XT_CI8 || (XT == XT_CI16 && NK < 6)) {
         if (ns == 4) {
-            hipLaunchKernelGGL((bf_f32_split_kernel<XT, PR, NK, 4>), g, b, 0, st, d, nbg, n);
+            hipLaunchKernelGGL((bf_f32_split_kernel<XT, PR, NK, 4>), g, b, 0, st, d, grid, n);
             return;
         }
     }
-    hipLaunchKernelGGL((bf_f32_split_kernel<XT, PR, NK, 2>), g, b, 0, st, d, nbg, n);
+    hipLaunchKernelGGL((bf_f32_split_kernel<XT, PR, NK, 2>), g, b, 0, st, d, grid, n);
 }
 
 template <int XT, int PR>
-inline void launch_split_pr(const BlockDesc& d, int nbg, int n, hipStream_t st) {
+inline void launch_split_pr(const BlockDesc& d, const ItemGrid& grid, int n, hipStream_t st) {
     const int ns = split_streams(d);
     switch (split_ksteps(d.S)) {
-        case 2: launch_split_nk<XT, PR, 2>(d, ns, nbg, n, st); break;
-        case 4: launch_split_nk<XT, PR, 4>(d, ns, nbg, n, st); break;
-        case 5: launch_split_nk<XT, PR, 5>(d, ns, nbg, n, st); break;
-        case 6: launch_split_nk<XT, PR, 6>(d, ns, nbg, n, st); break;
-        case 7: launch_split_nk<XT, PR, 7>(d, ns, nbg, n, st); break;
-        default: launch_split_nk<XT, PR, 8>(d, ns, nbg, n, st); break;
+        case 2: launch_split_nk<XT, PR, 2>(d, ns, grid, n, st); break;
+        case 4: launch_split_nk<XT, PR, 4>(d, ns, grid, n, st); break;
+        case 5: launch_split_nk<XT, PR, 5>(d, ns, grid, n, st); break;
+        case 6: launch_split_nk<XT, PR, 6>(d, ns, grid, n, st); break;
+        case 7: launch_split_nk<XT, PR, 7>(d, ns, grid, n, st); break;
+        default: launch_split_nk<XT, PR, 8>(d, ns, grid, n, st); break;
     }
 }
 
 template <int XT>
 inline hipError_t launch_split_xt(const BlockDesc& d, hipStream_t st) {
-    int nbg;
-    const int n = block_items_split(d, &nbg);
-    if (d.product == PR_VOLT) launch_split_pr<XT, PR_VOLT>(d, nbg, n, st);
-    else if (d.product == PR_I) launch_split_pr<XT, PR_I>(d, nbg, n, st);
-    else launch_split_pr<XT, PR_IQUV>(d, nbg, n, st);
+    ItemGrid grid;
+    const int n = block_items_split(d, &grid);
+    if (d.product == PR_VOLT) launch_split_pr<XT, PR_VOLT>(d, grid, n, st);
+    else if (d.product == PR_I) launch_split_pr<XT, PR_I>(d, grid, n, st);
+    else launch_split_pr<XT, PR_IQUV>(d, grid, n, st);
     return hipGetLastError();
 }
 

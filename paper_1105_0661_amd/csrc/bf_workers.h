@@ -60,13 +60,13 @@ LBF_INLINE void stage_weights_f32_planes(float* pl, const BlockDesc& d, int c, i
 }
 
 template <int XT, int PR, int TI>
-LBF_INLINE void item_f32_fast(const BlockDesc& d, int item, int nbg, float* pl) {
+LBF_INLINE void item_f32_fast(const BlockDesc& d, int item, const ItemGrid& grid, float* pl) {
     typedef Raw<XT> R;
     typedef typename R::type RT;
     constexpr int BYTES = sizeof(RT);
     constexpr int NOUT = PR == PR_VOLT ? 1 : 16 / TI;
     const int T = d.T, S = d.S, B = d.B;
-    const ItemPos ip = item_pos(d, item, nbg);
+    const ItemPos ip = item_pos(d, grid, item, kBeamGroup);
     const int c = ip.c, bg = ip.bg, tile_lo = ip.tile_lo, ntiles = ip.ntiles;
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
     const int r = lane & 31, h = lane >> 5;
@@ -305,7 +305,8 @@ struct TileLoader {
     int row, swz;                                          // LDS words of the thread's place in a tile and a group
 
     LBF_INLINE void init(const BlockDesc& d, const ItemPos& ip) {
-        const int tid = threadIdx.x, q = chunk_q(tid, CPS), s = chunk_station(tid, CPS);
+        const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave;
+        const uint32_t q = chunk_q(lane, CPS), s = chunk_station(wave, lane, CPS);
         x = d.x;
         S = d.S, T = d.T, c = ip.c, tile_lo = ip.tile_lo, ntiles = ip.ntiles;
         stride_bytes = (uint32_t)((size_t)d.C * T * BYTES);
@@ -313,13 +314,13 @@ struct TileLoader {
         // warms the cache for it, and stage nothing
 #pragma unroll
         for (int i = 0; i < CPT; ++i) {
-            const int n = __builtin_amdgcn_readfirstlane(chunk_group(tid, i, CPS));
+            const uint32_t n = chunk_group(wave, i, CPS);
             g[i] = n % NK;
             sg[i] = n / NK;
         }
         voff = chunk_off(s, q, stride_bytes);
-        row = 2 * q * SPC * kARow + (s & 3);
-        swz = 4 * ((s >> 2) ^ a_swz(q * SPC));
+        row = (int)(2 * q * SPC * kARow + (s & 3));
+        swz = 4 * ((int)(s >> 2) ^ a_swz((int)(q * SPC)));
         __asm__ volatile("" : "+v"(row), "+v"(swz));
     }
     LBF_INLINE int stream(int i) const { return sg[i]; }
@@ -377,14 +378,14 @@ constexpr int kIncLdsFloats = 2 * 8 * kTile * 4;
 // after the step's barrier, which then integrates t_int consecutive samples
 // in an xor butterfly and stores I (Q, U, V) into inc [K][T'][C].
 template <int XT, int CT, int PR, int TI, int NK, int NS, bool INC = false>
-LBF_INLINE void item_h_fast(const BlockDesc& d, int item, int nbg, uint32_t* at) {
+LBF_INLINE void item_h_fast(const BlockDesc& d, int item, const ItemGrid& grid, uint32_t* at) {
     typedef typename MfmaH<CT>::vec V;
     constexpr int NBT = 8 / NS;                            // beam tiles per item
     typedef TileLoader<XT, CT, NK, NS> Loader;
     constexpr int CPT = Loader::CPT;                       // chunks per thread per step
     // item = (channel, beam group, segment of sample tiles: seg_tiles)
     const int T = d.T;
-    const ItemPos ip = item_pos(d, item, nbg);             // tiles [tile_lo, tile_lo + ntiles)
+    const ItemPos ip = item_pos(d, grid, item, NBT * kTile);   // tiles [tile_lo, tile_lo + ntiles)
     const int c = ip.c, bg = ip.bg, tile_lo = ip.tile_lo, ntiles = ip.ntiles;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
     const int r = lane & 31, h = lane >> 5;
@@ -450,8 +451,19 @@ LBF_INLINE void item_h_fast(const BlockDesc& d, int item, int nbg, uint32_t* at)
                 take(kk, *reinterpret_cast<const u32x4*>(at + (bt * kTile + r) * WROW + 8 * kk + 4 * h));
             __syncthreads();                               // the weights' LDS becomes the tiles'
         } else {
+            u32x4 w[NK];
 #pragma unroll
-            for (int kk = 0; kk < NK; ++kk) take(kk, load_row(beam, 8 * kk + 4 * h));
+            for (int kk = 0; kk < NK; ++kk)                // (a beam past the channel's is out of range: zeros)
+                w[kk] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                    rs, (int)weight_off(beam, S, 8 * kk + 4 * h, 4), 0, 0));
+#pragma unroll
+            for (int kk = 0; kk < NK; ++kk) {
+                if (8 * kk + 8 > S) {                      // uniform: the last group, padded ones
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) w[kk][i] = 8 * kk + 4 * h + i < S ? w[kk][i] : 0u;
+                }
+                take(kk, w[kk]);
+            }
         }
     }
 

@@ -113,12 +113,11 @@ __host__ __device__ inline int tile_row_sample(int r) {
 // Block index remap so that the blocks resident at the same time on one XCD
 // (blocks are dispatched round-robin over the 8 XCDs) work on adjacent items:
 // their beam-major stores then land in the same cache lines of that XCD's L2.
-__device__ inline int xcd_remap(int i, int n) {
-    constexpr int R = kXcds * kCusPerXcd;
-    const int full = (n / R) * R;
-    if (i >= full) return i;
-    const int round = i / R, j = i % R;
-    return round * R + (j % kXcds) * kCusPerXcd + j / kXcds;
+__device__ inline int xcd_remap(uint32_t i, uint32_t n) {
+    constexpr uint32_t R = kXcds * kCusPerXcd;
+    if (i >= n / R * R) return (int)i;
+    const uint32_t j = i % R;
+    return (int)(i - j + j % kXcds * kCusPerXcd + j / kXcds);
 }
 
 }  // namespace lbf

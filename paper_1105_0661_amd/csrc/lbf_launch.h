@@ -7,6 +7,8 @@
 
 namespace lbf {
 
+struct ItemGrid;
+
 constexpr int kMaxBatch = 32;   // equals LBF_MAX_BATCH in include/lbf.h
 constexpr int kBatchCounters = 64;   // work counters of one batch call: one per kernel variant
 
@@ -55,13 +57,13 @@ hipError_t launch_split_ci8(const BlockDesc& d, hipStream_t st);    // FP32 spli
 hipError_t launch_split_ci16(const BlockDesc& d, hipStream_t st);
 hipError_t launch_fast_f16(const BlockDesc& d, hipStream_t st);
 hipError_t launch_fast_bf16(const BlockDesc& d, hipStream_t st);
-// FP16/BF16 fast kernels of one block part (n work items, nbg beam groups) by sample type
-hipError_t launch_f16_ci8(const BlockDesc& d, int nbg, int n, hipStream_t st);
-hipError_t launch_f16_ci16(const BlockDesc& d, int nbg, int n, hipStream_t st);
-hipError_t launch_f16_cf32(const BlockDesc& d, int nbg, int n, hipStream_t st);
-hipError_t launch_bf16_ci8(const BlockDesc& d, int nbg, int n, hipStream_t st);
-hipError_t launch_bf16_ci16(const BlockDesc& d, int nbg, int n, hipStream_t st);
-hipError_t launch_bf16_cf32(const BlockDesc& d, int nbg, int n, hipStream_t st);
+// FP16/BF16 fast kernels of one block part (n work items) by sample type
+hipError_t launch_f16_ci8(const BlockDesc& d, const ItemGrid& grid, int n, hipStream_t st);
+hipError_t launch_f16_ci16(const BlockDesc& d, const ItemGrid& grid, int n, hipStream_t st);
+hipError_t launch_f16_cf32(const BlockDesc& d, const ItemGrid& grid, int n, hipStream_t st);
+hipError_t launch_bf16_ci8(const BlockDesc& d, const ItemGrid& grid, int n, hipStream_t st);
+hipError_t launch_bf16_ci16(const BlockDesc& d, const ItemGrid& grid, int n, hipStream_t st);
+hipError_t launch_bf16_cf32(const BlockDesc& d, const ItemGrid& grid, int n, hipStream_t st);
 // stage == nullptr: staging from the stream-ordered pool; else block j has
 // cap[j] bytes of caller staging at stage[j] (blocks whose staging holds all
 // their channels share the persistent launches, the others run alone in
