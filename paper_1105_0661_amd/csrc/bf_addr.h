@@ -165,9 +165,10 @@ LBF_HD int stream_tile(int sg, int k, int ns, int tile_lo, int ntiles) {
     return tile_lo + (i < ntiles - 1 ? i : ntiles - 1);
 }
 
-// The FP16/BF16 worker's weight rows on their way into LDS, in items of at
-// least kRowSteps steps: 16 lanes to a
+// The FP16/BF16 worker's weight rows on their way into LDS, where nk and the
+// streams ask for them, in items of at least kRowSteps steps: 16 lanes to a
 // beam's row, 4 stations each; pass j is 32 beams further
+LBF_HD constexpr bool h_weight_rows(int nk, int ns) { return nk == 8 && ns <= 2; }
 constexpr int kRowSteps = 8;
 LBF_HD constexpr int h_weight_row(int tid, int j) { return tid / 16 + 32 * j; }
 LBF_HD constexpr int h_weight_station(int tid) { return tid % 16 * 4; }

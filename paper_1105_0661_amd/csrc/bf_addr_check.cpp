@@ -140,7 +140,7 @@ void walk_h(Walk& w, const BlockDesc& d, int lo, int hi) {
                          ok ? ((uint64_t)bw * d.S + s4) * 4u : kNoAccess, ok ? weight_off(bw, d.S, s4, 4) : kNoAccess, 16,
                          wbuf, false);
             };
-            if (nsteps >= kRowSteps)
+            if (h_weight_rows(NK, NS) && nsteps >= kRowSteps)
                 for (int j = 0; j < NBT * kTile / 32; ++j)
                     weights(d.b0 + ip.bg * NBT * kTile + h_weight_row(tid, j), h_weight_station(tid));
             else

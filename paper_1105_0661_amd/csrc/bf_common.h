@@ -486,12 +486,12 @@ LBF_INLINE __amdgpu_buffer_rsrc_t stokes_rsrc(const BlockDesc& d, int c, int PR,
 
 // The Stokes parameters of one (t', beam): one 16-byte store for IQUV into
 // the channel-major s[t'][b][k] of its channel (rows of ld_row floats per
-// t'), or one 4-byte store per parameter into the final order.
-template <int PR>
+// t'), or (FINAL) one 4-byte store per parameter into the final order.
+template <int PR, bool FINAL>
 LBF_INLINE void stokes_store_row(const float (&v)[4], __amdgpu_buffer_rsrc_t rs, const BlockDesc& d, int c, int T2, int tq,
                                  int beam, bool ok) {
     constexpr int K = PR == PR_IQUV ? 4 : 1;
-    if (d.order == 0) {                                        // uniform
+    if constexpr (FINAL) {
         const uint32_t off = store_off(ok, stokes_off_final(d, c, T2, tq, beam, K)), pl = stokes_plane(d, T2);
 #pragma unroll
         for (int k = 0; k < K; ++k)
@@ -511,8 +511,8 @@ LBF_INLINE void stokes_store_row(const float (&v)[4], __amdgpu_buffer_rsrc_t rs,
 }
 
 // Stokes of one 32x32 tile
-template <int PR, int TI>
-LBF_INLINE void stokes_store_cm(const floatx16 (&acc)[4], __amdgpu_buffer_rsrc_t rs, const BlockDesc& d, int c, int T2,
+template <int PR, int TI, bool FINAL>
+LBF_INLINE void stokes_store_tile(const floatx16 (&acc)[4], __amdgpu_buffer_rsrc_t rs, const BlockDesc& d, int c, int T2,
                                 int beam, int t0, int h, bool ok) {
     constexpr int NOUT = 16 / TI;
     const int tq0 = (t0 + 16 * h) / TI;
@@ -522,7 +522,7 @@ LBF_INLINE void stokes_store_cm(const floatx16 (&acc)[4], __amdgpu_buffer_rsrc_t
         stokes_sums<PR, TI>(acc, o * TI, sm);
         stokes_from_sums<PR>(sm, v);
         const int tq = tq0 + o;
-        stokes_store_row<PR>(v, rs, d, c, T2, tq, beam, ok && tq < T2);
+        stokes_store_row<PR, FINAL>(v, rs, d, c, T2, tq, beam, ok && tq < T2);
     }
 }
 

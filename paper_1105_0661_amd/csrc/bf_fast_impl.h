@@ -7,10 +7,10 @@
 namespace lbf {
 
 // 8 waves, two per SIMD; LDS: the three weight planes of 128 beams
-template <int XT, int PR, int TI>
+template <int XT, int PR, int TI, bool FINAL>
 __global__ __launch_bounds__(kThreadsH) void bf_f32_fast_kernel(BlockDesc d, ItemGrid grid, int nitems) {
     __shared__ __attribute__((aligned(16))) float pl[3 * kPlaneWords];
-    item_f32_fast<XT, PR, TI>(d, xcd_remap(blockIdx.x, nitems), grid, pl);
+    item_f32_fast<XT, PR, TI, FINAL>(d, xcd_remap(blockIdx.x, nitems), grid, pl);
 }
 
 // 8 waves, two per SIMD; LDS: NS streams x 2 buffers of one A tile (and the
@@ -25,7 +25,13 @@ __global__ __launch_bounds__(kThreadsH) void bf_h_fast_kernel(BlockDesc d, ItemG
 // launch one instantiation; PR/TI/NK chosen from the block by the callers
 template <int XT, int PR, int TI>
 inline hipError_t launch_f32_k(const BlockDesc& d, const ItemGrid& grid, int n, hipStream_t st) {
-    hipLaunchKernelGGL((bf_f32_fast_kernel<XT, PR, TI>), dim3(n), dim3(kThreadsH), 0, st, d, grid, n);
+    if constexpr (PR != PR_VOLT) {
+        if (d.order == 0) {
+            hipLaunchKernelGGL((bf_f32_fast_kernel<XT, PR, TI, true>), dim3(n), dim3(kThreadsH), 0, st, d, grid, n);
+            return hipGetLastError();
+        }
+    }
+    hipLaunchKernelGGL((bf_f32_fast_kernel<XT, PR, TI, false>), dim3(n), dim3(kThreadsH), 0, st, d, grid, n);
     return hipGetLastError();
 }
 
@@ -89,7 +95,8 @@ inline hipError_t launch_h_k(const BlockDesc& d, const ItemGrid& grid, int n, hi
 template <int XT, int CT, int PR>
 inline hipError_t launch_h_pr(const BlockDesc& d, const ItemGrid& grid, int n, hipStream_t st) {
     if constexpr (PR == PR_VOLT) return launch_h_k<XT, CT, PR, 1>(d, grid, n, st);
-    else switch (d.t_int) {
+    else switch (d.order == 0 ? 0 : d.t_int) {
+        case 0: return launch_h_k<XT, CT, PR, 0>(d, grid, n, st);     // the final order, any t_int
         case 1: return launch_h_k<XT, CT, PR, 1>(d, grid, n, st);
         case 2: return launch_h_k<XT, CT, PR, 2>(d, grid, n, st);
         case 4: return launch_h_k<XT, CT, PR, 4>(d, grid, n, st);

@@ -113,7 +113,7 @@ LBF_INLINE uint32_t residual_i16x2(uint32_t w) {
 }
 
 // Stokes or voltages of one tile out of scaled accumulators (weights times
-// 2^sc): as stokes_store_cm / volt_store_cm, with the scale taken out exactly
+// 2^sc): as stokes_store_tile / volt_store_cm, with the scale taken out exactly
 template <int PR, int TI>
 LBF_INLINE void split_stokes_store(const floatx16 (&acc)[4], __amdgpu_buffer_rsrc_t rs, const BlockDesc& d, int c,
                                    int beam, int t0, int h, bool ok, int sc) {
@@ -128,7 +128,8 @@ LBF_INLINE void split_stokes_store(const floatx16 (&acc)[4], __amdgpu_buffer_rsr
 #pragma unroll
         for (int q = 0; q < (PR == PR_IQUV ? 4 : 1); ++q) v[q] = __builtin_amdgcn_ldexpf(v[q], -2 * sc);
         const int tq = tq0 + o;
-        stokes_store_row<PR>(v, rs, d, c, T2, tq, beam, ok && tq < T2);
+        if (d.order == 0) stokes_store_row<PR, true>(v, rs, d, c, T2, tq, beam, ok && tq < T2);      // uniform
+        else stokes_store_row<PR, false>(v, rs, d, c, T2, tq, beam, ok && tq < T2);
         __builtin_amdgcn_sched_barrier(0);                     // one period's temporaries at a time
     }
 }

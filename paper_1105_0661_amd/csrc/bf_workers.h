@@ -59,7 +59,7 @@ LBF_INLINE void stage_weights_f32_planes(float* pl, const BlockDesc& d, int c, i
     }
 }
 
-template <int XT, int PR, int TI>
+template <int XT, int PR, int TI, bool FINAL>
 LBF_INLINE void item_f32_fast(const BlockDesc& d, int item, const ItemGrid& grid, float* pl) {
     typedef Raw<XT> R;
     typedef typename R::type RT;
@@ -80,7 +80,7 @@ LBF_INLINE void item_f32_fast(const BlockDesc& d, int item, const ItemGrid& grid
     const int ngrp = min(8, ((S + 7) / 8 + 1) & ~1);
     const uint32_t stride_bytes = (uint32_t)((size_t)d.C * T * BYTES);
     const int T2 = PR == PR_VOLT ? T : T / TI;
-    const __amdgpu_buffer_rsrc_t ors = PR == PR_VOLT ? channel_rsrc(d, c, out_channel_bytes(d, PR, T2)) : stokes_rsrc(d, c, PR, T2);
+    const __amdgpu_buffer_rsrc_t ors = FINAL ? stokes_rsrc(d, c, PR, T2) : channel_rsrc(d, c, out_channel_bytes(d, PR, T2));
     const int trow = tile_row_sample(r);
 
     stage_weights_f32_planes(pl, d, c, b0);
@@ -175,7 +175,7 @@ LBF_INLINE void item_f32_fast(const BlockDesc& d, int item, const ItemGrid& grid
                 float v[4];
                 stokes_from_sums<PR>(sm[o], v);
                 const int tq = tq0 + o;
-                stokes_store_row<PR>(v, ors, d, c, T2, tq, beam, okprev && beam < B && tq < T2);
+                stokes_store_row<PR, FINAL>(v, ors, d, c, T2, tq, beam, okprev && beam < B && tq < T2);
             }
         }
     };
@@ -183,7 +183,7 @@ LBF_INLINE void item_f32_fast(const BlockDesc& d, int item, const ItemGrid& grid
         const int tile = tile_of(klast);
         const bool ok = klast >= 0 && beam < B;
         if (PR == PR_VOLT) volt_store_cm(prev, ors, T, beam, tile * kTile, h, ok);
-        else stokes_store_cm<PR, TI>(prev, ors, d, c, T2, beam, tile * kTile, h, ok);
+        else stokes_store_tile<PR, TI, FINAL>(prev, ors, d, c, T2, beam, tile * kTile, h, ok);
     };
 
     load_quad(0, 0, 0);
@@ -381,6 +381,7 @@ template <int XT, int CT, int PR, int TI, int NK, int NS, bool INC = false>
 LBF_INLINE void item_h_fast(const BlockDesc& d, int item, const ItemGrid& grid, uint32_t* at) {
     typedef typename MfmaH<CT>::vec V;
     constexpr int NBT = 8 / NS;                            // beam tiles per item
+    constexpr bool FINAL = PR != PR_VOLT && TI == 0;       // any t_int, straight into the final order
     typedef TileLoader<XT, CT, NK, NS> Loader;
     constexpr int CPT = Loader::CPT;                       // chunks per thread per step
     // item = (channel, beam group, segment of sample tiles: seg_tiles)
@@ -397,8 +398,8 @@ LBF_INLINE void item_h_fast(const BlockDesc& d, int item, const ItemGrid& grid, 
     // the matrix pipe to itself
     const bool idle = d.b0 + (bg * NBT + bt) * kTile >= d.b1;
     const int nsteps = (ntiles + NS - 1) / NS;
-    const int T2 = PR == PR_VOLT ? T : T / TI;
-    const __amdgpu_buffer_rsrc_t ors = PR == PR_VOLT ? channel_rsrc(d, c, out_channel_bytes(d, PR, T2)) : stokes_rsrc(d, c, PR, T2);
+    const int ti = TI ? TI : d.t_int, T2 = PR == PR_VOLT ? T : T / ti;
+    const __amdgpu_buffer_rsrc_t ors = FINAL ? stokes_rsrc(d, c, PR, T2) : channel_rsrc(d, c, out_channel_bytes(d, PR, T2));
 
     Loader ld;
     ld.init(d, ip);
@@ -435,7 +436,7 @@ LBF_INLINE void item_h_fast(const BlockDesc& d, int item, const ItemGrid& grid, 
                 wi[kk][i] = swap16(v[i]);
             }
         };
-        if (nsteps >= kRowSteps) {
+        if (h_weight_rows(NK, NS) && nsteps >= kRowSteps) {
             constexpr int NBEAM = NBT * kTile, WROW = 8 * NK + 4;   // words per row: 4 mod 8, rows spread over the banks
             const int row = h_weight_row(tid, 0), s4 = h_weight_station(tid);
             u32x4 w[NBEAM / 32];
@@ -480,8 +481,8 @@ LBF_INLINE void item_h_fast(const BlockDesc& d, int item, const ItemGrid& grid, 
     // two accumulator sets, unless the loaders' registers leave no room
     // (complex int16 with several streams, more than two chunks per thread) or
     // there is no arithmetic to overlap (voltages)
-    constexpr bool PIPE = !(XT == XT_CI16 && NS >= 2) && CPT <= 2 && PR != PR_VOLT;
-    constexpr int NOUT = PR == PR_VOLT ? 1 : 16 / TI;
+    constexpr bool PIPE = !(XT == XT_CI16 && NS >= 2) && CPT <= 2 && PR != PR_VOLT && !FINAL;
+    constexpr int NOUT = PR == PR_VOLT || FINAL ? 1 : 16 / TI;
 
     // incoherent beam of the item's tiles (INC form, first beam group only)
     constexpr int SPW = 8 * NK / NBT;                      // stations per wave of a stream
@@ -525,13 +526,14 @@ LBF_INLINE void item_h_fast(const BlockDesc& d, int item, const ItemGrid& grid, 
             for (int q = 0; q < 4; ++q) v[q] += p[q];
         }
 #pragma unroll
-        for (int m = 1; m < TI; m <<= 1)
+        for (int m = 1; m < 16; m <<= 1)
+            if (m < ti)                                    // uniform
 #pragma unroll
-            for (int q = 0; q < 4; ++q) v[q] += __shfl_xor(v[q], m, kWave);
+                for (int q = 0; q < 4; ++q) v[q] += __shfl_xor(v[q], m, kWave);
         float o[4];
         stokes_from_sums<PR_IQUV>(v, o);                   // I, Q, U, V from |X|^2, |Y|^2, X conj(Y)
-        const int tq = (tile * kTile + r) / TI;
-        if (h == 0 && (r & (TI - 1)) == 0 && tq < T2) {
+        const int tq = (tile * kTile + r) / ti;
+        if (h == 0 && (r & (ti - 1)) == 0 && tq < T2) {
             constexpr int K = PR == PR_IQUV ? 4 : 1;
 #pragma unroll
             for (int kk = 0; kk < K; ++kk) d.inc[((size_t)kk * T2 + tq) * d.C + c] = o[kk];
@@ -568,7 +570,7 @@ LBF_INLINE void item_h_fast(const BlockDesc& d, int item, const ItemGrid& grid, 
             // epilogue slice: samples [16 kk / NK, 16 (kk + 1) / NK) of the previous tile
 #pragma unroll
             for (int smp = 16 * kk / NK; smp < 16 * (kk + 1) / NK; ++smp) {
-                stokes_add<PR>(prev, smp, sm[smp / TI]);
+                stokes_add<PR>(prev, smp, sm[smp * NOUT / 16]);
             }
             if (kk >= NK - 2) {                              // stage step k+1's samples
 #pragma unroll
@@ -590,13 +592,13 @@ LBF_INLINE void item_h_fast(const BlockDesc& d, int item, const ItemGrid& grid, 
             __builtin_amdgcn_sched_barrier(0);
         }
         if (PR != PR_VOLT) {
-            const int tq0 = (tprev * kTile + 16 * h) / TI;
+            const int tq0 = (tprev * kTile + 16 * h) / ti;
 #pragma unroll
             for (int o = 0; o < NOUT; ++o) {
                 float v[4];
                 stokes_from_sums<PR>(sm[o], v);
                 const int tq = tq0 + o;
-                stokes_store_row<PR>(v, ors, d, c, T2, tq, beam, okprev && tq < T2);
+                stokes_store_row<PR, FINAL>(v, ors, d, c, T2, tq, beam, okprev && tq < T2);
             }
         }
         __syncthreads();
@@ -618,7 +620,14 @@ LBF_INLINE void item_h_fast(const BlockDesc& d, int item, const ItemGrid& grid, 
             volt_store_rows(prev, reinterpret_cast<float*>(at + h_lds_words(NK, NS)) + wave * kVoltWords, ors, T, beam - r, bend,
                             tile * kTile, klast >= 0 && tile < tile_lo + ntiles, 0);
         else if constexpr (PR == PR_VOLT) volt_store_cm(prev, ors, T, beam, tile * kTile, h, ok);
-        else stokes_store_cm<PR, TI>(prev, ors, d, c, T2, beam, tile * kTile, h, ok);
+        else if constexpr (!FINAL) stokes_store_tile<PR, TI, false>(prev, ors, d, c, T2, beam, tile * kTile, h, ok);
+        else switch (ti) {                                       // uniform
+            case 1: stokes_store_tile<PR, 1, true>(prev, ors, d, c, T2, beam, tile * kTile, h, ok); break;
+            case 2: stokes_store_tile<PR, 2, true>(prev, ors, d, c, T2, beam, tile * kTile, h, ok); break;
+            case 4: stokes_store_tile<PR, 4, true>(prev, ors, d, c, T2, beam, tile * kTile, h, ok); break;
+            case 8: stokes_store_tile<PR, 8, true>(prev, ors, d, c, T2, beam, tile * kTile, h, ok); break;
+            default: stokes_store_tile<PR, 16, true>(prev, ors, d, c, T2, beam, tile * kTile, h, ok); break;
+        }
     };
 
 #pragma unroll
