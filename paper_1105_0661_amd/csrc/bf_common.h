@@ -676,13 +676,24 @@ __host__ __device__ inline int fast_h_ksteps(int S) { return S <= 32 ? 4 : (S + 
 // Voltages of more beams than this take at most 2 sample streams, whose tiles
 // leave LDS for volt_store_rows; fewer take 4 where Stokes would, and store
 // straight from the lanes: there the loads bound the block, and a store
-// touches only the lanes' beams.  2 streams against 4, ci8, 52 stations, 932
-// channels x 1356 samples: 2 beams 214 / 141 us, 8 217 / 167, 16 219 / 203, 32
-// 256 / 310; 64 stations, 512 x 3072: 8 beams 243 / 257, 16 250 / 294; ci16,
-// 40 stations: 8 beams 197 / 191, 16 209 / 238.
+// touches only the lanes' beams.  A block of 3 or 4 tiles is one step of 4
+// streams, and keeps them for longer.  2 streams against 4, F16, blocks of 0.2
+// GB: ci8, 16 / 18 / 20 / 22 beams of 1536 samples: 30 stations 62 / 62 / 63 /
+// 62 against 55 / 57 / 60 / 63 us, 64 stations 57 / 56 / 56 / 56 against 51 /
+// 50 / 51 / 52; ci16, 14 / 16 / 18 / 20 beams: 30 stations 62 / 63 / 45 / 45
+// against 54 / 57 / 47 / 49, 40 stations 49 / 49 / 49 / 49 against 45 / 47 / 48
+// / 50; 128 samples of 40 stations, 20 / 24 beams: ci16 66 / 61 against 55 /
+// 53, ci8 80 / 57 against 64 / 53 (64 samples, 24 beams 70 against 85).
 inline int volt_straight_beams(const BlockDesc& d) {
-    return d.xtype == XT_CI8 && fast_h_ksteps(d.S) < 8 ? 16 : 8;
+    if (d.T > 2 * kTile && d.T <= 4 * kTile) return 24;
+    return d.xtype == XT_CI8 ? 20 : 16;
 }
+
+// Voltages of at most this many beams are stored straight from the lanes with
+// 2 streams too (complex int16 of 41 stations and more never has 4): F16, 53
+// stations, 4096 channels x 384 samples, 1 / 3 / 6 / 9 beams 224 / 229 / 245 /
+// 257 us straight, 244 / 246 / 250 / 255 through rows.
+constexpr int kVoltFewBeams = 6;
 
 // Sample streams of the fast FP16/BF16 worker, the tile shape of its work
 // items: 1, 2 or 4 streams of 32-sample tiles beside 8, 4 or 2 beam tiles of

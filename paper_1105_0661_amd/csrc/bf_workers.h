@@ -616,10 +616,11 @@ LBF_INLINE void item_h_fast(const BlockDesc& d, int item, const ItemGrid& grid, 
     auto final_epilogue = [&](const floatx16 (&prev)[4], int klast) {
         const int tile = tile_lo + sigma + NS * klast;
         const bool ok = klast >= 0 && tile < tile_lo + ntiles && beam < bend;
-        if constexpr (PR == PR_VOLT && NS <= 2)
+        if (PR == PR_VOLT && (NS > 2 || bend - d.b0 <= kVoltFewBeams))    // uniform
+            volt_store_cm(prev, ors, T, beam, tile * kTile, h, ok);
+        else if constexpr (PR == PR_VOLT)
             volt_store_rows(prev, reinterpret_cast<float*>(at + h_lds_words(NK, NS)) + wave * kVoltWords, ors, T, beam - r, bend,
                             tile * kTile, klast >= 0 && tile < tile_lo + ntiles, 0);
-        else if constexpr (PR == PR_VOLT) volt_store_cm(prev, ors, T, beam, tile * kTile, h, ok);
         else if constexpr (!FINAL) stokes_store_tile<PR, TI, false>(prev, ors, d, c, T2, beam, tile * kTile, h, ok);
         else switch (ti) {                                       // uniform
             case 1: stokes_store_tile<PR, 1, true>(prev, ors, d, c, T2, beam, tile * kTile, h, ok); break;
