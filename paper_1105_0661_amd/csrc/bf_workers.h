@@ -540,7 +540,10 @@ LBF_INLINE void item_h_fast(const BlockDesc& d, int item, const ItemGrid& grid, 
         }
     };
     auto step = [&](int k, floatx16 (&acc)[4], const floatx16 (&prev)[4]) {
-        load_chunks(k + 1);
+        // the last step neither loads nor stages: 16384 channels of ci8, 12
+        // stations, 64 samples, 34 beams 179 -> 162 us
+        const bool more = k + 1 < nsteps;                    // uniform
+        if (more) load_chunks(k + 1);
         int rowx = (sigma * 2 + (k & 1)) * kATileWords + 2 * trow * kARow;
         __asm__ volatile("" : "+v"(rowx));
         const uint32_t* ax0 = at + rowx;
@@ -572,7 +575,7 @@ LBF_INLINE void item_h_fast(const BlockDesc& d, int item, const ItemGrid& grid, 
             for (int smp = 16 * kk / NK; smp < 16 * (kk + 1) / NK; ++smp) {
                 stokes_add<PR>(prev, smp, sm[smp * NOUT / 16]);
             }
-            if (kk >= NK - 2) {                              // stage step k+1's samples
+            if (kk >= NK - 2 && more) {                      // stage step k+1's samples
 #pragma unroll
                 for (int i = 0; i < CPT; ++i)
                     if (i % 2 == kk - (NK - 2)) store_chunk(k + 1, i);
@@ -605,10 +608,12 @@ LBF_INLINE void item_h_fast(const BlockDesc& d, int item, const ItemGrid& grid, 
     };
     // the step of an idle wave: the loaders' and the incoherent beam's share only
     auto idle_step = [&](int k) {
-        load_chunks(k + 1);
+        const bool more = k + 1 < nsteps;
+        if (more) load_chunks(k + 1);
         if (INC && inc_on) inc_partial(k);
 #pragma unroll
-        for (int i = 0; i < CPT; ++i) store_chunk(k + 1, i);
+        for (int i = 0; i < CPT; ++i)
+            if (more) store_chunk(k + 1, i);
         if (INC && inc_on) inc_finish(k - 1);
         __syncthreads();
     };
@@ -642,20 +647,21 @@ LBF_INLINE void item_h_fast(const BlockDesc& d, int item, const ItemGrid& grid, 
 #pragma unroll
         for (int q = 0; q < 4; ++q) acc[q] = zero16();
         u32x4 rr[2][CPT];
-        load_chunks_to(1, rr[1]);
         // waves 4-7 (the second wave of each SIMD) run a tile's epilogue at
         // the start of the next step, so that on every SIMD one wave's
         // epilogue (VALU) meets the other wave's MFMAs
         const bool late = wave >= 4;
-        auto plain_step = [&](int k, u32x4 (&mine)[CPT], u32x4 (&next)[CPT]) {
-            load_chunks_to(k + 2, mine);                       // mine held step k's samples, now in LDS
+        // after: steps that follow, as far as it matters (a compile-time 0, 1 or 2)
+        auto plain_step = [&](int k, u32x4 (&mine)[CPT], u32x4 (&next)[CPT], auto after) {
+            if (after == 2) load_chunks_to(k + 2, mine);        // mine held step k's samples, now in LDS
             if (idle) {
                 if (INC && inc_on) {
                     inc_finish(k - 1);
                     inc_partial(k);
                 }
 #pragma unroll
-                for (int i = 0; i < CPT; ++i) store_chunk_from(k + 1, i, next);
+                for (int i = 0; i < CPT; ++i)
+                    if (after > 0) store_chunk_from(k + 1, i, next);
                 __syncthreads();
                 return;
             }
@@ -680,15 +686,37 @@ LBF_INLINE void item_h_fast(const BlockDesc& d, int item, const ItemGrid& grid, 
             }
             if (!late) final_epilogue(acc, k);
 #pragma unroll
-            for (int i = 0; i < CPT; ++i) store_chunk_from(k + 1, i, next);
+            for (int i = 0; i < CPT; ++i)
+                if (after > 0) store_chunk_from(k + 1, i, next);
             __syncthreads();
         };
-        int k = 0;
-        for (; k + 1 < nsteps; k += 2) {
-            plain_step(k, rr[0], rr[1]);
-            plain_step(k + 1, rr[1], rr[0]);
+        // Items of one and two steps on paths of their own, without the loads
+        // and stages nothing follows: 16384 channels of ci16, 15 stations, 64
+        // samples, 108 beams 168 -> 152 us, 8 stations, 192 samples, 4 beams 288
+        // -> 253 (not beside the longer epilogues of a shorter t_int, where the
+        // steps' share is less).  Conditions around the loads of the loop
+        // instead make every step wait for all loads in flight (6900
+        // channels of ci8, 19 stations, 1536 samples, 7 beams as voltages 726 ->
+        // 827 us).
+        typedef std::integral_constant<int, 0> After0;
+        typedef std::integral_constant<int, 1> After1;
+        typedef std::integral_constant<int, 2> After2;
+        constexpr bool SHORT = PR == PR_VOLT || TI == 16;
+        if (SHORT && nsteps == 1) {
+            plain_step(0, rr[0], rr[1], After0{});
+        } else if (SHORT && nsteps == 2) {
+            load_chunks_to(1, rr[1]);
+            plain_step(0, rr[0], rr[1], After1{});
+            plain_step(1, rr[1], rr[0], After0{});
+        } else {
+            load_chunks_to(1, rr[1]);
+            int k = 0;
+            for (; k + 1 < nsteps; k += 2) {
+                plain_step(k, rr[0], rr[1], After2{});
+                plain_step(k + 1, rr[1], rr[0], After2{});
+            }
+            if (k < nsteps) plain_step(k, rr[0], rr[1], After2{});
         }
-        if (k < nsteps) plain_step(k, rr[0], rr[1]);
         if (late && !idle) final_epilogue(acc, nsteps - 1);
         if (INC && inc_on) inc_finish(nsteps - 1);
         return;
