@@ -311,8 +311,9 @@ hipError_t launch_stokes(const float* y, int B, int C, int T, int product, int t
     const floatx4* yy = reinterpret_cast<const floatx4*>(y);
     // the flat kernel where a period lies in one wave and one channel; it wins
     // at every size (1.3x at 1.6 GB, no index divisions on small arrays either)
+    // that its grid, of fewer than 2^32 threads, covers (256 GiB of voltages)
     const size_t nflat = (size_t)C * B * T, bflat = (nflat + 1023) / 1024;
-    if (f_int == 1 && (t_int & (t_int - 1)) == 0 && t_int <= kWave && bflat < (1u << 31)) {
+    if (f_int == 1 && (t_int & (t_int - 1)) == 0 && t_int <= kWave && bflat <= 0xffffffffu / 256) {
         if (product == PR_IQUV) launch_stokes_flat<4>(__builtin_ctz(t_int), dim3((unsigned)bflat), st, yy, nflat, s);
         else launch_stokes_flat<1>(__builtin_ctz(t_int), dim3((unsigned)bflat), st, yy, nflat, s);
         return hipGetLastError();
