@@ -10,6 +10,6 @@ hipError_t launch_fast_f32(const BlockDesc& d, hipStream_t st) {
     if (d.xtype == XT_CI16) return launch_split_ci16(d, st);
     ItemGrid grid;
     const int n = block_items_fast_f32(d, &grid);
-    return launch_f32_xt<XT_CF32>(d, grid, n, st);
+    return launch_f32(d, grid, n, st);
 }
 }  // namespace lbf

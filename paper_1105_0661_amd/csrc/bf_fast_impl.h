@@ -7,10 +7,10 @@
 namespace lbf {
 
 // 8 waves, two per SIMD; LDS: the three weight planes of 128 beams
-template <int XT, int PR, int TI, bool FINAL>
+template <int PR, int TI, bool FINAL>
 __global__ __launch_bounds__(kThreadsH) void bf_f32_fast_kernel(BlockDesc d, ItemGrid grid, int nitems) {
     __shared__ __attribute__((aligned(16))) float pl[3 * kPlaneWords];
-    item_f32_fast<XT, PR, TI, FINAL>(d, xcd_remap(blockIdx.x, nitems), grid, pl);
+    item_f32_fast<PR, TI, FINAL>(d, xcd_remap(blockIdx.x, nitems), grid, pl);
 }
 
 // 8 waves, two per SIMD; LDS: NS streams x 2 buffers of one A tile (and the
@@ -23,35 +23,34 @@ __global__ __launch_bounds__(kThreadsH) void bf_h_fast_kernel(BlockDesc d, ItemG
 }
 
 // launch one instantiation; PR/TI/NK chosen from the block by the callers
-template <int XT, int PR, int TI>
+template <int PR, int TI>
 inline hipError_t launch_f32_k(const BlockDesc& d, const ItemGrid& grid, int n, hipStream_t st) {
     if constexpr (PR != PR_VOLT) {
         if (d.order == 0) {
-            hipLaunchKernelGGL((bf_f32_fast_kernel<XT, PR, TI, true>), dim3(n), dim3(kThreadsH), 0, st, d, grid, n);
+            hipLaunchKernelGGL((bf_f32_fast_kernel<PR, TI, true>), dim3(n), dim3(kThreadsH), 0, st, d, grid, n);
             return hipGetLastError();
         }
     }
-    hipLaunchKernelGGL((bf_f32_fast_kernel<XT, PR, TI, false>), dim3(n), dim3(kThreadsH), 0, st, d, grid, n);
+    hipLaunchKernelGGL((bf_f32_fast_kernel<PR, TI, false>), dim3(n), dim3(kThreadsH), 0, st, d, grid, n);
     return hipGetLastError();
 }
 
-template <int XT, int PR>
+template <int PR>
 inline hipError_t launch_f32_pr(const BlockDesc& d, const ItemGrid& grid, int n, hipStream_t st) {
-    if constexpr (PR == PR_VOLT) return launch_f32_k<XT, PR, 1>(d, grid, n, st);
+    if constexpr (PR == PR_VOLT) return launch_f32_k<PR, 1>(d, grid, n, st);
     else switch (d.t_int) {
-        case 1: return launch_f32_k<XT, PR, 1>(d, grid, n, st);
-        case 2: return launch_f32_k<XT, PR, 2>(d, grid, n, st);
-        case 4: return launch_f32_k<XT, PR, 4>(d, grid, n, st);
-        case 8: return launch_f32_k<XT, PR, 8>(d, grid, n, st);
-        default: return launch_f32_k<XT, PR, 16>(d, grid, n, st);
+        case 1: return launch_f32_k<PR, 1>(d, grid, n, st);
+        case 2: return launch_f32_k<PR, 2>(d, grid, n, st);
+        case 4: return launch_f32_k<PR, 4>(d, grid, n, st);
+        case 8: return launch_f32_k<PR, 8>(d, grid, n, st);
+        default: return launch_f32_k<PR, 16>(d, grid, n, st);
     }
 }
 
-template <int XT>
-inline hipError_t launch_f32_xt(const BlockDesc& d, const ItemGrid& grid, int n, hipStream_t st) {
-    if (d.product == PR_VOLT) return launch_f32_pr<XT, PR_VOLT>(d, grid, n, st);
-    if (d.product == PR_I) return launch_f32_pr<XT, PR_I>(d, grid, n, st);
-    return launch_f32_pr<XT, PR_IQUV>(d, grid, n, st);
+inline hipError_t launch_f32(const BlockDesc& d, const ItemGrid& grid, int n, hipStream_t st) {
+    if (d.product == PR_VOLT) return launch_f32_pr<PR_VOLT>(d, grid, n, st);
+    if (d.product == PR_I) return launch_f32_pr<PR_I>(d, grid, n, st);
+    return launch_f32_pr<PR_IQUV>(d, grid, n, st);
 }
 
 template <int XT, int CT, int PR, int TI, int NS, bool INC>

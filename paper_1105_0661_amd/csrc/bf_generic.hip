@@ -1,7 +1,6 @@
 // bf_generic.hip -- contraction workers for any station count and input type
-// (stations in chunks of 64 whose weights are restaged in LDS per tile).  The
-// fast workers in bf_fast.hip cover up to 64 stations of complex int8/int16;
-// these cover the rest (more stations, complex float32 input).
+// (stations in chunks of 64 whose weights are restaged in LDS per tile): what
+// the fast workers do not take (fast_path).
 #include "bf_common.h"
 #include "bf_workers.h"
 

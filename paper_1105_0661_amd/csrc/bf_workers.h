@@ -3,7 +3,7 @@
 // Fast workers (up to 64 stations, t_int <= 16, no channel integration):
 // item_f32_fast and item_h_fast, described where they are defined, and
 // item_f32_split (bf_split_worker.h); they write Stokes products
-// channel-major.
+// channel-major, or a small block's into the final order.
 //
 // Generic workers (any station count, any integration): work item = (channel group of f_int channels,
 // group of up to 128 beams).  A work group of 4 waves stages that beam group's
@@ -22,7 +22,7 @@ namespace lbf {
 // fast workers: up to 64 stations
 // ===========================================================================
 
-// FP32 operands and complex float samples (MFMA 32x32x2 f32: one station per
+// FP32 operands, complex float samples (MFMA 32x32x2 f32: one station per
 // MFMA, K = (re, im)); integer samples take bf_split_worker.h's worker.
 //
 // A work item is one channel, 128 beams and a segment of sample tiles
@@ -59,11 +59,10 @@ LBF_INLINE void stage_weights_f32_planes(float* pl, const BlockDesc& d, int c, i
     }
 }
 
-template <int XT, int PR, int TI, bool FINAL>
+template <int PR, int TI, bool FINAL>
 LBF_INLINE void item_f32_fast(const BlockDesc& d, int item, const ItemGrid& grid, float* pl) {
-    typedef Raw<XT> R;
-    typedef typename R::type RT;
-    constexpr int BYTES = sizeof(RT);
+    typedef Raw<XT_CF32> R;
+    constexpr int BYTES = sizeof(R::type);
     constexpr int NOUT = PR == PR_VOLT ? 1 : 16 / TI;
     const int T = d.T, S = d.S, B = d.B;
     const ItemPos ip = item_pos(d, grid, item, kBeamGroup);
@@ -90,22 +89,18 @@ LBF_INLINE void item_f32_fast(const BlockDesc& d, int item, const ItemGrid& grid
     int wro = (h ? kPlaneWords : 0) + (bt * kTile + r) * kWRow;
     int wio = (h ? 0 : 2 * kPlaneWords) + (bt * kTile + r) * kWRow;
     __asm__ volatile("" : "+v"(wro), "+v"(wio));
-    // bit offset of this lane half's component in a raw sample word
-    uint32_t hsh = (uint32_t)h * (XT == XT_CI8 ? 8u : 16u);
-    __asm__ volatile("" : "+v"(hsh));
-
     auto tile_of = [&](int k) { return tile_lo + ts + 2 * k; };
     // Two-deep ring of 8-station groups: group n of the wave's sequence
     // (tile n / ngrp, group n % ngrp) lands in slot n % 2 two groups before
     // it is used, which covers a cache-missing load.
-    RT ring[2][8];
+    R::type ring[2][8];
     auto load_quad = [&](int slot, int q4, int n) {            // stations 4 q4 .. 4 q4 + 3 of group n
         const int k = min(n / ngrp, nmine - 1), g = n % ngrp;
         const int t = min(tile_of(k) * kTile + trow, T - 1);
         const __amdgpu_buffer_rsrc_t rs = group_rsrc(d.x, 8 * g, S, stride_bytes);
 #pragma unroll
         for (int i = 4 * q4; i < 4 * q4 + 4; ++i)
-            ring[slot][i] = buffer_sample<XT>(rs, sample_off(i, stride_bytes, c, T, t, BYTES));
+            ring[slot][i] = buffer_sample<XT_CF32>(rs, sample_off(i, stride_bytes, c, T, t, BYTES));
     };
     auto epi_sample = [&](const floatx16 (&prev)[4], int tprev, bool okprev, int smp, float (&sm)[NOUT][4]) {
         if (PR == PR_VOLT) {
@@ -143,7 +138,7 @@ LBF_INLINE void item_f32_fast(const BlockDesc& d, int item, const ItemGrid& grid
                     const int s4 = 8 * gi + 4 * i4;
                     float ax[4], ay[4];
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) R::half(ring[gi & 1][4 * i4 + i], hsh, ax[i], ay[i]);
+                    for (int i = 0; i < 4; ++i) R::half(ring[gi & 1][4 * i4 + i], h, ax[i], ay[i]);
                     load_quad(gi & 1, i4, k * ngrp + gi + 2);
                     __builtin_amdgcn_sched_barrier(0);                     // the refill issues before the MFMAs
                     const floatx4 br = *reinterpret_cast<const floatx4*>(pl + wro + s4);
