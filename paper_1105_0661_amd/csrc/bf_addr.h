@@ -121,13 +121,18 @@ LBF_HD uint32_t weight_range(const BlockDesc& d, int bytes) { return (uint32_t)d
 LBF_HD uint32_t weight_off(int beam, int S, int s, int bytes) { return ((uint32_t)beam * S + s) * (uint32_t)bytes; }
 
 // Station planes of a tile: the descriptor of group_base / group_range moved
-// to sample t of channel c (tile_off bytes into each plane), so that a
-// thread's offset, station and sample within the tile, is the same for every
-// tile and channel.
-LBF_HD uint32_t tile_off(int c, int T, int t, int bytes) { return (uint32_t)(c * T + t) * (uint32_t)bytes; }
-LBF_HD uint32_t tile_range(int s0, int S, uint32_t stride_bytes, uint32_t off) {
-    const uint32_t r = group_range(s0, S, stride_bytes);
-    return r == 0 ? 0 : r - off;
+// to channel c (channel_off bytes into each plane) and to sample t of it
+// (tile_off further), so that a thread's offset, station and sample within the
+// tile, is the same for every tile and channel.  What remains of the range is
+// kept signed: past the stations it is negative, and a range of none.
+LBF_HD uint32_t channel_off(int c, int T, int bytes) { return (uint32_t)(c * T) * (uint32_t)bytes; }
+LBF_HD uint32_t tile_off(int t, int bytes) { return (uint32_t)t * (uint32_t)bytes; }
+LBF_HD int channel_limit(int s0, int S, uint32_t stride_bytes, uint32_t coff) {
+    return (int)group_range(s0, S, stride_bytes) - (int)coff;
+}
+LBF_HD uint32_t tile_range(int limit, uint32_t toff) {
+    const int r = limit - (int)toff;
+    return r > 0 ? (uint32_t)r : 0u;
 }
 
 // The sample loaders of the workers that stage tiles in LDS: a tile's 16-byte

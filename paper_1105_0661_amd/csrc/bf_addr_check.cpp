@@ -153,9 +153,11 @@ void walk_h(Walk& w, const BlockDesc& d, int lo, int hi) {
                 for (int i = 0; i < CPT; ++i) {
                     const int n = chunk_group(wave, i, CPS), sg = n / NK, s = chunk_station(wave, lane, CPS), s0 = 8 * (n % NK);
                     const int t = stream_tile(sg, k, NS, ip.tile_lo, ip.ntiles) * kTile, q = chunk_q(lane, CPS);
-                    const uint32_t off = tile_off(ip.c, d.T, t, bytes);
-                    if (off != ((uint64_t)ip.c * d.T + t) * bytes) return w.fail("the tile's offset wraps");
-                    w.access("sample load", group_base(s0, stride) + off, tile_range(s0, d.S, stride, off),
+                    const uint32_t coff = channel_off(ip.c, d.T, bytes), toff = tile_off(t, bytes);
+                    if ((uint64_t)coff + toff != ((uint64_t)ip.c * d.T + t) * bytes || coff + (uint64_t)toff >= 1ull << 31)
+                        return w.fail("the tile's offset wraps");
+                    w.access("sample load", group_base(s0, stride) + coff + toff,
+                             tile_range(channel_limit(s0, d.S, stride, coff), toff),
                              (uint64_t)s * stride64 + 16u * q, chunk_off(s, q, stride), 16, xbuf, false);
                 }
             for (int k = 0; k < nsteps; ++k) {
@@ -199,9 +201,11 @@ void walk_split(Walk& w, const BlockDesc& d, int lo, int hi) {
                 for (int i = 0; i < CPT; ++i) {
                     const int n = chunk_group(wave, i, CPS), sg = n / NK, s = chunk_station(wave, lane, CPS), s0 = 8 * (n % NK);
                     const int t = stream_tile(sg, k, NS, ip.tile_lo, ip.ntiles) * kTile, q = chunk_q(lane, CPS);
-                    const uint32_t off = tile_off(ip.c, d.T, t, bytes);
-                    if (off != ((uint64_t)ip.c * d.T + t) * bytes) return w.fail("the tile's offset wraps");
-                    w.access("sample load", group_base(s0, stride) + off, tile_range(s0, d.S, stride, off),
+                    const uint32_t coff = channel_off(ip.c, d.T, bytes), toff = tile_off(t, bytes);
+                    if ((uint64_t)coff + toff != ((uint64_t)ip.c * d.T + t) * bytes || coff + (uint64_t)toff >= 1ull << 31)
+                        return w.fail("the tile's offset wraps");
+                    w.access("sample load", group_base(s0, stride) + coff + toff,
+                             tile_range(channel_limit(s0, d.S, stride, coff), toff),
                              (uint64_t)s * stride64 + 16u * q, chunk_off(s, q, stride), 16, xbuf, false);
                 }
             for (int k = 0; k < nsteps; ++k) {

@@ -293,18 +293,19 @@ struct TileLoader {
     static constexpr int CPT = chunks_per_thread(NS, NK, CPS);
     static constexpr bool EVEN = NS * NK * wave_loads(CPS) % kLoaderWaves == 0;   // every wave has CPT chunks to stage
 
-    const void* x;
-    uint32_t stride_bytes, voff;
-    int S, T, c, tile_lo, ntiles;
-    int g[CPT], sg[CPT];                                   // station group and stream of the wave's chunks (uniform)
+    uint32_t voff;
+    int tile_lo, ntiles;
+    // of the wave's chunks, uniform: station group, stream, the group's planes
+    // at the item's channel and what is left of them
+    int g[CPT], sg[CPT], limit[CPT];
+    uint64_t base[CPT];
     int row, swz;                                          // LDS words of the thread's place in a tile and a group
 
     LBF_INLINE void init(const BlockDesc& d, const ItemPos& ip) {
         const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave;
         const uint32_t q = chunk_q(lane, CPS), s = chunk_station(wave, lane, CPS);
-        x = d.x;
-        S = d.S, T = d.T, c = ip.c, tile_lo = ip.tile_lo, ntiles = ip.ntiles;
-        stride_bytes = (uint32_t)((size_t)d.C * T * BYTES);
+        const uint32_t stride_bytes = (uint32_t)((size_t)d.C * d.T * BYTES), coff = channel_off(ip.c, d.T, BYTES);
+        tile_lo = ip.tile_lo, ntiles = ip.ntiles;
         // waves past the step's chunks load the tile of a later step, which
         // warms the cache for it, and stage nothing
 #pragma unroll
@@ -312,6 +313,8 @@ struct TileLoader {
             const uint32_t n = chunk_group(wave, i, CPS);
             g[i] = n % NK;
             sg[i] = n / NK;
+            base[i] = reinterpret_cast<uint64_t>(d.x) + group_base(8 * g[i], stride_bytes) + coff;
+            limit[i] = channel_limit(8 * g[i], d.S, stride_bytes, coff);
         }
         voff = chunk_off(s, q, stride_bytes);
         row = (int)(2 * q * SPC * kARow + (s & 3));
@@ -323,11 +326,11 @@ struct TileLoader {
     LBF_INLINE void load(int k, u32x4 (&dst)[CPT]) const {
 #pragma unroll
         for (int i = 0; i < CPT; ++i) {
-            const uint32_t off = tile_off(c, T, stream_tile(sg[i], k, NS, tile_lo, ntiles) * kTile, BYTES);
-            const uint64_t base = reinterpret_cast<uint64_t>(x) + group_base(8 * g[i], stride_bytes) + off;
-            const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)base);
-            const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(base >> 32));
-            const uint32_t n = __builtin_amdgcn_readfirstlane(tile_range(8 * g[i], S, stride_bytes, off));
+            const uint32_t off = tile_off(stream_tile(sg[i], k, NS, tile_lo, ntiles) * kTile, BYTES);
+            const uint64_t b = base[i] + off;
+            const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)b);
+            const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(b >> 32));
+            const uint32_t n = __builtin_amdgcn_readfirstlane(tile_range(limit[i], off));
             const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
                 reinterpret_cast<void*>(((uint64_t)hi << 32) | lo), (short)0, (int)n, 0x00020000);
             dst[i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)voff, 0, 0));
