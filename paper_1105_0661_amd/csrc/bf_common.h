@@ -523,6 +523,40 @@ LBF_INLINE void stokes_store_tile(const floatx16 (&acc)[4], __amdgpu_buffer_rsrc
         stokes_from_sums<PR>(sm, v);
         const int tq = tq0 + o;
         stokes_store_row<PR, FINAL>(v, rs, d, c, T2, tq, beam, ok && tq < T2);
+        if (FINAL) __builtin_amdgcn_sched_barrier(0);             // one period's temporaries at a time
+    }
+}
+
+// The same into the final order for any t_int up to 16.  Stokes I in one copy
+// of the code for all: with a copy for each, the BF16 kernels of complex int8
+// spilled 36 to 121 registers; with four parameters one copy spills more than
+// the five.
+template <int PR>
+LBF_INLINE void stokes_store_any(const floatx16 (&acc)[4], __amdgpu_buffer_rsrc_t rs, const BlockDesc& d, int c, int T2,
+                                 int beam, int t0, int h, bool ok) {
+    const int ti = d.t_int;
+    if constexpr (PR == PR_IQUV) {
+        switch (ti) {                                          // uniform
+            case 1: stokes_store_tile<PR, 1, true>(acc, rs, d, c, T2, beam, t0, h, ok); break;
+            case 2: stokes_store_tile<PR, 2, true>(acc, rs, d, c, T2, beam, t0, h, ok); break;
+            case 4: stokes_store_tile<PR, 4, true>(acc, rs, d, c, T2, beam, t0, h, ok); break;
+            case 8: stokes_store_tile<PR, 8, true>(acc, rs, d, c, T2, beam, t0, h, ok); break;
+            default: stokes_store_tile<PR, 16, true>(acc, rs, d, c, T2, beam, t0, h, ok); break;
+        }
+        return;
+    }
+    int tq = (t0 + 16 * h) >> __builtin_ctz(ti);
+    float sm[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+        stokes_add<PR>(acc, k, sm);
+        if (((k + 1) & (ti - 1)) == 0) {                       // uniform
+            float v[4];
+            stokes_from_sums<PR>(sm, v);
+            stokes_store_row<PR, true>(v, rs, d, c, T2, tq, beam, ok && tq < T2);
+            ++tq;
+            sm[0] = 0.f;
+        }
     }
 }
 

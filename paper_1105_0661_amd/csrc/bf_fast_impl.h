@@ -94,8 +94,9 @@ inline hipError_t launch_h_k(const BlockDesc& d, const ItemGrid& grid, int n, hi
 template <int XT, int CT, int PR>
 inline hipError_t launch_h_pr(const BlockDesc& d, const ItemGrid& grid, int n, hipStream_t st) {
     if constexpr (PR == PR_VOLT) return launch_h_k<XT, CT, PR, 1>(d, grid, n, st);
-    else switch (d.order == 0 ? 0 : d.t_int) {
-        case 0: return launch_h_k<XT, CT, PR, 0>(d, grid, n, st);     // the final order, any t_int
+    else switch (d.order == 0 ? (d.t_int == 16 ? -16 : 0) : d.t_int) {
+        case -16: return launch_h_k<XT, CT, PR, -16>(d, grid, n, st);     // the final order
+        case 0: return launch_h_k<XT, CT, PR, 0>(d, grid, n, st);
         case 1: return launch_h_k<XT, CT, PR, 1>(d, grid, n, st);
         case 2: return launch_h_k<XT, CT, PR, 2>(d, grid, n, st);
         case 4: return launch_h_k<XT, CT, PR, 4>(d, grid, n, st);

@@ -379,7 +379,9 @@ template <int XT, int CT, int PR, int TI, int NK, int NS, bool INC = false>
 LBF_INLINE void item_h_fast(const BlockDesc& d, int item, const ItemGrid& grid, uint32_t* at) {
     typedef typename MfmaH<CT>::vec V;
     constexpr int NBT = 8 / NS;                            // beam tiles per item
-    constexpr bool FINAL = PR != PR_VOLT && TI == 0;       // any t_int, straight into the final order
+    // TI: the block's t_int; straight into the final order, 0 for any t_int or -16
+    constexpr bool FINAL = PR != PR_VOLT && TI <= 0;
+    constexpr int TIV = TI < 0 ? -TI : TI;
     typedef TileLoader<XT, CT, NK, NS> Loader;
     constexpr int CPT = Loader::CPT;                       // chunks per thread per step
     // item = (channel, beam group, segment of sample tiles: seg_tiles)
@@ -396,7 +398,7 @@ LBF_INLINE void item_h_fast(const BlockDesc& d, int item, const ItemGrid& grid, 
     // the matrix pipe to itself
     const bool idle = d.b0 + (bg * NBT + bt) * kTile >= d.b1;
     const int nsteps = (ntiles + NS - 1) / NS;
-    const int ti = TI ? TI : d.t_int, T2 = PR == PR_VOLT ? T : T / ti;
+    const int ti = TIV ? TIV : d.t_int, T2 = PR == PR_VOLT ? T : T / ti;
     const __amdgpu_buffer_rsrc_t ors = FINAL ? stokes_rsrc(d, c, PR, T2) : channel_rsrc(d, c, out_channel_bytes(d, PR, T2));
 
     Loader ld;
@@ -479,8 +481,8 @@ LBF_INLINE void item_h_fast(const BlockDesc& d, int item, const ItemGrid& grid, 
     // two accumulator sets, unless the loaders' registers leave no room
     // (complex int16 with several streams, more than two chunks per thread) or
     // there is no arithmetic to overlap (voltages)
-    constexpr bool PIPE = !(XT == XT_CI16 && NS >= 2) && CPT <= 2 && PR != PR_VOLT && !FINAL;
-    constexpr int NOUT = PR == PR_VOLT || FINAL ? 1 : 16 / TI;
+    constexpr bool PIPE = !(XT == XT_CI16 && NS >= 2) && CPT <= 2 && PR != PR_VOLT && TI != 0;
+    constexpr int NOUT = PR == PR_VOLT || TI == 0 ? 1 : 16 / TIV;
 
     // incoherent beam of the item's tiles (INC form, first beam group only)
     constexpr int SPW = 8 * NK / NBT;                      // stations per wave of a stream
@@ -624,14 +626,8 @@ LBF_INLINE void item_h_fast(const BlockDesc& d, int item, const ItemGrid& grid, 
         else if constexpr (PR == PR_VOLT)
             volt_store_rows(prev, reinterpret_cast<float*>(at + h_lds_words(NK, NS)) + wave * kVoltWords, ors, T, beam - r, bend,
                             tile * kTile, klast >= 0 && tile < tile_lo + ntiles, 0);
-        else if constexpr (!FINAL) stokes_store_tile<PR, TI, false>(prev, ors, d, c, T2, beam, tile * kTile, h, ok);
-        else switch (ti) {                                       // uniform
-            case 1: stokes_store_tile<PR, 1, true>(prev, ors, d, c, T2, beam, tile * kTile, h, ok); break;
-            case 2: stokes_store_tile<PR, 2, true>(prev, ors, d, c, T2, beam, tile * kTile, h, ok); break;
-            case 4: stokes_store_tile<PR, 4, true>(prev, ors, d, c, T2, beam, tile * kTile, h, ok); break;
-            case 8: stokes_store_tile<PR, 8, true>(prev, ors, d, c, T2, beam, tile * kTile, h, ok); break;
-            default: stokes_store_tile<PR, 16, true>(prev, ors, d, c, T2, beam, tile * kTile, h, ok); break;
-        }
+        else if constexpr (TI != 0) stokes_store_tile<PR, TIV, FINAL>(prev, ors, d, c, T2, beam, tile * kTile, h, ok);
+        else stokes_store_any<PR>(prev, ors, d, c, T2, beam, tile * kTile, h, ok);
     };
 
 #pragma unroll
